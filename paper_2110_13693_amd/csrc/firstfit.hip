@@ -10,6 +10,342 @@ static __device__ __forceinline__ uint32_t set_lane(uint32_t x, uint32_t v, int 
     return (uint32_t)wo_writelane_i32((int)v, l, (int)x);
 }
 
+// value of a 64-bit lane register pair in lane l (uniform)
+static __device__ __forceinline__ uint64_t lane64(uint32_t lo, uint32_t hi, int l)
+{
+    return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)lo, l) |
+           ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)hi, l) << 32);
+}
+
+// LDS accesses of the (only) wave take effect in program order: the compiler
+// must keep it
+static __device__ __forceinline__ void lds_order() { asm volatile("" ::: "memory"); }
+
+// Tours under seed batching, packed form (SEED_PACKED_ORDERS and
+// SEED_PACKED_LINES above): the same rule as the general form below, with the
+// search for the next order turned from a scan over every position into
+// operations on bit masks.  Lane b holds a 64-bit word of positions 64 b ..
+// 64 b + 63 of every mask: the positions in no tour, the bit planes of the
+// orders' sizes, and the bit planes of their counts of aisles new to the tour.
+// The order that joins next is found from the highest plane of the counts
+// down: the fitting positions whose bit is clear, where there are any, else
+// those whose bit is set; the first position left is the one.  An order that
+// joins with no new aisle changes only the room.  Otherwise every order that
+// visits an aisle it adds loses one new aisle: the aisle's mask of positions is
+// subtracted from the planes of all positions at once.  The aisles of more
+// than SEED_COLD orders (a few dozen, which most of the added aisles are: 290
+// orders on average at the paper scale) keep their mask in memory, 512 bytes;
+// the others keep a list, which becomes a mask in LDS.
+//
+// A chain of about n dependent steps per plan, bound by their latency and
+// issue: the plans in flight set the rate, so LDS holds little (2.4 KB for
+// 400 aisles; the registers allow 16 plans per CU) and the lists, read once per added aisle, stay
+// in L2 and the last-level cache.  4,096 plans of 4,000 orders: 4.66 ms,
+// against 70.6 ms for the general form, which reads every position per step
+// and fits four plans per CU.  With the counts as bytes in LDS, decremented by
+// atomics over the lists: 8.5 ms; with every list kept as a list: 6.6 ms; with
+// a store to memory per join: 5.1 ms.
+static __device__ int seed_tours_packed(const EvalArgs &A, const InstDev &I, const uint16_t *seq, const uint8_t *cnt,
+                                        const uint32_t *zs, uint16_t *tour_of, unsigned char *smem)
+{
+    const int lane = threadIdx.x;
+    const int n = I.n_orders, NA = I.n_aisles;
+    const uint32_t Q = (uint32_t)I.capacity;
+    const SeedPackedLayout L = seed_packed_layout(NA);
+    uint32_t *mask = (uint32_t *)(smem + L.mask);      // a mask of positions, zero between uses
+    uint32_t *aend = (uint32_t *)(smem + L.aend);      // end of each aisle's list of positions; bits 16 and up: 1 + its mask
+    uint32_t *tbits = (uint32_t *)(smem + L.tbits);    // the tour's aisle set
+    unsigned char *scr = A.seed_scr + (int64_t)blockIdx.x * A.seed_stride;
+    uint16_t *fwd = (uint16_t *)scr;                   // a position's first SEED_FWD aisles
+    uint16_t *apos = (uint16_t *)(scr + A.seed_apos);  // positions by aisle
+    uint2 *hot = (uint2 *)(scr + A.seed_hot);          // masks of the longest lists
+    uint32_t *joins = A.ff_queue + (int64_t)blockIdx.x * A.ff_stride;   // every join: position | tour << 16
+    const uint32_t *oo = A.ordoff + I.ordoff_off;
+    const uint32_t *orr = A.ordrec + I.ordrec_off;
+    const uint32_t magic = I.magic;
+    const int n_blk = (n + 63) / 64;
+    const uint32_t n_lines = (uint32_t)I.n_lines;
+
+    auto aisle_of = [&](uint32_t rec) { return mulhi24(rec + zs[rec >> 26], magic); };
+    // the distinct aisles of the order at position q: the first 8 lines in
+    // registers, the rest (rare) one at a time
+    auto for_aisles = [&](int q, auto f) {
+        const uint32_t o = min((uint32_t)seq[q], (uint32_t)(n - 1));
+        const uint32_t l0 = oo[o], len = oo[o + 1] - l0;
+        uint32_t a[8];
+#pragma unroll
+        for (int i = 0; i < 8; i++) a[i] = orr[min(l0 + (uint32_t)i, n_lines - 1u)];
+#pragma unroll
+        for (int i = 0; i < 8; i++) a[i] = (uint32_t)i < len ? aisle_of(a[i]) : 0xFFFFFFFFu;
+#pragma unroll
+        for (int i = 0; i < 8; i++) {
+            bool dup = (uint32_t)i >= len;
+#pragma unroll
+            for (int j = 0; j < i; j++) dup = dup || a[j] == a[i];
+            if (!dup) f(a[i]);
+        }
+        for (uint32_t i = 8; i < len; i++) {
+            const uint32_t x = aisle_of(orr[l0 + i]);
+            bool dup = false;
+            for (uint32_t j = 0; j < i; j++) dup = dup || aisle_of(orr[l0 + j]) == x;
+            if (!dup) f(x);
+        }
+    };
+
+    // ---- the tables -----------------------------------------------------
+    for (int a = lane; a < NA; a += 64) aend[a] = 0u;
+    for (int i = lane; i < 128; i += 64) mask[i] = 0u;
+    __syncthreads();
+    uint32_t free_lo = 0, free_hi = 0;                         // positions in no tour
+    uint32_t k_lo[4] = {0, 0, 0, 0}, k_hi[4] = {0, 0, 0, 0};   // bit planes of the orders' aisle counts
+    uint32_t s_lo[4] = {0, 0, 0, 0}, s_hi[4] = {0, 0, 0, 0};   // bit planes of the sizes
+    uint32_t smax = 1;
+    for (int b = 0; b < n_blk; b++) {
+        const int q = 64 * b + lane;
+        uint32_t k = 0, sz = 0;
+        uint32_t fa[SEED_FWD] = {0xFFFFu, 0xFFFFu, 0xFFFFu, 0xFFFFu};
+        if (q < n) {
+            for_aisles(q, [&](uint32_t a) {
+#pragma unroll
+                for (int i = 0; i < SEED_FWD; i++)
+                    if (k == (uint32_t)i) fa[i] = a;
+                k++;
+                atomicAdd(&aend[a], 1u);
+            });
+            if (k > (uint32_t)SEED_FWD) fa[SEED_FWD - 1] = 0xFFFEu;   // more aisles than the record holds
+            sz = cnt[min((uint32_t)seq[q], (uint32_t)(n - 1))];
+            *(uint2 *)(fwd + SEED_FWD * q) = make_uint2(fa[0] | (fa[1] << 16), fa[2] | (fa[3] << 16));
+        }
+        smax = max(smax, sz);
+        auto put = [&](uint64_t m, uint32_t &lo, uint32_t &hi) {
+            lo = set_lane(lo, (uint32_t)m, b);
+            hi = set_lane(hi, (uint32_t)(m >> 32), b);
+        };
+        put(__ballot(q < n), free_lo, free_hi);
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            put(__ballot((k >> i) & 1u), k_lo[i], k_hi[i]);
+            put(__ballot((sz >> i) & 1u), s_lo[i], s_hi[i]);
+        }
+    }
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) smax = max(smax, (uint32_t)__shfl_xor((int)smax, d, 64));
+    smax = (uint32_t)__builtin_amdgcn_readfirstlane((int)smax);
+    __syncthreads();
+    {
+        uint32_t carry = 0;                              // starts of the lists (exclusive scan)
+        for (int a0 = 0; a0 < NA; a0 += 64) {
+            const int a = a0 + lane;
+            const uint32_t c = a < NA ? aend[a] : 0u;
+            const uint32_t inc = wave_incl_scan(c) + carry;
+            if (a < NA) aend[a] = inc - c;
+            carry = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+        }
+    }
+    __syncthreads();
+    for (int q = lane; q < n; q += 64)                   // each start advances to its list's end
+        for_aisles(q, [&](uint32_t a) {
+            const uint32_t e = atomicAdd(&aend[a], 1u);
+            if (e < n_lines) apos[e] = (uint16_t)q;      // (a malformed sequence could hold more)
+        });
+    __syncthreads();                                     // the lists are in memory
+    // the long lists as masks of positions: the aisle's end then names its mask
+    {
+        uint32_t n_hot = 0;
+        for (int a0 = 0; a0 < NA; a0 += 64) {
+            const int a = a0 + lane;
+            const uint32_t e1 = a < NA ? min(aend[a], n_lines) : 0u;
+            const uint32_t e0 = a < NA && a > 0 ? min(aend[a - 1] & 0xFFFFu, n_lines) : 0u;
+            const uint64_t want = __ballot(a < NA && e1 > e0 + SEED_COLD);
+            const uint32_t idx = n_hot + __builtin_amdgcn_mbcnt_hi((uint32_t)(want >> 32),
+                                                                  __builtin_amdgcn_mbcnt_lo((uint32_t)want, 0u));
+            lds_order();
+            if (a < NA) aend[a] = e1 | (((want >> lane) & 1ull) ? (idx + 1u) << 16 : 0u);
+            lds_order();
+            for (uint64_t m = want; m; m &= m - 1ull) {
+                const int j = (int)__builtin_ctzll(m);
+                const uint32_t s0 = (uint32_t)__builtin_amdgcn_readlane((int)e0, j);
+                const uint32_t s1 = (uint32_t)__builtin_amdgcn_readlane((int)e1, j);
+                for (uint32_t e = s0 + (uint32_t)lane; e < s1; e += 64) {
+                    const uint32_t r = min((uint32_t)apos[e], (uint32_t)(n - 1));
+                    atomicOr(&mask[r >> 5], 1u << (r & 31u));
+                }
+                lds_order();
+                hot[64u * n_hot + (uint32_t)lane] = ((const uint2 *)mask)[lane];
+                ((uint2 *)mask)[lane] = make_uint2(0u, 0u);
+                lds_order();
+                n_hot++;
+            }
+        }
+    }
+    __syncthreads();
+
+    // ---- tour by tour ------------------------------------------------------
+    // the joins, (position, tour) each, collect in a register and go to
+    // memory 64 at a time: a store per join would have every step wait for it
+    int T = 0, n_join = 0;                               // uniform
+    uint32_t joined = 0;
+    for (;;) {
+        const uint64_t any = __ballot((free_lo | free_hi) != 0u);
+        if (!any) break;
+        // a new tour: every aisle of every order is new to it
+        uint32_t c_lo[4], c_hi[4];
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            c_lo[i] = k_lo[i];
+            c_hi[i] = k_hi[i];
+        }
+        // positions with no new aisle
+        uint32_t z_lo = ~(c_lo[0] | c_lo[1] | c_lo[2] | c_lo[3]), z_hi = ~(c_hi[0] | c_hi[1] | c_hi[2] | c_hi[3]);
+        lds_order();
+        for (int w = lane; w < (NA + 31) / 32; w += 64) tbits[w] = 0u;
+        lds_order();
+        // the seed: the earliest position in no tour
+        int b = (int)__builtin_ctzll(any);
+        int q = 64 * b + (int)__builtin_ctzll(lane64(free_lo, free_hi, b));
+        bool adds = true;                                // the order at q adds an aisle (uniform)
+        uint32_t room = Q;
+        for (;;) {
+            // the order at q joins
+            const uint32_t av = adds ? (uint32_t)fwd[SEED_FWD * q + (lane & (SEED_FWD - 1))] : 0u;
+            joined = set_lane(joined, (uint32_t)q | ((uint32_t)T << 16), n_join & 63);
+            if ((++n_join & 63) == 0) joins[n_join - 64 + lane] = joined;
+            const uint32_t bit = 1u << (q & 31);
+            uint32_t sz = 0;
+            if (q & 32) {
+                free_hi &= lane == b ? ~bit : ~0u;
+#pragma unroll
+                for (int i = 0; i < 4; i++)
+                    sz |= (((uint32_t)__builtin_amdgcn_readlane((int)s_hi[i], b) >> (q & 31)) & 1u) << i;
+            } else {
+                free_lo &= lane == b ? ~bit : ~0u;
+#pragma unroll
+                for (int i = 0; i < 4; i++)
+                    sz |= (((uint32_t)__builtin_amdgcn_readlane((int)s_lo[i], b) >> (q & 31)) & 1u) << i;
+            }
+            room = sz < room ? room - sz : 0u;           // a larger order rides alone
+            if (room == 0u) break;
+            uint32_t m_lo = free_lo, m_hi = free_hi;     // in no tour and fitting
+            if (room < smax) {
+                uint32_t g_lo = 0, g_hi = 0;             // size > room, bit by bit from the lowest
+#pragma unroll
+                for (int i = 0; i < 4; i++) {
+                    if ((room >> i) & 1u) {
+                        g_lo &= s_lo[i];
+                        g_hi &= s_hi[i];
+                    } else {
+                        g_lo |= s_lo[i];
+                        g_hi |= s_hi[i];
+                    }
+                }
+                m_lo &= ~g_lo;
+                m_hi &= ~g_hi;
+            }
+            if (adds) {
+                if (!__ballot((m_lo | m_hi) != 0u)) break;
+                // its aisles new to the tour, in lanes of nm
+                uint32_t a;
+                uint64_t nm;
+                if ((uint32_t)__builtin_amdgcn_readlane((int)av, SEED_FWD - 1) != 0xFFFEu) {
+                    a = av;
+                    const uint32_t ac = min(a, (uint32_t)NA - 1u);
+                    nm = __ballot(a != 0xFFFFu && !((tbits[ac >> 5] >> (ac & 31u)) & 1u)) & ((1ull << SEED_FWD) - 1ull);
+                } else {
+                    // more aisles than the record: from the order's lines,
+                    // one per lane (an aisle counts at its first line)
+                    const uint32_t o = min((uint32_t)seq[q], (uint32_t)(n - 1));
+                    const uint32_t l0 = oo[o], len = min(oo[o + 1] - l0, (uint32_t)SEED_PACKED_LINES);
+                    a = (uint32_t)lane < len ? aisle_of(orr[l0 + (uint32_t)lane]) : 0xFFFFFFFFu;
+                    const uint32_t ac = min(a, (uint32_t)NA - 1u);
+                    bool fresh = (uint32_t)lane < len && !((tbits[ac >> 5] >> (ac & 31u)) & 1u);
+                    for (uint32_t i = 0; i + 1 < len; i++)
+                        fresh = fresh && !(i < (uint32_t)lane && (uint32_t)__builtin_amdgcn_readlane((int)a, (int)i) == a);
+                    nm = __ballot(fresh);
+                }
+                const uint32_t ac = min(a, (uint32_t)NA - 1u);
+                const uint32_t e1 = aend[ac], e0 = ac ? aend[ac - 1u] & 0xFFFFu : 0u;
+                lds_order();
+                if ((nm >> lane) & 1ull) atomicOr(&tbits[ac >> 5], 1u << (ac & 31u));
+                // two aisles at a time: the mask of each is read, or its
+                // (short) position list; the loads carry no condition, so
+                // that both are in flight together
+                while (nm) {
+                    const int j0 = (int)__builtin_ctzll(nm);
+                    nm &= nm - 1ull;
+                    const bool two = nm != 0ull;
+                    const int j1 = two ? (int)__builtin_ctzll(nm) : j0;
+                    nm &= two ? nm - 1ull : 0ull;
+                    const uint32_t v0 = (uint32_t)__builtin_amdgcn_readlane((int)e1, j0);
+                    const uint32_t v1 = (uint32_t)__builtin_amdgcn_readlane((int)e1, j1);
+                    const uint32_t s0 = (uint32_t)__builtin_amdgcn_readlane((int)e0, j0);
+                    const uint32_t s1 = (uint32_t)__builtin_amdgcn_readlane((int)e0, j1);
+                    uint2 w0 = make_uint2(0u, 0u), w1 = make_uint2(0u, 0u);
+                    if (v0 >> 16) w0 = hot[64u * ((v0 >> 16) - 1u) + (uint32_t)lane];
+                    else w0.x = apos[min(s0 + (uint32_t)lane, n_lines - 1u)];
+                    if (two) {
+                        if (v1 >> 16) w1 = hot[64u * ((v1 >> 16) - 1u) + (uint32_t)lane];
+                        else w1.x = apos[min(s1 + (uint32_t)lane, n_lines - 1u)];
+                    }
+                    auto to_mask = [&](uint2 &w, uint32_t len) {
+                        lds_order();
+                        if ((uint32_t)lane < len && w.x < (uint32_t)n) atomicOr(&mask[w.x >> 5], 1u << (w.x & 31u));
+                        lds_order();
+                        w = ((const uint2 *)mask)[lane];
+                        ((uint2 *)mask)[lane] = make_uint2(0u, 0u);
+                        lds_order();
+                    };
+                    // one new aisle fewer at the mask's positions
+                    auto subtract = [&](uint2 w) {
+#pragma unroll
+                        for (int k = 0; k < 4; k++) {
+                            const uint32_t x = c_lo[k], y = c_hi[k];
+                            c_lo[k] = x ^ w.x;
+                            c_hi[k] = y ^ w.y;
+                            w.x &= ~x;
+                            w.y &= ~y;
+                        }
+                    };
+                    if (!(v0 >> 16)) to_mask(w0, v0 - s0);
+                    subtract(w0);
+                    if (two) {
+                        if (!(v1 >> 16)) to_mask(w1, v1 - s1);
+                        subtract(w1);
+                    }
+                }
+                z_lo = ~(c_lo[0] | c_lo[1] | c_lo[2] | c_lo[3]);
+                z_hi = ~(c_hi[0] | c_hi[1] | c_hi[2] | c_hi[3]);
+            }
+            // the next order: the fewest new aisles, then the earliest
+            const uint32_t x0 = m_lo & z_lo, y0 = m_hi & z_hi;
+            adds = __ballot((x0 | y0) != 0u) == 0ull;
+            if (!adds) {
+                m_lo = x0;
+                m_hi = y0;
+            } else {
+                if (!__ballot((m_lo | m_hi) != 0u)) break;
+#pragma unroll
+                for (int k = 3; k >= 0; k--) {
+                    const uint32_t x = m_lo & ~c_lo[k], y = m_hi & ~c_hi[k];
+                    if (__ballot((x | y) != 0u)) {
+                        m_lo = x;
+                        m_hi = y;
+                    }
+                }
+            }
+            b = (int)__builtin_ctzll(__ballot((m_lo | m_hi) != 0u));
+            q = 64 * b + (int)__builtin_ctzll(lane64(m_lo, m_hi, b));
+        }
+        T++;
+    }
+    if (lane < (n_join & 63)) joins[(n_join & ~63) + lane] = joined;
+    __syncthreads();                                     // the joins are in memory
+    for (int i = lane; i < n_join; i += 64) {
+        const uint32_t x = joins[i];
+        tour_of[min((uint32_t)seq[x & 0xFFFFu], (uint32_t)(n - 1))] = (uint16_t)(x >> 16);
+    }
+    return T;
+}
+
 // Plans under first-fit or seed order batching (the other greedy batching
 // rules of the order-picking literature beside next fit; section 5,
 // Subproblem 2 leaves the batching of orders into tours open), for each
@@ -39,7 +375,7 @@ static __device__ __forceinline__ uint32_t set_lane(uint32_t x, uint32_t v, int 
 //      its tour's pick row, then one lane per tour sorts the picks and walks
 //      them as the next-fit kernel does;
 //   4. the wave's sum, saturated to int32, and the rate over the window.
-template <int ROUTE, bool SEED>
+template <int ROUTE, int BATCH>
 __global__ __launch_bounds__(64) void eval_ff_kernel(EvalArgs A)
 {
     constexpr int TILE = ff_tile(ROUTE);
@@ -102,7 +438,9 @@ __global__ __launch_bounds__(64) void eval_ff_kernel(EvalArgs A)
         // a chain of dependent steps: it issues ahead of other plans' tiles
         __builtin_amdgcn_s_setprio(2);
         int T = 0;                                      // tours opened (uniform)
-        if constexpr (SEED) {
+        if constexpr (BATCH == FF_SEED_PACKED) {
+            T = seed_tours_packed(A, I, seq, cnt, zs, tour_of, smem);
+        } else if constexpr (BATCH == FF_SEED) {
             // seed batching
             const int NA = I.n_aisles;
             const SeedLayout L = seed_layout(n, NA, I.n_lines);
@@ -439,12 +777,12 @@ __global__ __launch_bounds__(64) void eval_ff_kernel(EvalArgs A)
     }
 }
 
-template <int ROUTE, bool SEED>
+template <int ROUTE, int BATCH>
 static hipError_t launch_eval_ff_r(const EvalArgs &a, uint32_t lds_bytes, int grid, hipStream_t s)
 {
     static uint32_t attr_bytes = 0;
     if (lds_bytes > attr_bytes) {
-        hipError_t e = hipFuncSetAttribute((const void *)eval_ff_kernel<ROUTE, SEED>,
+        hipError_t e = hipFuncSetAttribute((const void *)eval_ff_kernel<ROUTE, BATCH>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
         if (e != hipSuccess) {
             (void)hipGetLastError();
@@ -452,55 +790,63 @@ static hipError_t launch_eval_ff_r(const EvalArgs &a, uint32_t lds_bytes, int gr
         }
         attr_bytes = lds_bytes;
     }
-    hipLaunchKernelGGL((eval_ff_kernel<ROUTE, SEED>), dim3(grid), dim3(64), lds_bytes, s, a);
+    hipLaunchKernelGGL((eval_ff_kernel<ROUTE, BATCH>), dim3(grid), dim3(64), lds_bytes, s, a);
     return hipGetLastError();
 }
 
-template <bool SEED>
+template <int BATCH>
 static hipError_t launch_eval_ff_s(const EvalArgs &a, uint32_t lds_bytes, int grid, int route, hipStream_t s)
 {
     switch (route) {
-    case WO_ROUTE_SSHAPE: return launch_eval_ff_r<WO_ROUTE_SSHAPE, SEED>(a, lds_bytes, grid, s);
-    case WO_ROUTE_RETURN: return launch_eval_ff_r<WO_ROUTE_RETURN, SEED>(a, lds_bytes, grid, s);
-    case WO_ROUTE_LARGEST_GAP: return launch_eval_ff_r<WO_ROUTE_LARGEST_GAP, SEED>(a, lds_bytes, grid, s);
-    case WO_ROUTE_OPTIMAL: return launch_eval_ff_r<WO_ROUTE_OPTIMAL, SEED>(a, lds_bytes, grid, s);
-    case WO_ROUTE_COMBINED: return launch_eval_ff_r<WO_ROUTE_COMBINED, SEED>(a, lds_bytes, grid, s);
+    case WO_ROUTE_SSHAPE: return launch_eval_ff_r<WO_ROUTE_SSHAPE, BATCH>(a, lds_bytes, grid, s);
+    case WO_ROUTE_RETURN: return launch_eval_ff_r<WO_ROUTE_RETURN, BATCH>(a, lds_bytes, grid, s);
+    case WO_ROUTE_LARGEST_GAP: return launch_eval_ff_r<WO_ROUTE_LARGEST_GAP, BATCH>(a, lds_bytes, grid, s);
+    case WO_ROUTE_OPTIMAL: return launch_eval_ff_r<WO_ROUTE_OPTIMAL, BATCH>(a, lds_bytes, grid, s);
+    case WO_ROUTE_COMBINED: return launch_eval_ff_r<WO_ROUTE_COMBINED, BATCH>(a, lds_bytes, grid, s);
     }
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_eval_ff(const EvalArgs &a, uint32_t lds_bytes, int grid, int route, bool seed, hipStream_t s)
+hipError_t launch_eval_ff(const EvalArgs &a, uint32_t lds_bytes, int grid, int route, int batch, hipStream_t s)
 {
-    return seed ? launch_eval_ff_s<true>(a, lds_bytes, grid, route, s)
-                : launch_eval_ff_s<false>(a, lds_bytes, grid, route, s);
+    switch (batch) {
+    case FF_FIRST_FIT: return launch_eval_ff_s<FF_FIRST_FIT>(a, lds_bytes, grid, route, s);
+    case FF_SEED: return launch_eval_ff_s<FF_SEED>(a, lds_bytes, grid, route, s);
+    case FF_SEED_PACKED: return launch_eval_ff_s<FF_SEED_PACKED>(a, lds_bytes, grid, route, s);
+    }
+    return hipErrorInvalidValue;
 }
 
-template <int ROUTE, bool SEED>
+template <int ROUTE, int BATCH>
 static int ff_max_blocks_r(uint32_t lds_bytes)
 {
     int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, eval_ff_kernel<ROUTE, SEED>, 64, lds_bytes) != hipSuccess) {
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, eval_ff_kernel<ROUTE, BATCH>, 64, lds_bytes) != hipSuccess) {
         (void)hipGetLastError();
         return 1;
     }
     return n > 0 ? n : 1;
 }
 
-template <bool SEED>
+template <int BATCH>
 static int ff_max_blocks_s(int route, uint32_t lds_bytes)
 {
     switch (route) {
-    case WO_ROUTE_RETURN: return ff_max_blocks_r<WO_ROUTE_RETURN, SEED>(lds_bytes);
-    case WO_ROUTE_LARGEST_GAP: return ff_max_blocks_r<WO_ROUTE_LARGEST_GAP, SEED>(lds_bytes);
-    case WO_ROUTE_OPTIMAL: return ff_max_blocks_r<WO_ROUTE_OPTIMAL, SEED>(lds_bytes);
-    case WO_ROUTE_COMBINED: return ff_max_blocks_r<WO_ROUTE_COMBINED, SEED>(lds_bytes);
+    case WO_ROUTE_RETURN: return ff_max_blocks_r<WO_ROUTE_RETURN, BATCH>(lds_bytes);
+    case WO_ROUTE_LARGEST_GAP: return ff_max_blocks_r<WO_ROUTE_LARGEST_GAP, BATCH>(lds_bytes);
+    case WO_ROUTE_OPTIMAL: return ff_max_blocks_r<WO_ROUTE_OPTIMAL, BATCH>(lds_bytes);
+    case WO_ROUTE_COMBINED: return ff_max_blocks_r<WO_ROUTE_COMBINED, BATCH>(lds_bytes);
     }
-    return ff_max_blocks_r<WO_ROUTE_SSHAPE, SEED>(lds_bytes);
+    return ff_max_blocks_r<WO_ROUTE_SSHAPE, BATCH>(lds_bytes);
 }
 
-int eval_ff_max_blocks_per_cu(int route, bool seed, uint32_t lds_bytes)
+int eval_ff_max_blocks_per_cu(int route, int batch, uint32_t lds_bytes)
 {
-    return seed ? ff_max_blocks_s<true>(route, lds_bytes) : ff_max_blocks_s<false>(route, lds_bytes);
+    switch (batch) {
+    case FF_SEED: return ff_max_blocks_s<FF_SEED>(route, lds_bytes);
+    case FF_SEED_PACKED: return ff_max_blocks_s<FF_SEED_PACKED>(route, lds_bytes);
+    }
+    return ff_max_blocks_s<FF_FIRST_FIT>(route, lds_bytes);
 }
 
 }  // namespace wo

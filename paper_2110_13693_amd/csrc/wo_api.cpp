@@ -110,6 +110,10 @@ struct wo_wh {
     uint32_t *d_ff_queue = nullptr;     // first fit: open tours past the first 64, one slice per workgroup
     int64_t ff_stride = 0;              // entries per slice (largest order count + 1, rounded up)
     int ff_slots = 0;                   // slices: the most workgroups a first-fit launch may have
+    int ff_batch = FF_FIRST_FIT;        // the batching kernel of this load's launches
+    unsigned char *d_seed_scr = nullptr;   // packed seed batching: one slice of lists per workgroup
+    int64_t seed_stride = 0;
+    uint32_t seed_apos = 0, seed_hot = 0;
     int small_orders = 1024;            // instances up to this size get a launch of 64-thread workgroups
     std::string arch;                   // the device's architecture name, e.g. "gfx950"
     bool cfg_chosen = false;            // set by wo_set_eval_config, the autotuner or a cache lookup
@@ -280,6 +284,9 @@ extern "C" wo_status wo_load_warehouse(const wo_instance_desc *descs, int32_t n_
     wh->inst.resize(n_instances);
     wh->lds.resize(n_instances);
     wh->ff_lds.resize(n_instances);
+    // seed batching: the packed form where every instance of the load fits it
+    wh->ff_batch = wh->batching == WO_BATCH_SEED ? FF_SEED_PACKED : FF_FIRST_FIT;
+    std::vector<uint32_t> seed_need(n_instances), packed_need(n_instances);
 
     // pooled host arrays
     std::vector<uint2> lines;
@@ -532,9 +539,19 @@ extern "C" wo_status wo_load_warehouse(const wo_instance_desc *descs, int32_t n_
             if (need > wh->lds_max)
                 return fail(WO_E_UNSUPPORTED, "instance %d: seed batching needs %u bytes of LDS (about 4 per order, "
                             "2 per line and 4 per aisle), the device has %u", i, need, wh->lds_max);
-            wh->ff_lds[i] = std::max(wh->ff_lds[i], need);
+            seed_need[i] = need;
+            const uint32_t packed = seed_packed_layout(d.n_aisles).total;
+            // the lists name aisles by 16 bits (the last two values mark
+            // the end and an overflow)
+            if (d.n_orders > SEED_PACKED_ORDERS || max_lines > SEED_PACKED_LINES || d.n_aisles > 65533 ||
+                packed > wh->lds_max)
+                wh->ff_batch = FF_SEED;
+            packed_need[i] = packed;
         }
     }
+    if (wh->batching == WO_BATCH_SEED)
+        for (int32_t i = 0; i < n_instances; i++)
+            wh->ff_lds[i] = std::max(wh->ff_lds[i], wh->ff_batch == FF_SEED ? seed_need[i] : packed_need[i]);
 
     size_t b_lines = lines.size() * sizeof(uint2), b_cnt = cnt.size();
     size_t o_cnt = (b_lines + 255) & ~size_t(255);
@@ -582,8 +599,18 @@ extern "C" wo_status wo_load_warehouse(const wo_instance_desc *descs, int32_t n_
         for (int32_t i = 0; i < n_instances; i++) n_max = std::max(n_max, descs[i].n_orders);
         wh->ff_stride = ((int64_t)n_max + 1 + 63) & ~(int64_t)63;
         wh->ff_slots = wh->cu_count *
-                       eval_ff_max_blocks_per_cu(wh->route, wh->batching == WO_BATCH_SEED,
+                       eval_ff_max_blocks_per_cu(wh->route, wh->ff_batch,
                                                  *std::min_element(wh->ff_lds.begin(), wh->ff_lds.end()));
+        if (wh->ff_batch == FF_SEED_PACKED) {
+            int32_t lines_max = 0;
+            for (int32_t i = 0; i < n_instances; i++) lines_max = std::max(lines_max, wh->inst[i].n_lines);
+            wh->ff_slots = std::min(wh->ff_slots, 16 * wh->cu_count);
+            wh->seed_apos = 2u * SEED_FWD * (uint32_t)wh->ff_stride;
+            wh->seed_hot = (uint32_t)(((int64_t)wh->seed_apos + 2 * (int64_t)lines_max + 255) & ~(int64_t)255);
+            // a line is in one list at most, so this bounds the long ones
+            wh->seed_stride = (int64_t)wh->seed_hot + 512 * (int64_t)(lines_max / (SEED_COLD + 1) + 1);
+            if ((st = dev_alloc((void **)&wh->d_seed_scr, (size_t)wh->seed_stride * wh->ff_slots))) return st;
+        }
         if ((st = dev_alloc((void **)&wh->d_ff_tour, sizeof(uint16_t) * (size_t)wh->ff_stride * wh->ff_slots)))
             return st;
         if ((st = dev_alloc((void **)&wh->d_ff_queue, sizeof(uint32_t) * (size_t)wh->ff_stride * wh->ff_slots)))
@@ -597,7 +624,8 @@ extern "C" wo_status wo_load_warehouse(const wo_instance_desc *descs, int32_t n_
 extern "C" wo_status wo_free_warehouse(wo_wh *wh)
 {
     if (!wh) return WO_OK;
-    if (wh->d_pool || wh->d_inst || wh->d_map || wh->d_err || wh->d_ff_tour || wh->d_ff_queue) (void)hipDeviceSynchronize();
+    if (wh->d_pool || wh->d_inst || wh->d_map || wh->d_err || wh->d_ff_tour || wh->d_ff_queue || wh->d_seed_scr)
+        (void)hipDeviceSynchronize();
     if (wh->d_pool) (void)hipFree(wh->d_pool);
     if (wh->d_inst) (void)hipFree(wh->d_inst);
     if (wh->d_map) (void)hipFree(wh->d_map);
@@ -607,6 +635,7 @@ extern "C" wo_status wo_free_warehouse(wo_wh *wh)
     if (wh->d_pinst) (void)hipFree(wh->d_pinst);
     if (wh->d_ff_tour) (void)hipFree(wh->d_ff_tour);
     if (wh->d_ff_queue) (void)hipFree(wh->d_ff_queue);
+    if (wh->d_seed_scr) (void)hipFree(wh->d_seed_scr);
     if (wh->last_done) (void)hipEventDestroy(wh->last_done);
     delete wh;
     return WO_OK;
@@ -634,7 +663,7 @@ static int launch_grid(const wo_wh *wh, int block, int per_cu_cfg, uint32_t lds,
 
 static int ff_grid(const wo_wh *wh, uint32_t lds, int64_t n_plans)
 {
-    const int64_t fit = (int64_t)wh->cu_count * eval_ff_max_blocks_per_cu(wh->route, wh->batching == WO_BATCH_SEED, lds);
+    const int64_t fit = (int64_t)wh->cu_count * eval_ff_max_blocks_per_cu(wh->route, wh->ff_batch, lds);
     return (int)std::min<int64_t>(n_plans, std::min<int64_t>(fit, wh->ff_slots));   // one tour table slice each
 }
 
@@ -831,6 +860,10 @@ extern "C" wo_status wo_eval_plans(wo_wh *wh, const int64_t *plan_offsets, int64
     a.ff_tour = wh->d_ff_tour;
     a.ff_stride = wh->ff_stride;
     a.ff_queue = wh->d_ff_queue;
+    a.seed_scr = wh->d_seed_scr;
+    a.seed_stride = wh->seed_stride;
+    a.seed_apos = wh->seed_apos;
+    a.seed_hot = wh->seed_hot;
     a.plan_spacing = nullptr;
     bool any_small = false;
     for (int32_t i = 0; i < wh->n_inst; i++) any_small |= class_of(wh, i) != 0 && map[i + 1] > map[i];
@@ -838,7 +871,7 @@ extern "C" wo_status wo_eval_plans(wo_wh *wh, const int64_t *plan_offsets, int64
         // first fit has a kernel of its own, one wavefront per plan; the
         // launch configuration above applies to next fit only
         HIP_TRY(launch_eval_ff(a, wh->ff_lds_max, ff_grid(wh, wh->ff_lds_max, n_plans), wh->route,
-                               wh->batching == WO_BATCH_SEED, s));
+                               wh->ff_batch, s));
     } else if (!any_small && !wh->queue) {
         // one launch, grid stride over the plan rows
         HIP_TRY(launch_eval(a, wh->lds_max, launch_grid(wh, wh->lds_max, n_plans), wh->block, wh->route, s));
@@ -923,10 +956,14 @@ wo_status wo::eval_instance(wo_wh *wh, int32_t inst, int64_t n_plans, const uint
     a.ff_tour = wh->d_ff_tour;
     a.ff_stride = wh->ff_stride;
     a.ff_queue = wh->d_ff_queue;
+    a.seed_scr = wh->d_seed_scr;
+    a.seed_stride = wh->seed_stride;
+    a.seed_apos = wh->seed_apos;
+    a.seed_hot = wh->seed_hot;
     a.plan_spacing = d_plan_spacing;
     if (wh->batching != WO_BATCH_NEXT_FIT) {
         const uint32_t lds = wh->ff_lds[inst];
-        HIP_TRY(launch_eval_ff(a, lds, ff_grid(wh, lds, n_plans), wh->route, wh->batching == WO_BATCH_SEED, s));
+        HIP_TRY(launch_eval_ff(a, lds, ff_grid(wh, lds, n_plans), wh->route, wh->ff_batch, s));
         return WO_OK;
     }
     const uint32_t lds = wh->lds[inst];

@@ -98,6 +98,11 @@ struct EvalArgs {
     uint16_t *ff_tour;      // first fit: tour of every order, ff_stride entries per workgroup
     int64_t ff_stride;
     uint32_t *ff_queue;     // first fit: open tours past the first 64, ff_stride entries per workgroup
+                            // (packed seed batching: every join of an order to a tour)
+    unsigned char *seed_scr;   // packed seed batching: aisle and position lists, seed_stride bytes per workgroup
+    int64_t seed_stride;
+    uint32_t seed_apos;     // byte offset of the position lists in a slice
+    uint32_t seed_hot;      // byte offset of the long lists' masks in a slice
     const int32_t *plan_spacing;   // device [n_plans]: aisle spacing of each plan row (null: the instance's)
 };
 
@@ -216,12 +221,40 @@ __host__ __device__ inline SeedLayout seed_layout(int32_t n_orders, int32_t n_ai
     return L;
 }
 
+// Packed seed batching: instances of at most SEED_PACKED_ORDERS orders, each of
+// at most SEED_PACKED_LINES lines (a wave then holds one 64-bit word per lane of
+// every mask of positions, and four bit planes hold a size or a count).  LDS:
+// a mask of positions, the ends of the aisles' position lists and the
+// tour's aisle set.  The lists themselves, the masks of the long ones and each
+// position's first SEED_FWD aisles go to a slice of global scratch per workgroup, so that 16 plans fit a
+// CU.
+constexpr int SEED_PACKED_ORDERS = 4096;
+constexpr int SEED_PACKED_LINES = 15;
+constexpr int SEED_FWD = 4;
+constexpr int SEED_COLD = 64;           // longest list kept as one: an entry per lane
+struct SeedPackedLayout {
+    uint32_t mask, aend, tbits, total;
+};
+__host__ __device__ inline SeedPackedLayout seed_packed_layout(int32_t n_aisles)
+{
+    SeedPackedLayout L;
+    uint32_t b = ff_rows_off();
+    L.mask = b;   b += 64u * 8u;
+    L.aend = b;   b += 4u * (uint32_t)n_aisles;
+    L.tbits = b;  b += 4u * (((uint32_t)n_aisles + 31u) / 32u);
+    L.total = (b + 15u) & ~15u;
+    return L;
+}
+
+// order batching kernels of firstfit.hip
+enum { FF_FIRST_FIT = 0, FF_SEED = 1, FF_SEED_PACKED = 2 };
+
 hipError_t launch_eval(const EvalArgs &a, uint32_t lds_bytes, int grid, int block, int route, hipStream_t s);
 // workgroups of the evaluation kernel that fit one CU (registers and LDS)
 int eval_max_blocks_per_cu(int block, int route, uint32_t lds_bytes, int line_pass = 0);
 // First-fit batching: one 64-thread workgroup per plan.
-hipError_t launch_eval_ff(const EvalArgs &a, uint32_t lds_bytes, int grid, int route, bool seed, hipStream_t s);
-int eval_ff_max_blocks_per_cu(int route, bool seed, uint32_t lds_bytes);
+hipError_t launch_eval_ff(const EvalArgs &a, uint32_t lds_bytes, int grid, int route, int batch, hipStream_t s);
+int eval_ff_max_blocks_per_cu(int route, int batch, uint32_t lds_bytes);
 
 // library-internal helpers over a loaded handle
 wo_status eval_instance(wo_wh *wh, int32_t inst, int64_t n_plans, const uint8_t *d_zone_of,

@@ -150,3 +150,30 @@ def test_orders_over_many_aisles_are_refused():
     with pytest.raises(wo.WoError) as e:
         wo.wo_load_warehouse([inst])
     assert e.value.status == wo.WO_E_UNSUPPORTED
+
+
+# where the packed form begins and ends: positions and lines per order at its
+# limits, and aisles of just as many orders as a list holds, and one more
+PACKED_EDGES = [
+    # (orders, lines of the longest order, capacity, orders of one aisle)
+    (4096, 15, 30, 64), (4097, 15, 30, 65), (700, 15, 14, 65), (700, 16, 30, 64), (64, 9, 32, 64), (65, 5, 3, 65),
+]
+
+
+@pytest.mark.parametrize("case", PACKED_EDGES, ids=lambda c: "n%d_l%d_Q%d_a%d" % c)
+def test_packed_form_edges(case):
+    from tests.whelpers import tiny_geometry
+    n, longest, Q, in_one = case
+    rng = np.random.default_rng(n + longest)
+    orders = [list(rng.integers(120, 1800, rng.integers(1, 5))) for _ in range(n)]   # beyond aisle 0
+    for i in range(in_one):
+        orders[i][0] = int(rng.integers(0, 60))                  # exactly in_one orders visit aisle 0
+    orders[n // 2] = list(rng.integers(120, 1800, longest))
+    if n // 2 < in_one:
+        orders[n // 2][0] = 7
+    inst = _sd(tiny_geometry([[int(x) for x in o] for o in orders], capacity=Q, n_aisles=30, slots=30, n_cat=12,
+                             cat_size=150))
+    Z, S = synth.make_plans(inst, 6, seed=n)
+    Z[0, :12] = np.arange(12)                                    # the identity: aisle 0 holds SKUs 0 .. 59
+    print("case", case, flush=True)
+    _compare(inst, Z, S)
