@@ -131,3 +131,25 @@ def test_prediction_shapes(F, K, n):
     torch.cuda.synchronize()
     assert np.array_equal(cls.cpu().numpy(), O.predict(x, w_gpu))
     s.free()
+
+
+@pytest.mark.parametrize("F,K,n,density", [(3, 2, 8192, 1.0), (2, 3, 8193, 0.04), (5, 16, 8200, 0.3), (1, 17, 16500, 1.0),
+                                           (4, 33, 600, 0.5), (64, 8, 8191, 0.0)])
+def test_training_rounds_and_zeros(F, K, n, density):
+    # whole rounds of samples and one more, pieces of the product buffer for
+    # every class count, features that are zero (of both signs) everywhere,
+    # nowhere and in part, infinities and NaN among them
+    wo = _wo()
+    rng = np.random.default_rng(F * 100 + K)
+    x = rng.normal(size=(n, F)) * (rng.random((n, F)) < density)
+    x[::7] *= -1.0                                       # and zeros of the other sign
+    if density == 0.3:
+        x[n // 2, 0], x[n // 3, 1] = np.inf, np.nan
+    y = rng.integers(0, K, n).astype(np.int32)
+    print("rounds", F, K, n, density, flush=True)
+    s = wo.wo_svm_create(F, K, n + 3, 0.05)              # a window not yet full
+    wo.wo_svm_push(s, _t(x, np.float64), _t(y, np.int32))
+    wo.wo_svm_train(s, 2)
+    w_gpu, _, _ = wo.wo_svm_get_weights(s)
+    assert np.array_equal(w_gpu, O.train(x, y, K, 0.05, 2), equal_nan=True)
+    s.free()
