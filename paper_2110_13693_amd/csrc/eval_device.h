@@ -22,6 +22,17 @@ static __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x)
     return x;
 }
 
+// x with lane l (uniform) set to v (uniform): v_writelane
+extern "C" __device__ int wo_writelane_i32(int src, int lane, int old) __asm("llvm.amdgcn.writelane.i32");
+static __device__ __forceinline__ uint32_t set_lane(uint32_t x, uint32_t v, int l)
+{
+    return (uint32_t)wo_writelane_i32((int)v, l, (int)x);
+}
+
+// A wave's LDS accesses take effect in program order: only the compiler must
+// keep it between accesses of different lanes of one wave.
+static __device__ __forceinline__ void lds_order() { asm volatile("" ::: "memory"); }
+
 // Smallest value over the 64 lanes of a wave (all lanes active), the same
 // shifts and broadcasts; every lane gets it.
 static __device__ __forceinline__ uint32_t wave_min_u32(uint32_t v)

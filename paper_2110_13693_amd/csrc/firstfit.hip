@@ -3,23 +3,12 @@
 
 namespace wo {
 
-// x with lane l (uniform) set to v (uniform): v_writelane
-extern "C" __device__ int wo_writelane_i32(int src, int lane, int old) __asm("llvm.amdgcn.writelane.i32");
-static __device__ __forceinline__ uint32_t set_lane(uint32_t x, uint32_t v, int l)
-{
-    return (uint32_t)wo_writelane_i32((int)v, l, (int)x);
-}
-
 // value of a 64-bit lane register pair in lane l (uniform)
 static __device__ __forceinline__ uint64_t lane64(uint32_t lo, uint32_t hi, int l)
 {
     return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)lo, l) |
            ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)hi, l) << 32);
 }
-
-// LDS accesses of the (only) wave take effect in program order: the compiler
-// must keep it
-static __device__ __forceinline__ void lds_order() { asm volatile("" ::: "memory"); }
 
 // Tours under seed batching, packed form (SEED_PACKED_ORDERS and
 // SEED_PACKED_LINES above): the same rule as the general form below, with the

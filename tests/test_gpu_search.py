@@ -145,3 +145,31 @@ def test_checkpoint_resumes_bit_exactly(tmp_path):
     r.free()
     s.free()
     wh.free()
+
+
+@pytest.mark.parametrize("n,thr", [(1, 0.5), (7, 1.0), (64, 1.0), (200, 0.9), (4096, 0.06), (4097, 0.02), (4099, 0.045),
+                                   (9000, 0.1)])
+def test_sequence_moves_match_cpu(monkeypatch, n, thr):
+    # sequences of one and several blocks of coins, odd lengths, and move
+    # counts on both sides of what one rebuild of the sequence takes, up to a
+    # move at every position (elements that move several times)
+    import torch
+    from tests.whelpers import tiny_geometry
+    wo = _wo()
+    t32 = min(int(thr * 2 ** 32), 2 ** 32 - 1)
+    monkeypatch.setattr(G, "P_MUT", t32)
+    inst = tiny_geometry([[i % 600] for i in range(n)])
+    P, seed = 6, 4321 + n
+    Z, S = _init(inst, P, n)
+    wh = wo.wo_load_warehouse([inst])
+    print("moves", n, thr, flush=True)
+    s = wo.wo_search_create(wh, 0, torch.from_numpy(Z).cuda(),
+                            torch.from_numpy(S.view(np.int16)).cuda().reshape(-1), P, mutation_threshold=t32, seed=seed)
+    D, _ = oracle.eval_plans(inst, Z, S)
+    for gen in range(2):
+        wo.wo_search_step(wh, s, None, 1)
+        Z, S, D = G.plain_generation(inst, Z, S, D, seed=seed, gen=gen)
+        zg, qg, dg = _population(wo, s, P, n)
+        assert np.array_equal(zg, Z) and np.array_equal(qg, S) and np.array_equal(dg, D), gen
+    s.free()
+    wh.free()
