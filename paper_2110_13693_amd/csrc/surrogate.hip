@@ -9,12 +9,11 @@
 //   y   = h2 W3 + b3           (standardised distance)
 //
 // GEMMs run on MFMA (v_mfma_f32_32x32x16_bf16 or v_mfma_f32_16x16x32_bf16:
-// bf16 operands, fp32 accumulation).  Weights are kept as fp32 masters in
-// [out][in] layout with bf16 working copies; the one-hot operand of the
-// forward products is generated in registers from the zone bytes and never
-// stored.  Every GEMM here is C[M][N] = A[M][K] . B[N][K]^T with both operands
-// K-contiguous.  The gradient of W1 is not a product: with a one-hot input it
-// is a sum of du1 rows per (category, zone) bin (w1_grad_kernel).
+// bf16 operands, fp32 accumulation).  Weights are kept as fp32 masters with bf16
+// working copies.  Every GEMM here is C[M][N] = A[M][K] . B[N][K]^T with both
+// operands K-contiguous.  Neither layer 1 nor the gradient of W1 is a product:
+// with a one-hot input they are sums, of one W1 row per category
+// (layer1_kernel) and of du1 rows per (category, zone) bin (w1_grad_kernel).
 #include <type_traits>
 
 #include "wo_internal.h"
@@ -63,15 +62,11 @@ static __device__ __forceinline__ float gelu_grad_f(float u)
 // step 64, four waves in 2 x 2, each (TM/2)^2 = (TM/32)^2 MFMA tiles of
 // 16 x 16.  The next K step's operands are loaded into registers while the
 // current one's MFMAs run from LDS.  M, N multiples of TM and K a multiple of
-// 64 (the host pads); rows of A at or beyond M_real read as zero when
-// generated from zone bytes.
+// 64 (the host pads).
 // ---------------------------------------------------------------------------
 constexpr int GBK = 64, GPAD = 8, GLDK = GBK + GPAD;
-// zone bytes of A rows at a 68-byte stride: the 16 rows of an MFMA tile then
-// read one category's bytes from 16 different LDS banks
-constexpr int ZLD = 68;
 
-template <int AMODE, int BMODE, int EPI, int TM, int MS>
+template <int EPI, int TM, int MS>
 __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g)
 {
     constexpr int WT = TM / 2;                 // wave tile
@@ -81,12 +76,8 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g)
     constexpr int NLD = TM * GBK / 8 / 256;    // 16-byte loads per thread per operand tile
     // operand tiles in two buffers: step k reads buffer k & 1 while the next
     // step's operands are written to the other one
-    __shared__ __align__(16) uint16_t As[2][(AMODE == A_BF16) ? TM * GLDK : 8];
+    __shared__ __align__(16) uint16_t As[2][TM * GLDK];
     __shared__ __align__(16) uint16_t Bs[2][TM * GLDK];
-    __shared__ __align__(16) uint8_t ZsA[(AMODE == A_ONEHOT) ? TM * ZLD : 16];
-    // one-hot fragments: pattern d < 8 holds bf16 1.0 at element d, pattern 8
-    // is all zeros
-    __shared__ __align__(16) uint32_t OneHot[(AMODE == A_ONEHOT) ? 9 * 4 : 4];
 
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int wm = w >> 1, wn = w & 1;
@@ -107,32 +98,12 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g)
 #pragma unroll
             for (int e = 0; e < (MS == 32 ? 16 : 4); e++) acc[i][j][e] = 0.f;
 
-    if (AMODE == A_ONEHOT) {
-        if (tid < 36) {
-            const uint32_t d = (uint32_t)tid >> 2, e = (uint32_t)tid & 3u;
-            OneHot[tid] = (d < 8u && (d >> 1) == e) ? (0x3F80u << ((d & 1u) * 16u)) : 0u;
-        }
-        // zone bytes of the block's rows, 0xFF past the real rows
-        for (int c = tid; c < TM * 4; c += 256) {
-            const int r = c >> 2, part = c & 3;
-            uint4 v = make_uint4(0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu);
-            if (m0 + r < g.M_real) v = *(const uint4 *)(g.zoneA + (int64_t)(m0 + r) * 64 + part * 16);
-            uint32_t *zw = (uint32_t *)(&ZsA[r * ZLD + part * 16]);
-            zw[0] = v.x;
-            zw[1] = v.y;
-            zw[2] = v.z;
-            zw[3] = v.w;
-        }
-    }
-
     u32x4 ra[NLD], rbv[NLD];   // native vectors, so that they stay in registers
 #define WO_LOAD_TILE(k0_)                                                                                        \
     do {                                                                                                         \
-        if (AMODE == A_BF16) {                                                                                   \
-            _Pragma("unroll") for (int i = 0; i < NLD; i++) {                                                    \
-                const int c = tid + i * 256, r = c >> 3, part = c & 7;                                           \
-                ra[i] = *(const u32x4 *)(g.A + (int64_t)(m0 + r) * g.lda + (k0_) + part * 8);                    \
-            }                                                                                                    \
+        _Pragma("unroll") for (int i = 0; i < NLD; i++) {                                                        \
+            const int c = tid + i * 256, r = c >> 3, part = c & 7;                                               \
+            ra[i] = *(const u32x4 *)(g.A + (int64_t)(m0 + r) * g.lda + (k0_) + part * 8);                        \
         }                                                                                                        \
         _Pragma("unroll") for (int i = 0; i < NLD; i++) {                                                        \
             const int c = tid + i * 256, r = c >> 3, part = c & 7;                                               \
@@ -141,11 +112,9 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g)
     } while (0)
 #define WO_STORE_TILE(buf)                                                                                       \
     do {                                                                                                         \
-        if (AMODE == A_BF16) {                                                                                   \
-            _Pragma("unroll") for (int i = 0; i < NLD; i++) {                                                    \
-                const int c = tid + i * 256, r = c >> 3, part = c & 7;                                           \
-                *(u32x4 *)(&As[buf][r * GLDK + part * 8]) = ra[i];                                               \
-            }                                                                                                    \
+        _Pragma("unroll") for (int i = 0; i < NLD; i++) {                                                        \
+            const int c = tid + i * 256, r = c >> 3, part = c & 7;                                               \
+            *(u32x4 *)(&As[buf][r * GLDK + part * 8]) = ra[i];                                                   \
         }                                                                                                        \
         _Pragma("unroll") for (int i = 0; i < NLD; i++) {                                                        \
             const int c = tid + i * 256, r = c >> 3, part = c & 7;                                               \
@@ -161,25 +130,13 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g)
     for (int k0 = kbeg, cur = 0; k0 < kend; k0 += GBK, cur ^= 1) {
         const bool more = k0 + GBK < kend;
         WO_LOAD_TILE(more ? k0 + GBK : k0);          // unconditional, so the operands stay in registers
-        // a K step of 64 is one category: the zone of each of the wave's rows
-        uint32_t zrow[FT];
-        if (AMODE == A_ONEHOT) {
-            const int cat = k0 >> 6;
-#pragma unroll
-            for (int ti = 0; ti < FT; ti++)
-                zrow[ti] = cat < g.n_cat ? (uint32_t)ZsA[(wm * WT + ti * MS + fr) * ZLD + cat] : 0xFFu;
-        }
 #pragma unroll
         for (int ks = 0; ks < GBK; ks += KM) {
             bf16x8 af[FT], bfr[FT];
 #pragma unroll
             for (int ti = 0; ti < FT; ti++) {
                 const int row = wm * WT + ti * MS + fr;
-                if (AMODE == A_BF16) {
-                    af[ti] = *(const bf16x8 *)(&As[cur][row * GLDK + ks + fk]);
-                } else {
-                    af[ti] = *(const bf16x8 *)(&OneHot[4u * min(zrow[ti] - (uint32_t)(ks + fk), 8u)]);
-                }
+                af[ti] = *(const bf16x8 *)(&As[cur][row * GLDK + ks + fk]);
             }
 #pragma unroll
             for (int tj = 0; tj < FT; tj++) {
@@ -283,6 +240,201 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs g)
             }
         }
     }
+}
+
+// ---------------------------------------------------------------------------
+// Layer 1.  With one-hot inputs u[b] is the bias plus one row of W1 per
+// category, the row of the zone it lies in: 64 row additions per sample instead
+// of a product 4,096 deep.  A workgroup takes a slice of 128 hidden units (a
+// row piece is 256 bytes) and TM samples.  The pieces of 4 categories (64 rows
+// each) sit in LDS, in two buffers: the next categories' load straight to LDS
+// while the current ones are added.  Sixteen lanes share a sample, 8 units
+// each, so a piece is read whole and its 256 bytes lie in all 64 banks: rows
+// at random do not conflict (pieces of 128 bytes did, 2.9 cycles a read).  Every
+// lane holds S consecutive samples.  The additions
+// run on the matrix cores: v_mfma_f32_4x4x4_16b_bf16 with the identity as its
+// left operand adds to each lane's four fp32 sums the lane's own four bf16
+// values, as they come from LDS.  Each sum adds its categories in order, one
+// product per step, so the results equal the 4,096-deep product's bit for bit.
+// A zone byte of 64 or more, like a category that does not exist, names a row
+// of zeros.
+//
+// Bound by the LDS reads, 16 bytes per lane for every 8 additions: 65,536
+// samples take 177 us (0.115 ms of them the reads at 8.9 cycles each, 23 us the
+// GELU), against 485 us for the one-hot product at 0.45 of the bf16 peak; a
+// training batch of 4,096 23 us, against 50.  With the reads in the compiler's
+// order, one or two in flight: 203 us.
+// ---------------------------------------------------------------------------
+typedef __attribute__((__vector_size__(4 * sizeof(short)))) short short4v;
+constexpr int L1_WAVES = 16, L1_CATS = 4;
+constexpr int L1_ROW_B = 2 * W1_UNITS;                       // bytes of a row piece
+constexpr int L1_CAT_B = 65 * L1_ROW_B;                      // bytes of a category in LDS: 64 rows and one of zeros
+static_assert(L1_ROW_B == 256 && N_H1 / W1_UNITS == 8, "16 lanes per row piece, a slice per XCD");
+
+template <int S>
+__global__ __launch_bounds__(64 * L1_WAVES) void layer1_kernel(Layer1Args a)
+{
+    constexpr int TM = 4 * S * L1_WAVES;
+    constexpr int SH = S < 4 ? S : 4;                        // row pieces in flight per lane
+    __shared__ __align__(16) unsigned char buf[2][L1_CATS * L1_CAT_B];
+    static_assert(W1_UNITS * (TM + 8) * 2 <= 2 * L1_CATS * L1_CAT_B, "the transposed tile fits the buffers");
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // an XCD (b % 8) takes one slice, 1 MB of W1, and keeps it in its L2
+    const int sl = (int)blockIdx.x & 7, m0 = ((int)blockIdx.x >> 3) * TM;
+    const uint16_t *W = a.W1 + (int64_t)sl * N_IN * W1_UNITS;
+    const int n_ph = (a.n_cat + L1_CATS - 1) / L1_CATS;
+
+    // the rows of zeros, which the loads below leave alone
+    for (int i = tid; i < 2 * L1_CATS * (L1_ROW_B / 4); i += 64 * L1_WAVES) {
+        const int c = i / (L1_ROW_B / 4);
+        *(uint32_t *)(&buf[c / L1_CATS][(c % L1_CATS) * L1_CAT_B + 64 * L1_ROW_B + 4 * (i % (L1_ROW_B / 4))]) = 0u;
+    }
+    auto load_cats = [&](int ph, int b) {
+        // 4 rows (1 KB) per wave and instruction
+#pragma unroll
+        for (int i = 0; i < L1_CATS * 16 / L1_WAVES; i++) {
+            const int piece = w + i * L1_WAVES, cat = piece >> 4, r4 = piece & 15;
+            const uint16_t *from = W + ((int64_t)(ph * L1_CATS + cat) * 64 + r4 * 4) * W1_UNITS + lane * 8;
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)from,
+                                             (__attribute__((address_space(3))) void *)&buf[b][cat * L1_CAT_B + r4 * 1024], 16, 0, 0);
+        }
+    };
+    const int row0 = m0 + w * 4 * S + (lane >> 4) * S;       // this lane's samples: row0 .. row0 + S - 1
+    // the zone bytes: lane l of a sample's sixteen holds those of categories
+    // 4 l .. 4 l + 3, one coalesced load per sample for all phases
+    uint32_t zall[S];
+#pragma unroll
+    for (int s = 0; s < S; s++)
+        zall[s] = ((const uint32_t *)(a.zone + (int64_t)min(row0 + s, a.M_real - 1) * 64))[lane & 15];
+    {
+        // 64, the row of zeros, in the bytes of categories and samples past the
+        // last ones and of zones of 64 and more; then twice the row, at most
+        // 128, still a byte each
+        const int left = min(max(a.n_cat - 4 * (lane & 15), 0), 4);
+        const uint32_t none = left == 4 ? 0u : 0x40404040u << (8 * left);
+#pragma unroll
+        for (int s = 0; s < S; s++) {
+            const uint32_t v = zall[s] | (row0 + s < a.M_real ? none : 0x40404040u);
+            const uint32_t f = (v | (v >> 1)) & 0x40404040u;
+            zall[s] = ((v & ~((f - (f >> 6)) | f) & 0x3F3F3F3Fu) | f) << 1;
+        }
+    }
+
+    floatx4 acc[S][2];
+#pragma unroll
+    for (int s = 0; s < S; s++)
+#pragma unroll
+        for (int q = 0; q < 2; q++) acc[s][q] = floatx4{0.f, 0.f, 0.f, 0.f};
+    short4v id = {0, 0, 0, 0};
+    id[0] = (lane & 3) == 0 ? 0x3F80 : 0;
+    id[1] = (lane & 3) == 1 ? 0x3F80 : 0;
+    id[2] = (lane & 3) == 2 ? 0x3F80 : 0;
+    id[3] = (lane & 3) == 3 ? 0x3F80 : 0;
+
+    const uint32_t lane_at = (uint32_t)(lane & 15) * 16u;
+    load_cats(0, 0);
+    for (int ph = 0; ph < n_ph; ph++) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // this wave's rows are in LDS
+        __syncthreads();                                     // and the other waves'; the other buffer is read
+        if (ph + 1 < n_ph) load_cats(ph + 1, (ph + 1) & 1);
+        // this phase's bytes, from the first of each sample's sixteen lanes
+        // (row_newbcast:0); the next phase's move there (row_ror:15)
+        uint32_t z[S];
+#pragma unroll
+        for (int s = 0; s < S; s++) {
+            z[s] = (uint32_t)__builtin_amdgcn_mov_dpp((int)zall[s], 0x150, 0xF, 0xF, true);
+            zall[s] = (uint32_t)__builtin_amdgcn_mov_dpp((int)zall[s], 0x12F, 0xF, 0xF, true);
+        }
+        // the row pieces of group g: SH samples of one category; byte c of
+        // twice the rows times 128, plus the lane's place: one 8-bit dot product
+        const uint32_t at0 = lane_at + (uint32_t)(ph & 1) * (uint32_t)(L1_CATS * L1_CAT_B);
+        u32x4 v[2][SH];
+        auto read = [&](int g, u32x4 (&d)[SH]) {
+            const int c = g / (S / SH), s0 = g % (S / SH) * SH;
+#pragma unroll
+            for (int s = 0; s < SH; s++)
+                d[s] = *(const u32x4 *)(&buf[0][0] + c * L1_CAT_B + __builtin_amdgcn_udot4(z[s0 + s], 128u << (8 * c), at0, false));
+        };
+        // the next group's reads are issued before a group is added (the
+        // scheduler would otherwise wait for each read in turn)
+        read(0, v[0]);
+#pragma unroll
+        for (int g = 0; g < L1_CATS * S / SH; g++) {
+            if (g + 1 < L1_CATS * S / SH) read(g + 1, v[(g + 1) & 1]);
+            __builtin_amdgcn_sched_barrier(0);
+            const int s0 = g % (S / SH) * SH;
+#pragma unroll
+            for (int s = 0; s < SH; s++) {
+                const u32x4 x = v[g & 1][s];
+                const u32x2 lo = {x[0], x[1]}, hi = {x[2], x[3]};
+                acc[s0 + s][0] =
+                    __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(id, __builtin_bit_cast(short4v, lo), acc[s0 + s][0], 0, 0, 0);
+                acc[s0 + s][1] =
+                    __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(id, __builtin_bit_cast(short4v, hi), acc[s0 + s][1], 0, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+
+    // bias and GELU: this lane's 8 units of its S samples
+    const int u0 = (lane & 15) * 8, h0 = sl * W1_UNITS + u0;
+    float bias[8];
+#pragma unroll
+    for (int e = 0; e < 8; e++) bias[e] = a.bias[h0 + e];
+    if (a.HT) __syncthreads();                               // the buffers are read: the transposed tile takes them
+    uint16_t *tile = (uint16_t *)&buf[0][0];                 // [W1_UNITS][TM + 8]
+#pragma unroll
+    for (int s = 0; s < S; s++) {
+        float u[8];
+        uint32_t hb[4];
+#pragma unroll
+        for (int e = 0; e < 8; e++) u[e] = acc[s][e >> 2][e & 3] + bias[e];
+#pragma unroll
+        for (int e = 0; e < 4; e++)
+            hb[e] = (uint32_t)f2bf(gelu_f(u[2 * e])) | ((uint32_t)f2bf(gelu_f(u[2 * e + 1])) << 16);
+        if (row0 + s < a.M) {
+            const int64_t at = (int64_t)(row0 + s) * N_H1 + h0;
+            if (a.U) {
+                *(float4 *)(a.U + at) = make_float4(u[0], u[1], u[2], u[3]);
+                *(float4 *)(a.U + at + 4) = make_float4(u[4], u[5], u[6], u[7]);
+            }
+            *(uint4 *)(a.H + at) = make_uint4(hb[0], hb[1], hb[2], hb[3]);
+        }
+        if (a.HT) {
+#pragma unroll
+            for (int e = 0; e < 8; e++)
+                tile[(u0 + e) * (TM + 8) + row0 + s - m0] = (uint16_t)((e & 1) ? hb[e >> 1] >> 16 : hb[e >> 1]);
+        }
+    }
+    if (a.HT) {
+        // 16-byte pieces along the samples (M is a multiple of 8)
+        __syncthreads();
+        for (int i = tid; i < W1_UNITS * (TM / 8); i += 64 * L1_WAVES) {
+            const int e = i / (TM / 8), r = i % (TM / 8) * 8;
+            if (m0 + r < a.M)
+                *(uint4 *)(a.HT + (int64_t)(sl * W1_UNITS + e) * a.ldt + m0 + r) = *(const uint4 *)(tile + e * (TM + 8) + r);
+        }
+    }
+}
+
+template <int S>
+static hipError_t launch_layer1_t(const Layer1Args &a, hipStream_t s)
+{
+    constexpr int TM = 4 * S * L1_WAVES;
+    hipLaunchKernelGGL(layer1_kernel<S>, dim3((a.M + TM - 1) / TM * (N_H1 / W1_UNITS)), dim3(64 * L1_WAVES), 0, s, a);
+    return hipGetLastError();
+}
+
+// Every workgroup loads its slice of W1 (1 MB) whatever its samples, so it takes
+// as many as leave a workgroup per CU: 512, fewer where that leaves CUs idle.
+hipError_t launch_layer1(const Layer1Args &a, hipStream_t s)
+{
+    if (a.M % 128 || a.M_real < 1 || a.M_real > a.M || a.n_cat < 1 || a.n_cat > 64) return hipErrorInvalidValue;
+    if (a.M >= 16384) return launch_layer1_t<8>(a, s);
+    if (a.M >= 8192) return launch_layer1_t<4>(a, s);
+    if (a.M >= 4096) return launch_layer1_t<2>(a, s);
+    return launch_layer1_t<1>(a, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -455,10 +607,10 @@ __global__ __launch_bounds__(256) void batch_sums_kernel(SumArgs a)
 // no bin.
 // ---------------------------------------------------------------------------
 constexpr int W1_SLICE = DU1_SLICE;
-constexpr int W1_UNITS = W1_SLICE / 64;                      // hidden units per lane
+constexpr int W1_LANE = W1_SLICE / 64;                      // hidden units per lane
 constexpr int W1_SLICES = N_H1 / W1_SLICE;
 constexpr int W1_WAVES = 16;
-static_assert(W1_UNITS == 4, "four units per lane, one 8-byte load");
+static_assert(W1_LANE == 4, "four units per lane, one 8-byte load");
 static_assert(8 % W1_SLICES == 0, "slices spread evenly over 8 XCDs");
 constexpr int W1_GROUPS = MAX_GRAD_ROWS / (64 * W1_WAVES);   // groups of 64 samples per wave when sorting
 
@@ -551,14 +703,14 @@ __global__ __launch_bounds__(64 * W1_WAVES) void w1_grad_kernel(const uint16_t *
             z = __builtin_amdgcn_readfirstlane(z);
             int zend = __builtin_amdgcn_readfirstlane(soff[z + 1]);
             bool first = __builtin_amdgcn_readfirstlane(soff[z]) < i0;   // the bin began in an earlier share
-            float a[W1_UNITS];
+            float a[W1_LANE];
 #pragma unroll
-            for (int u = 0; u < W1_UNITS; u++) a[u] = 0.f;
+            for (int u = 0; u < W1_LANE; u++) a[u] = 0.f;
             // the slice as a buffer: a position's row offset is uniform and
             // goes in a scalar register, the lane's units are the vector offset
             const __amdgpu_buffer_rsrc_t slice = __builtin_amdgcn_make_buffer_rsrc(
                 (void *)(du1 + (int64_t)sl * n * W1_SLICE), 0, n * 2 * W1_SLICE, 0x00020000);
-            const int lane_off = 2 * W1_UNITS * lane;
+            const int lane_off = 2 * W1_LANE * lane;
             using Row = u32x2;
             auto ld = [&](int so) -> Row { return __builtin_amdgcn_raw_buffer_load_b64(slice, lane_off, so, 0); };
             auto add = [&](const Row &r) {
@@ -569,9 +721,9 @@ __global__ __launch_bounds__(64 * W1_WAVES) void w1_grad_kernel(const uint16_t *
             };
             auto flush = [&](bool to_head) {
 #pragma unroll
-                for (int u = 0; u < W1_UNITS; u++) {
-                    if (to_head) head[w][W1_UNITS * lane + u] = a[u];
-                    else out[W1_UNITS * lane + u][z] = a[u];
+                for (int u = 0; u < W1_LANE; u++) {
+                    if (to_head) head[w][W1_LANE * lane + u] = a[u];
+                    else out[W1_LANE * lane + u][z] = a[u];
                     a[u] = 0.f;
                 }
                 if (to_head && lane == 0) headz[w] = z;
@@ -622,8 +774,9 @@ __global__ __launch_bounds__(64 * W1_WAVES) void w1_grad_kernel(const uint16_t *
     }
     __syncthreads();
     for (int k = tid; k < W1_SLICE * 64; k += 64 * W1_WAVES) {
-        const int r = k >> 6, j = k & 63;
-        gW1[(int64_t)(h0 + r) * N_IN + c * 64 + j] = out[r][j];
+        // slice k / 4096 of W1's layout, row (zone) j, unit r of the slice
+        const int q = k / (64 * W1_UNITS), j = (k / W1_UNITS) & 63, r = k % W1_UNITS;
+        gW1[((int64_t)(h0 / W1_UNITS + q) * N_IN + c * 64 + j) * W1_UNITS + r] = out[q * W1_UNITS + r][j];
     }
 }
 
@@ -660,8 +813,8 @@ __global__ __launch_bounds__(256) void adam_kernel(float *p, const float *g, flo
     }
 }
 
-// bf16 working copies: W1 [1024][4096] and W2 [256][1024] as stored, plus W2
-// transposed to [1024][256] for the backward product.
+// bf16 working copies: W1 and W2 as stored, plus W2 transposed to [1024][256]
+// for the backward product.
 __global__ __launch_bounds__(256) void refresh_bf16_kernel(const float *W1t, const float *W2t, uint16_t *W1b,
                                                            uint16_t *W2b, uint16_t *W2kn)
 {
@@ -676,6 +829,55 @@ __global__ __launch_bounds__(256) void refresh_bf16_kernel(const float *W1t, con
             W2b[k] = v;
             W2kn[i2 * N_H2 + j] = v;
         }
+    }
+}
+
+// The parameter vector from the device layout to the host's or the files', or
+// back.  W1: tiles of 64 inputs x 64 units through LDS (input-major rows of the
+// host layout are copies, the files' output-major ones a transpose); then W2
+// the same way (its device layout is the files'), then the rest as it is.
+__global__ __launch_bounds__(256) void relayout_kernel(const float *from, float *to, int layout, int to_device)
+{
+    __shared__ float tile[64][65];
+    const int tid = threadIdx.x;
+    constexpr int T1 = (N_IN / 64) * (N_H1 / 64), T2 = (N_H1 / 64) * (N_H2 / 64);
+    const int64_t P2 = P_W2;
+    const int blk = blockIdx.x;
+    if (blk < T1 + T2) {
+        // element (input i, output o) of the tile at device offset dev(i, o) and other offset oth(i, o)
+        const bool one = blk < T1;
+        const int t = one ? blk : blk - T1;
+        const int ti = one ? t / (N_H1 / 64) : t / (N_H2 / 64), to_ = one ? t % (N_H1 / 64) : t % (N_H2 / 64);
+        const int n_in = one ? N_IN : N_H1, n_out = one ? N_H1 : N_H2;
+        const int64_t base = one ? P_W1 : P2;
+        auto dev = [&](int i, int o) -> int64_t {
+            const int u = to_ * 64 + o;
+            return one ? ((int64_t)(u / W1_UNITS) * N_IN + ti * 64 + i) * W1_UNITS + u % W1_UNITS
+                       : (int64_t)u * n_in + ti * 64 + i;
+        };
+        auto oth = [&](int i, int o) -> int64_t {
+            return layout == LAYOUT_HOST ? (int64_t)(ti * 64 + i) * n_out + to_ * 64 + o
+                                         : (int64_t)(to_ * 64 + o) * n_in + ti * 64 + i;
+        };
+        // each side is read or written along its contiguous index
+        const bool dev_o = one, oth_o = layout == LAYOUT_HOST;
+        const bool src_o = to_device ? oth_o : dev_o, dst_o = to_device ? dev_o : oth_o;
+        for (int e = tid; e < 4096; e += 256) {
+            const int x = e >> 6, y = e & 63, i = src_o ? x : y, o = src_o ? y : x;
+            tile[i][o] = from[base + (to_device ? oth(i, o) : dev(i, o))];
+        }
+        __syncthreads();
+        for (int e = tid; e < 4096; e += 256) {
+            const int x = e >> 6, y = e & 63, i = dst_o ? x : y, o = dst_o ? y : x;
+            to[base + (to_device ? dev(i, o) : oth(i, o))] = tile[i][o];
+        }
+        return;
+    }
+    // biases and W3
+    for (int64_t i = (int64_t)(blk - T1 - T2) * 256 + tid; i < P_TOTAL - (int64_t)N_IN * N_H1 - (int64_t)N_H1 * N_H2;
+         i += (int64_t)(gridDim.x - T1 - T2) * 256) {
+        const int64_t at = i < N_H1 ? P_B1 + i : P_B2 + (i - N_H1);
+        to[at] = from[at];
     }
 }
 
@@ -873,7 +1075,7 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_kernel(const void *src, int
 // MFMA shape: 32 x 32 x 16 where there is about one workgroup per CU (the
 // training products: 5 % faster); 16 x 16 x 32 for the large screening
 // passes (at least 1,024 workgroups: 3 % faster)
-template <int AM, int BM, int EP>
+template <int EP>
 static hipError_t launch_gemm_t(const GemmArgs &g, hipStream_t s)
 {
     const int ks = g.ksplit > 1 ? g.ksplit : 1;
@@ -881,26 +1083,25 @@ static hipError_t launch_gemm_t(const GemmArgs &g, hipStream_t s)
     // a short K (dU1: 256) leaves the epilogue most of a workgroup's time:
     // 64 x 64 tiles, so that four workgroups per CU overlap their epilogues
     if (g.K <= 256 && t128 < 1024) {
-        hipLaunchKernelGGL((gemm_kernel<AM, BM, EP, 64, 32>), dim3(g.N / 64, g.M / 64, ks), dim3(256), 0, s, g);
+        hipLaunchKernelGGL((gemm_kernel<EP, 64, 32>), dim3(g.N / 64, g.M / 64, ks), dim3(256), 0, s, g);
     } else if (t128 >= 1024) {
-        hipLaunchKernelGGL((gemm_kernel<AM, BM, EP, 128, 16>), dim3(g.N / 128, g.M / 128, ks), dim3(256), 0, s, g);
+        hipLaunchKernelGGL((gemm_kernel<EP, 128, 16>), dim3(g.N / 128, g.M / 128, ks), dim3(256), 0, s, g);
     } else if (t128 >= 256) {
-        hipLaunchKernelGGL((gemm_kernel<AM, BM, EP, 128, 32>), dim3(g.N / 128, g.M / 128, ks), dim3(256), 0, s, g);
+        hipLaunchKernelGGL((gemm_kernel<EP, 128, 32>), dim3(g.N / 128, g.M / 128, ks), dim3(256), 0, s, g);
     } else {
-        hipLaunchKernelGGL((gemm_kernel<AM, BM, EP, 64, 32>), dim3(g.N / 64, g.M / 64, ks), dim3(256), 0, s, g);
+        hipLaunchKernelGGL((gemm_kernel<EP, 64, 32>), dim3(g.N / 64, g.M / 64, ks), dim3(256), 0, s, g);
     }
     return hipGetLastError();
 }
 
-hipError_t launch_gemm(int amode, int bmode, int epi, const GemmArgs &g, hipStream_t s)
+hipError_t launch_gemm(int epi, const GemmArgs &g, hipStream_t s)
 {
     if (g.M % 128 || g.N % 128 || g.K % GBK) return hipErrorInvalidValue;
     if (g.ksplit > 1 && (epi != EPI_STORE || g.K % (g.ksplit * GBK))) return hipErrorInvalidValue;
     if ((int64_t)g.M * g.ldc >= (int64_t)1 << 31) return hipErrorInvalidValue;   // 32-bit output offsets
-    if (amode == A_ONEHOT && bmode == B_BF16 && epi == EPI_BIAS_GELU) return launch_gemm_t<A_ONEHOT, B_BF16, EPI_BIAS_GELU>(g, s);
-    if (amode == A_BF16 && bmode == B_BF16 && epi == EPI_BIAS_GELU) return launch_gemm_t<A_BF16, B_BF16, EPI_BIAS_GELU>(g, s);
-    if (amode == A_BF16 && bmode == B_BF16 && epi == EPI_STORE) return launch_gemm_t<A_BF16, B_BF16, EPI_STORE>(g, s);
-    if (amode == A_BF16 && bmode == B_BF16 && epi == EPI_GELU_GRAD_T) return launch_gemm_t<A_BF16, B_BF16, EPI_GELU_GRAD_T>(g, s);
+    if (epi == EPI_BIAS_GELU) return launch_gemm_t<EPI_BIAS_GELU>(g, s);
+    if (epi == EPI_STORE) return launch_gemm_t<EPI_STORE>(g, s);
+    if (epi == EPI_GELU_GRAD_T) return launch_gemm_t<EPI_GELU_GRAD_T>(g, s);
     return hipErrorInvalidValue;
 }
 
@@ -956,6 +1157,13 @@ hipError_t launch_gather_batch(const uint8_t *zone, const int32_t *dist, int64_t
 {
     hipLaunchKernelGGL(gather_batch_kernel, dim3((n + 3) / 4), dim3(256), 0, s, zone, dist, n_all, h, key, first, n,
                        mean, inv_std, zb, zt, tb);
+    return hipGetLastError();
+}
+
+hipError_t launch_relayout(const float *from, float *to, int layout, bool to_device, hipStream_t s)
+{
+    constexpr int tiles = (N_IN / 64) * (N_H1 / 64) + (N_H1 / 64) * (N_H2 / 64);
+    hipLaunchKernelGGL(relayout_kernel, dim3(tiles + 4), dim3(256), 0, s, from, to, layout, to_device ? 1 : 0);
     return hipGetLastError();
 }
 

@@ -75,27 +75,22 @@ wo_status alloc(T **p, size_t count)
 // are at zone; U1/H1/H1T/U2 filled.  train: keep U1 and the transposed H1.
 wo_status forward(wo_sur *s, const uint8_t *zone, int rows_real, int rows, bool train, hipStream_t st)
 {
-    GemmArgs g{};
+    Layer1Args g{};
     g.M = rows;
-    g.N = N_H1;
-    g.K = N_IN;
     g.M_real = rows_real;
     g.n_cat = s->n_cat;
-    g.zoneA = zone;
-    g.B = s->d_W1b;
-    g.ldb = N_IN;
-    g.ldc = N_H1;
+    g.zone = zone;
+    g.W1 = s->d_W1b;
     g.bias = s->d_p + P_B1;
     g.U = train ? s->d_U1 : nullptr;
     g.H = s->d_H1;
     g.HT = train ? s->d_H1T : nullptr;
     g.ldt = rows;
-    WO_HIP(launch_gemm(A_ONEHOT, B_BF16, EPI_BIAS_GELU, g, st));
+    WO_HIP(launch_layer1(g, st));
     GemmArgs h{};
     h.M = rows;
     h.N = N_H2;
     h.K = N_H1;
-    h.M_real = rows_real;
     h.A = s->d_H1;
     h.lda = N_H1;
     h.B = s->d_W2b;
@@ -103,7 +98,7 @@ wo_status forward(wo_sur *s, const uint8_t *zone, int rows_real, int rows, bool 
     h.ldc = N_H2;
     h.bias = s->d_p + P_B2;
     h.U = s->d_U2;
-    WO_HIP(launch_gemm(A_BF16, B_BF16, EPI_BIAS_GELU, h, st));
+    WO_HIP(launch_gemm(EPI_BIAS_GELU, h, st));
     return WO_OK;
 }
 
@@ -142,7 +137,7 @@ wo_status gradients(wo_sur *s, int rows, hipStream_t st, float *loss_out = nullp
     g1.HT = s->d_DU1T;
     g1.ldt = rows;
     g1.H = s->d_H1;   // du1 in column slices as well, in h1's buffer (free after layer 2)
-    WO_HIP(launch_gemm(A_BF16, B_BF16, EPI_GELU_GRAD_T, g1, st));
+    WO_HIP(launch_gemm(EPI_GELU_GRAD_T, g1, st));
     // gW2^T [256][1024] = du2^T [256][b] . (h1^T [1024][b])^T: a long K over
     // few outputs, so K is split in parts (into u1's buffer, free now) that
     // the batch sums add in order
@@ -160,7 +155,7 @@ wo_status gradients(wo_sur *s, int rows, hipStream_t st, float *loss_out = nullp
     g2.ldc = N_H1;
     g2.ksplit = ks;
     g2.c_split = (int64_t)N_H2 * N_H1;
-    WO_HIP(launch_gemm(A_BF16, B_BF16, EPI_STORE, g2, st));
+    WO_HIP(launch_gemm(EPI_STORE, g2, st));
     // gW1 [1024][4096] = du1^T . x with x one-hot: sums of du1 rows per
     // (category, zone) bin
     WO_HIP(launch_w1_grad(s->d_H1, s->d_zt, rows, s->n_cat, s->d_g + P_W1, st));
@@ -223,37 +218,6 @@ struct SurBusy {
     }
 };
 
-// canonical host layout (W1 [4096][1024], b1, W2 [1024][256], b2, W3 [256], b3)
-// <-> device [out][in] layout
-void host_to_device_layout(const float *h, std::vector<float> &d)
-{
-    d.assign(P_TOTAL, 0.f);
-    const float *W1 = h, *b1 = W1 + (int64_t)N_IN * N_H1, *W2 = b1 + N_H1, *b2 = W2 + (int64_t)N_H1 * N_H2,
-                *W3 = b2 + N_H2, *b3 = W3 + N_H2;
-    for (int i = 0; i < N_IN; i++)
-        for (int o = 0; o < N_H1; o++) d[P_W1 + (int64_t)o * N_IN + i] = W1[(int64_t)i * N_H1 + o];
-    for (int o = 0; o < N_H1; o++) d[P_B1 + o] = b1[o];
-    for (int i = 0; i < N_H1; i++)
-        for (int o = 0; o < N_H2; o++) d[P_W2 + (int64_t)o * N_H1 + i] = W2[(int64_t)i * N_H2 + o];
-    for (int o = 0; o < N_H2; o++) d[P_B2 + o] = b2[o];
-    for (int i = 0; i < N_H2; i++) d[P_W3 + i] = W3[i];
-    d[P_B3] = b3[0];
-}
-
-void device_to_host_layout(const std::vector<float> &d, float *h)
-{
-    float *W1 = h, *b1 = W1 + (int64_t)N_IN * N_H1, *W2 = b1 + N_H1, *b2 = W2 + (int64_t)N_H1 * N_H2,
-          *W3 = b2 + N_H2, *b3 = W3 + N_H2;
-    for (int i = 0; i < N_IN; i++)
-        for (int o = 0; o < N_H1; o++) W1[(int64_t)i * N_H1 + o] = d[P_W1 + (int64_t)o * N_IN + i];
-    for (int o = 0; o < N_H1; o++) b1[o] = d[P_B1 + o];
-    for (int i = 0; i < N_H1; i++)
-        for (int o = 0; o < N_H2; o++) W2[(int64_t)i * N_H2 + o] = d[P_W2 + (int64_t)o * N_H1 + i];
-    for (int o = 0; o < N_H2; o++) b2[o] = d[P_B2 + o];
-    for (int i = 0; i < N_H2; i++) W3[i] = d[P_W3 + i];
-    b3[0] = d[P_B3];
-}
-
 // He-uniform initial weights from a counter generator: weight e of layer L
 // gets splitmix64(seed, L, e) mapped to U(-sqrt(6/fan_in), sqrt(6/fan_in)).
 void default_init(uint64_t seed, std::vector<float> &h)
@@ -277,8 +241,8 @@ void default_init(uint64_t seed, std::vector<float> &h)
 
 }  // namespace
 
-extern "C" wo_status wo_sur_create(int32_t n_categories, const float *h_init, uint64_t seed, void *stream,
-                                   wo_sur **out)
+// init: set the parameters (from h_init or the seed); without it the caller does
+static wo_status create(int32_t n_categories, const float *h_init, uint64_t seed, void *stream, wo_sur **out, bool init)
 {
     if (!out) return wo_fail(WO_E_INVAL, "out is NULL");
     *out = nullptr;
@@ -303,7 +267,14 @@ extern "C" wo_status wo_sur_create(int32_t n_categories, const float *h_init, ui
         (r = alloc(&s->d_mom, 2)) || (r = alloc(&s->d_loss, 1)) || (r = alloc(&s->d_red, W3_SLICES * N_H2 + 16)) ||
         (r = alloc(&s->d_zt, (size_t)64 * MAX_GRAD_ROWS)))
         return r;
-    std::vector<float> host, dev;
+    hipStream_t st = (hipStream_t)stream;
+    WO_HIP(hipMemsetAsync(s->d_red, 0, sizeof(float) * (W3_SLICES * N_H2 + 16), st));
+    if (!init) {
+        guard.release();
+        *out = s;
+        return WO_OK;
+    }
+    std::vector<float> host;
     if (h_init) {
         host.assign(h_init, h_init + P_TOTAL);
     } else {
@@ -311,17 +282,21 @@ extern "C" wo_status wo_sur_create(int32_t n_categories, const float *h_init, ui
     }
     for (float x : host)
         if (!std::isfinite(x)) return wo_fail(WO_E_INVAL, "initial parameters must be finite");
-    host_to_device_layout(host.data(), dev);
-    hipStream_t st = (hipStream_t)stream;
-    WO_HIP(hipMemcpyAsync(s->d_p, dev.data(), sizeof(float) * P_TOTAL, hipMemcpyHostToDevice, st));
+    WO_HIP(hipMemcpyAsync(s->d_g, host.data(), sizeof(float) * P_TOTAL, hipMemcpyHostToDevice, st));
+    WO_HIP(launch_relayout(s->d_g, s->d_p, LAYOUT_HOST, true, st));
     WO_HIP(hipMemsetAsync(s->d_m, 0, sizeof(float) * P_TOTAL, st));
     WO_HIP(hipMemsetAsync(s->d_v, 0, sizeof(float) * P_TOTAL, st));
-    WO_HIP(hipMemsetAsync(s->d_red, 0, sizeof(float) * (W3_SLICES * N_H2 + 16), st));
     WO_HIP(launch_refresh_bf16(s->d_p + P_W1, s->d_p + P_W2, s->d_W1b, s->d_W2b, s->d_W2kn, st));
     WO_HIP(hipStreamSynchronize(st));
     guard.release();
     *out = s;
     return WO_OK;
+}
+
+extern "C" wo_status wo_sur_create(int32_t n_categories, const float *h_init, uint64_t seed, void *stream,
+                                   wo_sur **out)
+{
+    return create(n_categories, h_init, seed, stream, out, true);
 }
 
 extern "C" wo_status wo_sur_free(wo_sur *s)
@@ -360,10 +335,10 @@ extern "C" wo_status wo_sur_get_scale(const wo_sur *s, double *mean, double *std
 extern "C" wo_status wo_sur_get_params(const wo_sur *s, float *h_out)
 {
     if (!s || !h_out) return wo_fail(WO_E_INVAL, "NULL argument");
-    std::vector<float> dev(P_TOTAL);
     WO_HIP(hipDeviceSynchronize());
-    WO_HIP(hipMemcpy(dev.data(), s->d_p, sizeof(float) * P_TOTAL, hipMemcpyDeviceToHost));
-    device_to_host_layout(dev, h_out);
+    // in the host layout by way of the gradient buffer, free between calls
+    WO_HIP(launch_relayout(s->d_p, s->d_g, LAYOUT_HOST, false, nullptr));
+    WO_HIP(hipMemcpy(h_out, s->d_g, sizeof(float) * P_TOTAL, hipMemcpyDeviceToHost));
     return WO_OK;
 }
 
@@ -385,12 +360,12 @@ extern "C" wo_status wo_sur_gradients(wo_sur *s, int32_t n, const uint8_t *d_zon
     WO_HIP(launch_zone_cols(s->d_zb, n, s->d_zt, st));
     wo_status r = gradients(s, n, st);
     if (r) return r;
-    std::vector<float> dev(P_TOTAL);
-    WO_HIP(hipMemcpyAsync(dev.data(), s->d_g, sizeof(float) * P_TOTAL, hipMemcpyDeviceToHost, st));
+    // in the host layout by way of u1's buffer, free after the backward pass
+    WO_HIP(launch_relayout(s->d_g, s->d_U1, LAYOUT_HOST, false, st));
+    WO_HIP(hipMemcpyAsync(h_grad, s->d_U1, sizeof(float) * P_TOTAL, hipMemcpyDeviceToHost, st));
     float loss = 0.f;
     WO_HIP(hipMemcpyAsync(&loss, s->d_loss, sizeof(float), hipMemcpyDeviceToHost, st));
     WO_HIP(hipStreamSynchronize(st));
-    device_to_host_layout(dev, h_grad);
     if (h_loss) *h_loss = loss;
     return WO_OK;
 }
@@ -510,9 +485,12 @@ extern "C" wo_status wo_sur_save(const wo_sur *s, const char *path)
     if (!s || !path) return wo_fail(WO_E_INVAL, "NULL argument");
     std::vector<float> p(P_TOTAL), m(P_TOTAL), v(P_TOTAL);
     WO_HIP(hipDeviceSynchronize());
-    WO_HIP(hipMemcpy(p.data(), s->d_p, sizeof(float) * P_TOTAL, hipMemcpyDeviceToHost));
-    WO_HIP(hipMemcpy(m.data(), s->d_m, sizeof(float) * P_TOTAL, hipMemcpyDeviceToHost));
-    WO_HIP(hipMemcpy(v.data(), s->d_v, sizeof(float) * P_TOTAL, hipMemcpyDeviceToHost));
+    const float *from[3] = {s->d_p, s->d_m, s->d_v};
+    float *to[3] = {p.data(), m.data(), v.data()};
+    for (int k = 0; k < 3; k++) {
+        WO_HIP(launch_relayout(from[k], s->d_g, LAYOUT_FILE, false, nullptr));
+        WO_HIP(hipMemcpy(to[k], s->d_g, sizeof(float) * P_TOTAL, hipMemcpyDeviceToHost));
+    }
     FILE *f = fopen(path, "wb");
     if (!f) return wo_fail(WO_E_INVAL, "cannot open %s for writing", path);
     const char magic[8] = {'W', 'O', 'S', 'U', 'R', '0', '0', '2'};
@@ -543,14 +521,19 @@ extern "C" wo_status wo_sur_load(const char *path, void *stream, wo_sur **out)
               fread(v.data(), 4, P_TOTAL, f) == (size_t)P_TOTAL;
     fclose(f);
     if (!ok) return wo_fail(WO_E_INVAL, "%s is not a surrogate checkpoint", path);
-    std::vector<float> host(P_TOTAL);
-    device_to_host_layout(p, host.data());
+    for (float x : p)
+        if (!std::isfinite(x)) return wo_fail(WO_E_INVAL, "initial parameters must be finite");
     wo_sur *s = nullptr;
-    wo_status r = wo_sur_create(hdr[2], host.data(), 0, stream, &s);
+    wo_status r = create(hdr[2], nullptr, 0, stream, &s, false);
     if (r) return r;
     hipStream_t st = (hipStream_t)stream;
-    if (hipMemcpyAsync(s->d_m, m.data(), sizeof(float) * P_TOTAL, hipMemcpyHostToDevice, st) != hipSuccess ||
-        hipMemcpyAsync(s->d_v, v.data(), sizeof(float) * P_TOTAL, hipMemcpyHostToDevice, st) != hipSuccess ||
+    const float *from[3] = {p.data(), m.data(), v.data()};
+    float *to[3] = {s->d_p, s->d_m, s->d_v};
+    bool up = true;
+    for (int k = 0; k < 3 && up; k++)
+        up = hipMemcpyAsync(s->d_g, from[k], sizeof(float) * P_TOTAL, hipMemcpyHostToDevice, st) == hipSuccess &&
+             launch_relayout(s->d_g, to[k], LAYOUT_FILE, true, st) == hipSuccess;
+    if (!up || launch_refresh_bf16(s->d_p + P_W1, s->d_p + P_W2, s->d_W1b, s->d_W2b, s->d_W2kn, st) != hipSuccess ||
         hipStreamSynchronize(st) != hipSuccess) {
         wo_sur_free(s);
         return wo_fail(WO_E_DEVICE, "copy of the optimiser state failed");

@@ -432,3 +432,49 @@ def test_training_is_deterministic_and_follows_its_seed():
         s.free()
     assert np.array_equal(out[0][0], out[1][0]) and out[0][1] == out[1][1]
     assert not np.array_equal(out[0][0], out[2][0])
+
+
+@pytest.mark.parametrize("n,n_cat", [(1, 64), (129, 63), (4000, 13), (4096, 64), (4097, 1), (8192, 5), (16384, 64),
+                                     (16500, 30)])
+def test_forward_at_the_sample_counts_of_each_launch(n, n_cat):
+    # every number of samples per workgroup, ragged last ones, category counts
+    # that end inside a group of four, and bytes that name no zone (they add
+    # nothing) among the categories that count
+    import torch
+    wo = _wo()
+    p = _params(3)
+    s = wo.wo_sur_create(n_cat, flat(p))
+    wo.wo_sur_set_scale(s, 0.0, 1.0)
+    Z = _zones(n, n, n_cat)
+    rng = np.random.default_rng(n)
+    Z[rng.random(Z.shape) < 0.02] = rng.integers(64, 256)
+    Z[:, n_cat:] = rng.integers(0, 256, size=(n, 64 - n_cat))
+    pred = torch.empty(n, dtype=torch.float32, device="cuda")
+    print("forward", n, n_cat, flush=True)
+    wo.wo_sur_predict(s, torch.from_numpy(Z).cuda(), pred)
+    torch.cuda.synchronize()
+    rows = np.unique(np.concatenate([np.arange(min(n, 40)), n // 2 + np.arange(min(n // 2, 40)), np.arange(max(0, n - 40), n)]))
+    x = np.zeros((rows.size, 64, 64))
+    for c in range(n_cat):
+        ok = Z[rows, c] < 64
+        x[np.flatnonzero(ok), c, Z[rows, c][ok]] = 1.0
+    q = _ref_params(p)
+    y, cache = S.forward(q, x.reshape(rows.size, 4096))
+    assert_within(pred.cpu().numpy()[rows], y, device_error_model(q, cache, y)["s_y"], "prediction")
+    s.free()
+
+
+def test_checkpoint_file_layout():
+    # the file's parameters: W1 and W2 output-major, whatever the device's layout
+    wo = _wo()
+    s = wo.wo_sur_create(64, flat(_params(8)))
+    v = unflat(wo.wo_sur_get_params(s))
+    with tempfile.TemporaryDirectory() as tdir:
+        path = os.path.join(tdir, "sur.bin")
+        wo.wo_sur_save(s, path)
+        raw = np.fromfile(path, np.float32, count=S.N_IN * S.N_H1 + S.N_H1 + S.N_H1 * S.N_H2, offset=8 + 8 + 12 + 16)
+    w1, b1, w2 = np.split(raw, [S.N_IN * S.N_H1, S.N_IN * S.N_H1 + S.N_H1])
+    assert np.array_equal(w1.reshape(S.N_H1, S.N_IN), v["W1"].T) and np.array_equal(b1, v["b1"])
+    assert np.array_equal(w2.reshape(S.N_H2, S.N_H1), v["W2"].T)
+    assert np.array_equal(wo.wo_sur_get_params(s), flat(_params(8)))
+    s.free()
