@@ -478,3 +478,31 @@ def test_checkpoint_file_layout():
     assert np.array_equal(w2.reshape(S.N_H2, S.N_H1), v["W2"].T)
     assert np.array_equal(wo.wo_sur_get_params(s), flat(_params(8)))
     s.free()
+
+
+@pytest.mark.parametrize("n,keep,distinct", [(1, 1, 64), (2000, 2000, 64), (8192, 4096, 3), (8193, 1, 64), (30000, 4096, 1),
+                                             (70000, 3277, 3), (70000, 4096, 64), (40000, 100, 2)])
+def test_screen_with_ties(n, keep, distinct):
+    # predictions of few distinct values: more equal ones than the selection
+    # holds at once, at and around the last kept one, down to one value; and
+    # counts at the selection's own limits
+    import torch
+    wo = _wo()
+    inst, _, _ = synth.workload("paper", n_plans=1)
+    p = {k: np.zeros(sh, np.float32) for k, sh in SHAPES}
+    p["W1"][:64, 0] = np.arange(64) % distinct           # category 0's zone decides
+    p["W2"][0, 0], p["W3"][0, 0] = 1.0, -1.0
+    wh = wo.wo_load_warehouse([inst])
+    s = wo.wo_sur_create(64, flat(p))
+    wo.wo_sur_set_scale(s, 0.0, 1.0)
+    z = torch.from_numpy(_zones(n, n)).cuda()
+    pred = torch.empty(n, dtype=torch.float32, device="cuda")
+    idx = torch.full((keep,), -1, dtype=torch.int32, device="cuda")
+    print("ties", n, keep, distinct, flush=True)
+    wo.wo_screen_plans(wh, 0, s, z, keep, idx, pred=pred)
+    torch.cuda.synchronize()
+    v = pred.cpu().numpy()
+    assert np.unique(v).size <= distinct
+    assert np.array_equal(idx.cpu().numpy(), np.lexsort((np.arange(n), v))[:keep])
+    s.free()
+    wh.free()
