@@ -29,6 +29,10 @@ static __device__ __forceinline__ uint32_t set_lane(uint32_t x, uint32_t v, int 
     return (uint32_t)wo_writelane_i32((int)v, l, (int)x);
 }
 
+// Whether this lane's bit of a uniform mask is set: the mask serves as the
+// condition itself, with no shift per lane.
+static __device__ __forceinline__ bool lane_in(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+
 // A wave's LDS accesses take effect in program order: only the compiler must
 // keep it between accesses of different lanes of one wave.
 static __device__ __forceinline__ void lds_order() { asm volatile("" ::: "memory"); }

@@ -149,7 +149,7 @@ static __device__ int seed_tours_packed(const EvalArgs &A, const InstDev &I, con
             const uint32_t idx = n_hot + __builtin_amdgcn_mbcnt_hi((uint32_t)(want >> 32),
                                                                   __builtin_amdgcn_mbcnt_lo((uint32_t)want, 0u));
             lds_order();
-            if (a < NA) aend[a] = e1 | (((want >> lane) & 1ull) ? (idx + 1u) << 16 : 0u);
+            if (a < NA) aend[a] = e1 | (lane_in(want) ? (idx + 1u) << 16 : 0u);
             lds_order();
             for (uint64_t m = want; m; m &= m - 1ull) {
                 const int j = (int)__builtin_ctzll(m);
@@ -254,7 +254,7 @@ static __device__ int seed_tours_packed(const EvalArgs &A, const InstDev &I, con
                 const uint32_t ac = min(a, (uint32_t)NA - 1u);
                 const uint32_t e1 = aend[ac], e0 = ac ? aend[ac - 1u] & 0xFFFFu : 0u;
                 lds_order();
-                if ((nm >> lane) & 1ull) atomicOr(&tbits[ac >> 5], 1u << (ac & 31u));
+                if (lane_in(nm)) atomicOr(&tbits[ac >> 5], 1u << (ac & 31u));
                 // two aisles at a time: the mask of each is read, or its
                 // (short) position list; the loads carry no condition, so
                 // that both are in flight together
@@ -341,14 +341,22 @@ static __device__ int seed_tours_packed(const EvalArgs &A, const InstDev &I, con
 // route.  One wavefront evaluates one plan:
 //   1. zone starts: each category's start is the total size of the
 //      categories in lower zones (one pass over the categories per lane);
-//   2. first fit, order by order in sequence, over the open tours only (a
-//      tour whose room falls below the instance's smallest order can never
-//      take another one).  Lane j keeps the j-th tour in opening order and
-//      its room, so one ballot finds the earliest tour with room; full tours
-//      leave the lanes only when the lanes run out.  The open tours stay few
-//      (first fit keeps filling the earliest ones), but any beyond 64 wait,
-//      in order, in a queue in global memory that is searched, 64 at a time,
-//      when no lane has room, and refills the lanes;
+//   2. first fit, 64 orders of the sequence at a time, one per lane, tour by
+//      tour: an order joins the earliest tour with room, so the first tour
+//      takes, in sequence, every order that fits what it has left, the next
+//      tour the same of those the first left, and so on.  The open tours come
+//      first, in opening order (a tour whose room falls below the instance's
+//      smallest order can never take another one), then new tours for the
+//      orders left.  A new tour takes all orders up to the first that does not
+//      fit by one running sum over the lanes; after that, as for an open tour,
+//      one ballot finds the next order that fits.  At the paper scale that is
+//      about 20 steps per 64 orders, and 4,096 plans take 0.309 ms, against
+//      0.546 when each order looked for its tour in turn; over half of it is
+//      this chain of steps, 16 plans per CU in turn.  Lane j also keeps the j-th open tour in
+//      opening order and its room; full tours leave the lanes only when the
+//      lanes run out.  The open tours stay few (first fit keeps filling the
+//      earliest ones), but any beyond 64 wait, in order, in a queue in global
+//      memory, which refills the lanes;
 //   2'. or seed batching: per position the order's size, aisle count and
 //      "new aisles" (for the tour being built) in one word, and per aisle the positions
 //      of the orders visiting it, all in LDS.  A tour starts from the
@@ -596,7 +604,7 @@ __global__ __launch_bounds__(64) void eval_ff_kernel(EvalArgs A)
                 const uint32_t below = __builtin_amdgcn_mbcnt_hi((uint32_t)(live >> 32),
                                                                  __builtin_amdgcn_mbcnt_lo((uint32_t)live, 0u));
                 // a permutation: open tours to lanes [0, nlive), the rest after them
-                const uint32_t dst = ((live >> lane) & 1ull) ? below : nlive + (uint32_t)lane - below;
+                const uint32_t dst = lane_in(live) ? below : nlive + (uint32_t)lane - below;
                 const uint32_t rr = (uint32_t)__builtin_amdgcn_ds_permute((int)(dst << 2), (int)room);
                 const uint32_t tt = (uint32_t)__builtin_amdgcn_ds_permute((int)(dst << 2), (int)tour);
                 room = (uint32_t)lane < nlive ? rr : 0u;
@@ -618,57 +626,91 @@ __global__ __launch_bounds__(64) void eval_ff_kernel(EvalArgs A)
                     qh = k < 64 ? min(qh + 64, qt) : qh + taken;
                 }
             };
+            // orders and sizes of the next windows load ahead: the sequence two
+            // windows, the sizes (a gather by order) one
+            auto order_at = [&](int i) { return (uint32_t)seq[min(i, n - 1)]; };
+            uint32_t o_n = min(order_at(lane), (uint32_t)n), o_n2 = order_at(64 + lane);
+            uint32_t s_n = cnt[o_n];
             for (int i0 = 0; i0 < n; i0 += 64) {
                 const int i = i0 + lane;
-                const uint32_t o_l = i < n ? min((uint32_t)seq[i], (uint32_t)n) : (uint32_t)n;
+                const uint32_t o_l = i < n ? o_n : (uint32_t)n;
                 // min(size, Q + 1); an id out of range (a malformed row, whose
                 // result is unspecified) counts as one item and is left out below
-                const uint32_t s_l = max((uint32_t)cnt[o_l], 1u);
-                const int m = __builtin_amdgcn_readfirstlane(min(64, n - i0));   // uniform: a scalar loop bound
+                const uint32_t s_l = i < n ? max(s_n, 1u) : 1u;
+                o_n = min(o_n2, (uint32_t)n);
+                s_n = cnt[o_n];
+                o_n2 = order_at(i + 128);
+                const int m = __builtin_amdgcn_readfirstlane(min(64, n - i0));
+                uint64_t alive = m == 64 ? ~0ull : (1ull << m) - 1ull;   // orders of the window in no tour (uniform)
                 uint32_t t_l = 0;                               // lane j: tour of position i0 + j
-    #pragma unroll 2
-                for (int j = 0; j < m; j++) {
-                    const uint32_t sz = (uint32_t)__builtin_amdgcn_readlane((int)s_l, j);
-                    // no order (of at least one item) fits room 0 or a room below mins
-                    const uint64_t hit = __ballot(room >= sz);
-                    uint32_t t = 0;
-                    if (hit) {                                   // the earliest tour in the lanes with room
-                        const int f = __builtin_ctzll(hit);
-                        t = (uint32_t)__builtin_amdgcn_readlane((int)tour, f);
-                        room = set_lane(room, (uint32_t)__builtin_amdgcn_readlane((int)room, f) - sz, f);
-                    } else {
-                        bool found = false;
-                        // the queued tours, in order, 64 at a time
-                        for (int b = qh; b < qt && !found; b += 64) {
-                            const uint32_t e = b + lane < qt ? queue[b + lane] : 0u;
-                            const uint64_t h = __ballot((e >> 16) >= sz);
-                            if (h) {
-                                const int f = __builtin_ctzll(h);
-                                const uint32_t ef = (uint32_t)__builtin_amdgcn_readlane((int)e, f);
-                                t = ef & 0xFFFFu;
-                                if (lane == 0) queue[b + f] = (((ef >> 16) - sz) << 16) | t;
-                                found = true;
-                            }
-                        }
-                        if (!found) {                            // no open tour has room: a new one
-                            t = (uint32_t)T++;
-                            const uint32_t r0 = sz <= (uint32_t)Q ? (uint32_t)Q - sz : 0u;   // a larger order rides alone
-                            if (r0 >= mins) {
-                                if (k == 64) compact();
-                                if (k < 64 && qh == qt) {
-                                    room = set_lane(room, r0, k);
-                                    tour = set_lane(tour, t, k);
-                                    k++;
-                                } else {
-                                    if (lane == 0) queue[qt] = (r0 << 16) | t;
-                                    qt++;
-                                }
-                            }
-                        }
-                        __threadfence_block();                   // queue stores before later loads of them
+                // a tour with room r takes, in sequence, every order of `rem`
+                // that fits what it then has left; returns that
+                auto fill = [&](uint32_t r, uint32_t t, uint64_t rem) -> uint32_t {
+                    uint64_t taken = 0;
+                    while (r >= mins) {
+                        rem &= __ballot(s_l <= r);
+                        if (!rem) break;
+                        const int j = (int)__builtin_ctzll(rem);
+                        r -= (uint32_t)__builtin_amdgcn_readlane((int)s_l, j);
+                        taken |= 1ull << j;
+                        rem &= rem - 1ull;                      // the next ones come after j
                     }
-                    t_l = set_lane(t_l, t, j);
+                    alive &= ~taken;
+                    t_l = lane_in(taken) ? t : t_l;
+                    return r;
+                };
+                // the open tours in opening order: those in the lanes, then the queued ones
+                for (uint64_t live = __ballot(room >= mins); live && alive; live &= live - 1ull) {
+                    const int f = (int)__builtin_ctzll(live);
+                    room = set_lane(room, fill((uint32_t)__builtin_amdgcn_readlane((int)room, f),
+                                               (uint32_t)__builtin_amdgcn_readlane((int)tour, f), alive), f);
                 }
+                for (int b = qh; b < qt && alive; b += 64) {
+                    const uint32_t e = b + lane < qt ? queue[b + lane] : 0u;
+                    uint32_t e_new = e;
+                    for (uint64_t live = __ballot((e >> 16) >= mins); live && alive; live &= live - 1ull) {
+                        const int f = (int)__builtin_ctzll(live);
+                        const uint32_t ef = (uint32_t)__builtin_amdgcn_readlane((int)e, f);
+                        e_new = set_lane(e_new, (fill(ef >> 16, ef & 0xFFFFu, alive) << 16) | (ef & 0xFFFFu), f);
+                    }
+                    if (b + lane < qt) queue[b + lane] = e_new;
+                }
+                // new tours for the orders left
+                while (alive) {
+                    const int j = (int)__builtin_ctzll(alive);
+                    const uint32_t sz = (uint32_t)__builtin_amdgcn_readlane((int)s_l, j);
+                    const uint32_t t = (uint32_t)T++;
+                    alive &= alive - 1ull;
+                    t_l = lane == j ? t : t_l;
+                    uint32_t r = sz <= (uint32_t)Q ? (uint32_t)Q - sz : 0u;   // a larger order rides alone
+                    if (r >= mins && alive) {
+                        // the orders up to the first that does not fit, at once
+                        // by their running sum, then one by one after it
+                        const uint32_t cum = wave_incl_scan(lane_in(alive) ? s_l : 0u);
+                        const uint64_t run = __ballot(cum <= r) & alive;
+                        const uint64_t rest = alive & ~run;
+                        if (run) {
+                            r -= (uint32_t)__builtin_amdgcn_readlane((int)cum, 63 - (int)__builtin_clzll(run));
+                            t_l = lane_in(run) ? t : t_l;
+                        }
+                        alive = rest;
+                        r = fill(r, t, rest & (rest - 1ull));
+                    }
+                    if (r >= mins) {
+                        if (k == 64) compact();
+                        if (k < 64 && qh == qt) {
+                            room = set_lane(room, r, k);
+                            tour = set_lane(tour, t, k);
+                            k++;
+                        } else {
+                            if (lane == 0) queue[qt] = (r << 16) | t;
+                            qt++;
+                        }
+                    }
+                }
+                // queue stores before later loads of them (not without a queue:
+                // the fence would wait for the loads ahead)
+                if (qh < qt) __threadfence_block();
                 // read after the tile loop's barrier
                 if (i < n && o_l < (uint32_t)n) tour_of[o_l] = (uint16_t)t_l;
             }
@@ -688,26 +730,42 @@ __global__ __launch_bounds__(64) void eval_ff_kernel(EvalArgs A)
                 const uint32_t *grec = A.grec + I.grec_off;
                 const uint32_t *gbase = A.gbase + I.gbase_off;
                 const uint16_t *gord = A.gord + I.gord_off;
+                // the next group's orders, tours and first lines load ahead
+                struct Group {
+                    uint32_t o, t, x[4], b0, len;
+                };
+                auto order_of = [&](int g) { return (uint32_t)gord[64 * min(g, I.n_grp - 1) + lane]; };   // 0xFFFF: no order
+                auto load = [&](int g, uint32_t o) -> Group {
+                    Group r;
+                    g = min(g, I.n_grp - 1);
+                    r.o = o;
+                    r.b0 = gbase[g];
+                    r.len = (gbase[g + 1] - r.b0) >> 6;                // lines of the group's longest order
+                    r.t = tour_of[min(o, (uint32_t)n)];                // entry n: no tour
+#pragma unroll
+                    for (int q = 0; q < 4; q++)                         // shorter orders repeat their first line
+                        r.x[q] = grec[r.b0 + 64u * min((uint32_t)q, r.len - 1u) + (uint32_t)lane];
+                    return r;
+                };
+                Group nx = load(0, order_of(0));
+                uint32_t o2 = order_of(1);
                 for (int g = 0; g < I.n_grp; g++) {
-                    const uint32_t o = gord[64 * g + lane];            // 0xFFFF: no order
-                    const uint32_t b0 = gbase[g];
-                    const uint32_t len = (gbase[g + 1] - b0) >> 6;     // lines of the group's longest order
-                    const uint32_t t = (o < (uint32_t)n ? (uint32_t)tour_of[o] : 0xFFFFu) - (uint32_t)t0;
+                    const Group c = nx;
+                    nx = load(g + 1, o2);
+                    o2 = order_of(g + 2);
+                    const uint32_t t = (c.o < (uint32_t)n ? c.t : 0xFFFFu) - (uint32_t)t0;
                     if (t >= (uint32_t)TILE) continue;
                     uint32_t far = 0;
-                    for (uint32_t k = 0; k < len; k += 4) {
-                        uint32_t x[4];
+                    auto add = [&](uint32_t x) {
+                        const uint32_t ls = x + zs[x >> 26];
+                        const uint32_t a = mulhi24(ls, I.magic);
+                        atomicOr(&rows[t * RW + 1u + (a >> 5)], 1u << (a & 31u));
+                        far = max(far, ls);
+                    };
 #pragma unroll
-                        for (int q = 0; q < 4; q++)                     // shorter orders repeat their first line
-                            x[q] = grec[b0 + 64u * min(k + (uint32_t)q, len - 1u) + (uint32_t)lane];
-#pragma unroll
-                        for (int q = 0; q < 4; q++) {
-                            const uint32_t ls = x[q] + zs[x[q] >> 26];
-                            const uint32_t a = mulhi24(ls, I.magic);
-                            atomicOr(&rows[t * RW + 1u + (a >> 5)], 1u << (a & 31u));
-                            far = max(far, ls);
-                        }
-                    }
+                    for (int q = 0; q < 4; q++)
+                        if ((uint32_t)q < c.len) add(c.x[q]);
+                    for (uint32_t k = 4; k < c.len; k++) add(grec[c.b0 + 64u * k + (uint32_t)lane]);
                     atomicMax(&rows[t * RW], far);
                 }
             } else {

@@ -261,7 +261,7 @@ __global__ __launch_bounds__(BR_THREADS) void breed_kernel(BreedArgs a)
                 const uint32_t k = (uint32_t)__popcll(b), inc = wave_incl_scan(k);
                 const uint64_t take = __ballot(in && inc <= (uint32_t)BR_LIST);   // consecutive words from w0
                 uint32_t at = inc - k;
-                if (!((take >> lane) & 1ull)) b = 0ull;
+                if (!lane_in(take)) b = 0ull;
                 while (b) {
                     list[at++] = (uint16_t)(blk + 64 * lane + (int)__builtin_ctzll(b));
                     b &= b - 1ull;

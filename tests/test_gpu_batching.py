@@ -276,3 +276,18 @@ def test_autotune_times_first_fit_once():
     d_gpu, _ = gpu_eval(wh, Z, S)
     wh.free()
     assert np.array_equal(d_gpu, oracle.eval_plans(_ff(inst), Z, S)[0])
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 128, 129])
+@pytest.mark.parametrize("Q", [1, 6, 32])
+def test_windows_of_the_sequence(n, Q):
+    # sequences around whole windows of 64 orders; sizes that leave every room
+    # open for a while (3, 5 and rarely 1 of 32), orders beyond the capacity
+    from tests.whelpers import tiny_geometry
+    rng = np.random.default_rng(1000 * n + Q)
+    lens = rng.choice([1, 3, 5, 7, 40], size=n, p=[0.05, 0.4, 0.4, 0.13, 0.02])
+    inst = tiny_geometry([[int(x) for x in rng.integers(0, 600, k)] for k in lens], capacity=Q)
+    inst = _ff(inst)
+    Z, S = synth.make_plans(inst, 5, seed=n)
+    print("windows", n, Q, flush=True)
+    _compare(inst, Z, S)
