@@ -27,12 +27,8 @@ namespace {
 constexpr int KM_MAX = 64;
 
 struct KmState {
-    long long S[KM_MAX], N[KM_MAX];       // centroids S / N
-    unsigned long long S2[KM_MAX], N2[KM_MAX];   // sums of the assignment in progress
-    long long cnt[KM_MAX];                // members after the last assignment
-    int changed, done, n_iter, pad;
+    int k_used, n_iter, err, pad;         // the results a caller reads, together
     int rank[KM_MAX];
-    int k_used;
 };
 
 // a * b < c * d for a, c < 2^47 and b, d < 2^23 (products up to 2^70: 128 bits)
@@ -49,14 +45,14 @@ __device__ __forceinline__ unsigned long long absdiff(long long x, long long y) 
 // gather in the workgroup's LDS first and reach memory once per workgroup.
 constexpr int KM_HOT_SKUS = 2048;
 __global__ __launch_bounds__(1024) void km_freq_kernel(const int32_t *skus, int64_t n_lines, int32_t n_skus,
-                                                       int32_t *freq, int32_t *err)
+                                                       int32_t *freq, KmState *st)
 {
     __shared__ int32_t hot[KM_HOT_SKUS];
     for (int i = threadIdx.x; i < KM_HOT_SKUS; i += blockDim.x) hot[i] = 0;
     __syncthreads();
     for (int64_t l = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; l < n_lines; l += (int64_t)gridDim.x * blockDim.x) {
         const int32_t s = skus[l];
-        if (s < 0 || s >= n_skus) atomicOr(err, 1);
+        if (s < 0 || s >= n_skus) atomicOr(&st->err, 1);
         else if (s < KM_HOT_SKUS) atomicAdd(&hot[s], 1);
         else atomicAdd(&freq[s], 1);
     }
@@ -107,112 +103,178 @@ __global__ void km_label_kernel(const int32_t *freq, int32_t n_skus, const int32
 
 // The whole iteration in one workgroup: the non-empty bins (the distinct
 // frequencies, at most sqrt(2 n_lines) + 1 <= KM_MAX_BINS of them since the
-// positive ones sum to at most n_lines) are compacted in order into LDS;
-// then the start, every assignment and centroid move, and the ranking run
-// with block barriers between them, and the bins' labels and the state go to
-// memory once.  The same steps as the kernels above, in one launch.
+// positive ones sum to at most n_lines) are compacted in order into LDS, 8
+// bins per thread and pass; then the start, every assignment and centroid
+// move, and the ranking run with block barriers between them, and the bins'
+// labels and the results go to memory once.
+//
+// There are about a hundred bins at the paper scale, and the assignment is a
+// chain of comparisons per bin: G = 2^g lanes share a bin, each taking every
+// G-th cluster, and the best of them follows in g exchanges (smallest distance,
+// ties to the lower index: associative, as the distances are exact).
+// EXACT64: n_lines * n_skus^2 < 2^53, which bounds every product of a
+// comparison, so that doubles hold them exactly; else 128-bit products.  10,006
+// lines over 150,000 SKUs, 16 classes, 9 assignments: 21 us, against 41 with one
+// lane per bin and 128-bit products throughout.
 constexpr int KM_MAX_BINS = 5800;
 constexpr int KM_BLOCK = 1024;
 
+template <bool EXACT64>
 __global__ __launch_bounds__(KM_BLOCK) void km_lloyd_kernel(const int32_t *hist, int32_t n_bins, int32_t k,
                                                            int32_t max_iter, int32_t *label, KmState *st)
 {
     __shared__ int32_t bv[KM_MAX_BINS], bm[KM_MAX_BINS];
     __shared__ uint8_t bl[KM_MAX_BINS];
-    __shared__ unsigned long long S2[KM_MAX], N2[KM_MAX];
+    __shared__ unsigned long long S2[KM_MAX];       // the assignment's sums: frequency total << 32 | members
     __shared__ long long S[KM_MAX], N[KM_MAX], cnt[KM_MAX];
-    __shared__ int part[KM_BLOCK / 64];
-    __shared__ int D_s, changed_s;
+    __shared__ double Sd[KM_MAX], Nd[KM_MAX];
+    __shared__ int part[2][KM_BLOCK / 64];
+    __shared__ int changed_s[2];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     // ---- compaction of the non-empty bins, in order of frequency
-    int base = 0;
-    int m_next = tid < n_bins ? hist[tid] : 0;       // each chunk's counts are read one chunk ahead
-    for (int v0 = 0; v0 < n_bins; v0 += KM_BLOCK) {
-        const int v = v0 + tid;
-        const int m = m_next;
-        m_next = v + KM_BLOCK < n_bins ? hist[v + KM_BLOCK] : 0;
-        const unsigned long long b = __ballot(m > 0);
-        const int below = __popcll(b & ((1ull << lane) - 1ull));
-        __syncthreads();                           // part[] of the previous chunk has been read
-        if (lane == 0) part[w] = __popcll(b);
-        __syncthreads();
-        int off = base;
-        for (int i = 0; i < w; i++) off += part[i];
-        if (m > 0 && off + below < KM_MAX_BINS) {
-            bv[off + below] = v;
-            bm[off + below] = m;
-            bl[off + below] = 0xFF;
+    int D = 0;
+    for (int v0 = 0, par = 0; v0 < n_bins; v0 += 8 * KM_BLOCK, par ^= 1) {
+        const int v = v0 + 8 * tid;                  // the array is padded to whole pieces of zeros
+        int m[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+        if (v < n_bins) {
+            const int4 x = *(const int4 *)(hist + v), y = *(const int4 *)(hist + v + 4);
+            m[0] = x.x; m[1] = x.y; m[2] = x.z; m[3] = x.w;
+            m[4] = y.x; m[5] = y.y; m[6] = y.z; m[7] = y.w;
         }
-        for (int i = 0; i < KM_BLOCK / 64; i++) base += part[i];
+        int own = 0;
+#pragma unroll
+        for (int j = 0; j < 8; j++) own += m[j] > 0;
+        int inc = own;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int u = __shfl_up(inc, d, 64);
+            if (lane >= d) inc += u;
+        }
+        if (lane == 63) part[par][w] = inc;
+        __syncthreads();                             // the other half is read before it is written again
+        int off = D + inc - own;
+#pragma unroll
+        for (int i = 0; i < KM_BLOCK / 64; i++) {
+            off += i < w ? part[par][i] : 0;
+            D += part[par][i];
+        }
+#pragma unroll
+        for (int j = 0; j < 8; j++)
+            if (m[j] > 0) {
+                if (off < KM_MAX_BINS) {
+                    bv[off] = v + j;
+                    bm[off] = m[j];
+                    bl[off] = 0xFF;
+                }
+                off++;
+            }
     }
-    if (tid == 0) D_s = min(base, KM_MAX_BINS);
+    D = min(D, KM_MAX_BINS);
     if (tid < KM_MAX) {
         S2[tid] = 0;
-        N2[tid] = 0;
         cnt[tid] = 0;
     }
+    if (tid < 2) changed_s[tid] = 0;
     __syncthreads();
-    const int D = D_s;
     // ---- start: centroid c is the distinct frequency of rank (2c + 1) D / (2k)
     if (tid < k) {
         const long long r = (2ll * tid + 1) * D / (2ll * k);
         S[tid] = bv[r];
         N[tid] = 1;
+        Sd[tid] = (double)bv[r];
+        Nd[tid] = 1.0;
     }
+    int g = 0;                                       // lanes per bin: 2^g, every one with a cluster
+    while (g < 6 && (2 << g) <= k && (D << (g + 1)) <= KM_BLOCK) g++;
+    const int G = 1 << g, sub = tid & (G - 1);
+    __syncthreads();
     int n_iter = 0;
     for (;;) {
-        if (tid == 0) changed_s = 0;
-        __syncthreads();
         // ---- assignment: the nearest centroid, exactly; ties to the lower index
-        for (int i = tid; i < D; i += KM_BLOCK) {
-            const long long v = bv[i];
-            int best = 0;
-            unsigned long long bd = absdiff(v * N[0], S[0]), bn = (unsigned long long)N[0];
-            for (int c = 1; c < k; c++) {
-                const unsigned long long dc = absdiff(v * N[c], S[c]);
-                const unsigned long long nc = (unsigned long long)N[c];
-                if (less_prod(dc, bn, bd, nc)) {
-                    best = c;
-                    bd = dc;
-                    bn = nc;
+        for (int i0 = 0; i0 < D; i0 += KM_BLOCK >> g) {
+            const int i = i0 + (tid >> g);
+            const int ic = min(i, D - 1);
+            int best = sub;
+            if (EXACT64) {
+                const double v = (double)bv[ic];
+                double bd = fabs(v * Nd[sub] - Sd[sub]), bn = Nd[sub];
+                for (int c = sub + G; c < k; c += G) {
+                    const double nc = Nd[c], dc = fabs(v * nc - Sd[c]);
+                    if (dc * bn < bd * nc) {
+                        best = c;
+                        bd = dc;
+                        bn = nc;
+                    }
+                }
+                for (int d = 1; d < G; d <<= 1) {
+                    const double pd = __shfl_xor(bd, d, 64), pn = __shfl_xor(bn, d, 64);
+                    const int pb = __shfl_xor(best, d, 64);
+                    const double x = pd * bn, y = bd * pn;
+                    if (x < y || (x == y && pb < best)) {
+                        best = pb;
+                        bd = pd;
+                        bn = pn;
+                    }
+                }
+            } else {
+                const long long v = bv[ic];
+                unsigned long long bd = absdiff(v * N[sub], S[sub]), bn = (unsigned long long)N[sub];
+                for (int c = sub + G; c < k; c += G) {
+                    const unsigned long long nc = (unsigned long long)N[c], dc = absdiff(v * N[c], S[c]);
+                    if (less_prod(dc, bn, bd, nc)) {
+                        best = c;
+                        bd = dc;
+                        bn = nc;
+                    }
+                }
+                for (int d = 1; d < G; d <<= 1) {
+                    const unsigned long long pd = __shfl_xor(bd, d, 64), pn = __shfl_xor(bn, d, 64);
+                    const int pb = __shfl_xor(best, d, 64);
+                    if (less_prod(pd, bn, bd, pn) || (pb < best && !less_prod(bd, pn, pd, bn))) {
+                        best = pb;
+                        bd = pd;
+                        bn = pn;
+                    }
                 }
             }
-            if (bl[i] != best) {
-                changed_s = 1;                     // benign race: every writer stores 1
-                bl[i] = (uint8_t)best;
+            if (i < D && sub == 0) {
+                if (bl[i] != best) {
+                    changed_s[n_iter & 1] = 1;         // benign race: every writer stores 1
+                    bl[i] = (uint8_t)best;
+                }
+                // frequencies sum to at most 2^24 and members to 2^22: both in one addition
+                atomicAdd(&S2[best], ((unsigned long long)bv[i] * (unsigned long long)bm[i]) << 32 | (unsigned long long)bm[i]);
             }
-            atomicAdd(&S2[best], (unsigned long long)v * (unsigned long long)bm[i]);
-            atomicAdd(&N2[best], (unsigned long long)bm[i]);
         }
         __syncthreads();
+        const int changed = changed_s[n_iter & 1];
         n_iter++;
-        const int changed = changed_s;
         // ---- centroids: each non-empty cluster moves to its members' mean
         if (tid < k) {
+            const unsigned long long s2 = S2[tid];
+            const long long ns = (long long)(s2 >> 32), nn = (long long)(s2 & 0xFFFFFFFFull);
             if (changed) {
-                cnt[tid] = (long long)N2[tid];
-                if (N2[tid] > 0) {
-                    S[tid] = (long long)S2[tid];
-                    N[tid] = (long long)N2[tid];
+                cnt[tid] = nn;
+                if (nn > 0) {
+                    S[tid] = ns;
+                    N[tid] = nn;
+                    Sd[tid] = (double)ns;
+                    Nd[tid] = (double)nn;
                 }
             }
             S2[tid] = 0;
-            N2[tid] = 0;
         }
+        if (tid == 0) changed_s[n_iter & 1] = 0;       // the next assignment's flag
         __syncthreads();
         if (!changed || n_iter >= max_iter) break;
     }
-    // ---- results: bin labels, state, ranks of the non-empty clusters
+    // ---- results: bin labels, ranks of the non-empty clusters
     for (int i = tid; i < D; i += KM_BLOCK) label[bv[i]] = bl[i];
     if (tid < KM_MAX) {
-        const bool in = tid < k;
-        st->S[tid] = in ? S[tid] : 0;
-        st->N[tid] = in ? N[tid] : 0;
-        st->cnt[tid] = in ? cnt[tid] : 0;
+        const bool used = tid < k && cnt[tid] > 0;
         int r = 0;
-        const bool used = in && cnt[tid] > 0;
         for (int d = 0; d < k; d++) {
-            if (cnt[d] <= 0) continue;
+            if (cnt[d] <= 0 || !used) continue;
             const long long a = S[d] * N[tid], b = S[tid] * N[d];
             r += a > b || (a == b && d < tid);
         }
@@ -221,45 +283,64 @@ __global__ __launch_bounds__(KM_BLOCK) void km_lloyd_kernel(const int32_t *hist,
         if (tid == 0) {
             st->k_used = __popcll(u);
             st->n_iter = n_iter;
-            st->done = 1;
         }
     }
 }
 
 int grid_for(int64_t n, int block) { return (int)std::min<int64_t>(std::max<int64_t>((n + block - 1) / block, 1), 4096); }
 
-// Scratch layout of one call: frequencies [n_skus], histogram [n_bins], bin
-// labels [n_bins], the state, the error flag; each part starts on 256 bytes.
+// Scratch layout of one call: frequencies [n_skus], histogram [n_bins], the
+// state (these start at zero), then bin labels [n_bins] (those of the bins in use
+// are written before they are read); each part starts on 256 bytes.
 struct KmLayout {
-    size_t o_hist, o_label, o_state, o_err, bytes;
+    size_t o_hist, o_state, o_label, bytes;
 };
 
 KmLayout km_layout(int32_t n_skus, int32_t n_bins)
 {
     KmLayout L;
     L.o_hist = ((size_t)n_skus * 4 + 255) & ~(size_t)255;
-    L.o_label = L.o_hist + (((size_t)n_bins * 4 + 255) & ~(size_t)255);
-    L.o_state = L.o_label + (((size_t)n_bins * 4 + 255) & ~(size_t)255);
-    L.o_err = L.o_state + ((sizeof(KmState) + 255) & ~(size_t)255);
-    L.bytes = L.o_err + 256;
+    L.o_state = L.o_hist + (((size_t)n_bins * 4 + 255) & ~(size_t)255);
+    L.o_label = L.o_state + ((sizeof(KmState) + 255) & ~(size_t)255);
+    L.bytes = L.o_label + (((size_t)n_bins * 4 + 255) & ~(size_t)255);
     return L;
 }
 
-// Fills words [0, n) with v: clears the scratch of the allocation-free
-// variant inside the stream (a kernel rather than a memset, so that the
-// call can sit in a captured graph).
-__global__ void km_fill_kernel(int32_t *p, int64_t n, int32_t v)
+// Clears n 16-byte pieces: the scratch, inside the stream (a kernel rather
+// than a memset, so that a call can sit in a captured graph).
+__global__ void km_clear_kernel(uint4 *p, int64_t n)
 {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = v;
+        p[i] = make_uint4(0u, 0u, 0u, 0u);
 }
 
 // Results of the allocation-free variant, written on the device.
-__global__ void km_finish_kernel(const KmState *st, const int32_t *err, int32_t *k_used, int32_t *n_iter)
+__global__ void km_finish_kernel(const KmState *st, int32_t *k_used, int32_t *n_iter)
 {
     if (threadIdx.x != 0) return;
-    if (k_used) *k_used = *err ? -1 : st->k_used;
+    if (k_used) *k_used = st->err ? -1 : st->k_used;
     if (n_iter) *n_iter = st->n_iter;
+}
+
+// The launches of a call on its scratch.
+hipError_t km_launch(char *buf, const KmLayout &L, const int32_t *skus, int64_t n_lines, int32_t n_skus, int32_t k,
+                     int32_t max_iter, int32_t *category, hipStream_t s)
+{
+    int32_t *freq = (int32_t *)buf, *hist = (int32_t *)(buf + L.o_hist), *label = (int32_t *)(buf + L.o_label);
+    KmState *st = (KmState *)(buf + L.o_state);
+    const int32_t n_bins = (int32_t)n_lines + 1;
+    const bool exact64 = (double)n_lines * (double)n_skus * (double)n_skus < 9007199254740992.0;
+    hipLaunchKernelGGL(km_clear_kernel, dim3(grid_for((int64_t)L.o_label / 16, 256)), dim3(256), 0, s, (uint4 *)buf,
+                       (int64_t)L.o_label / 16);
+    hipLaunchKernelGGL(km_freq_kernel, dim3(std::min(grid_for(n_lines, 1024), 64)), dim3(1024), 0, s, skus, n_lines, n_skus,
+                       freq, st);
+    hipLaunchKernelGGL(km_hist_kernel, dim3(std::min(grid_for(n_skus, 1024), 128)), dim3(1024), 0, s, freq, n_skus, hist);
+    if (exact64)
+        hipLaunchKernelGGL(km_lloyd_kernel<true>, dim3(1), dim3(KM_BLOCK), 0, s, hist, n_bins, k, max_iter, label, st);
+    else
+        hipLaunchKernelGGL(km_lloyd_kernel<false>, dim3(1), dim3(KM_BLOCK), 0, s, hist, n_bins, k, max_iter, label, st);
+    hipLaunchKernelGGL(km_label_kernel, dim3(grid_for(n_skus, 256)), dim3(256), 0, s, freq, n_skus, label, st, category);
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -310,45 +391,28 @@ extern "C" wo_status wo_kmeans_categories(const int32_t *d_order_skus, int64_t n
     if (max_iter < 1) return wo_fail(WO_E_INVAL, "max_iter must be >= 1");
     hipStream_t s = (hipStream_t)stream;
     const int32_t n_bins = (int32_t)n_lines + 1;      // a frequency is at most n_lines
-    // scratch: frequencies, histogram, bin labels, state, error flag
     char *buf = nullptr;
     const KmLayout Ly = km_layout(n_skus, n_bins);
-    const size_t o_hist = Ly.o_hist, o_label = Ly.o_label, o_state = Ly.o_state, o_err = Ly.o_err;
-    const size_t bytes = Ly.bytes;
     if (wo_fault_injected()) return wo_fail(WO_E_NOMEM, "injected allocation failure");
-    if (hipMalloc((void **)&buf, bytes) != hipSuccess) {
+    if (hipMalloc((void **)&buf, Ly.bytes) != hipSuccess) {
         (void)hipGetLastError();
-        return wo_fail(WO_E_NOMEM, "hipMalloc(%zu) failed", bytes);
+        return wo_fail(WO_E_NOMEM, "hipMalloc(%zu) failed", Ly.bytes);
     }
-    int32_t *freq = (int32_t *)buf, *hist = (int32_t *)(buf + o_hist), *label = (int32_t *)(buf + o_label);
-    KmState *st = (KmState *)(buf + o_state);
-    int32_t *err = (int32_t *)(buf + o_err);
     wo_status ret = WO_OK;
-    int32_t h_err = 0;
-    KmState h{};
+    int32_t h[3] = {0, 0, 0};                         // k_used, n_iter, err
     auto run = [&]() -> wo_status {
-        WO_HIP(hipMemsetAsync(buf, 0, o_label, s));                       // frequencies, histogram
-        WO_HIP(hipMemsetAsync(label, 0xFF, o_state - o_label, s));        // no cluster yet
-        WO_HIP(hipMemsetAsync(st, 0, bytes - o_state, s));                // state, error flag
-        hipLaunchKernelGGL(km_freq_kernel, dim3(std::min(grid_for(n_lines, 1024), 64)), dim3(1024), 0, s, d_order_skus, n_lines,
-                           n_skus, freq, err);
-        hipLaunchKernelGGL(km_hist_kernel, dim3(std::min(grid_for(n_skus, 1024), 128)), dim3(1024), 0, s, freq, n_skus, hist);
-        hipLaunchKernelGGL(km_lloyd_kernel, dim3(1), dim3(KM_BLOCK), 0, s, hist, n_bins, k, max_iter, label, st);
-        hipLaunchKernelGGL(km_label_kernel, dim3(grid_for(n_skus, 256)), dim3(256), 0, s, freq, n_skus, label, st,
-                           d_category);
-        WO_HIP(hipGetLastError());
-        WO_HIP(hipMemcpyAsync(&h, st, sizeof(KmState), hipMemcpyDeviceToHost, s));
-        WO_HIP(hipMemcpyAsync(&h_err, err, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+        WO_HIP(km_launch(buf, Ly, d_order_skus, n_lines, n_skus, k, max_iter, d_category, s));
+        WO_HIP(hipMemcpyAsync(h, buf + Ly.o_state, sizeof h, hipMemcpyDeviceToHost, s));
         WO_HIP(hipStreamSynchronize(s));
-        if (h_err) return wo_fail(WO_E_INVAL, "an order line names a SKU outside 0 .. %d", n_skus - 1);
+        if (h[2]) return wo_fail(WO_E_INVAL, "an order line names a SKU outside 0 .. %d", n_skus - 1);
         return WO_OK;
     };
     ret = run();
-    (void)hipStreamSynchronize(s);
+    if (ret != WO_OK) (void)hipStreamSynchronize(s);
     (void)hipFree(buf);
     if (ret == WO_OK) {
-        if (k_used) *k_used = h.k_used;
-        if (n_iter) *n_iter = h.n_iter;
+        if (k_used) *k_used = h[0];
+        if (n_iter) *n_iter = h[1];
     }
     return ret;
 }
@@ -375,23 +439,11 @@ extern "C" wo_status wo_kmeans_categories_noalloc(const int32_t *d_order_skus, i
     if (st0) return st0;
     hipStream_t s = (hipStream_t)stream;
     char *buf = (char *)base;
-    int32_t *freq = (int32_t *)buf, *hist = (int32_t *)(buf + Ly.o_hist), *label = (int32_t *)(buf + Ly.o_label);
-    KmState *st = (KmState *)(buf + Ly.o_state);
-    int32_t *err = (int32_t *)(buf + Ly.o_err);
-    // the previous call's contents stay in the array: clear what starts at
-    // zero (frequencies, histogram, state, flag) and mark no cluster yet
-    const int64_t w_lab = (int64_t)(Ly.o_state - Ly.o_label) / 4, w_state = (int64_t)(Ly.bytes - Ly.o_state) / 4;
-    hipLaunchKernelGGL(km_fill_kernel, dim3(grid_for((int64_t)Ly.o_label / 4, 256)), dim3(256), 0, s, freq,
-                       (int64_t)Ly.o_label / 4, 0);
-    hipLaunchKernelGGL(km_fill_kernel, dim3(grid_for(w_lab, 256)), dim3(256), 0, s, label, w_lab, -1);
-    hipLaunchKernelGGL(km_fill_kernel, dim3(1), dim3(256), 0, s, (int32_t *)st, w_state, 0);
-    hipLaunchKernelGGL(km_freq_kernel, dim3(std::min(grid_for(n_lines, 1024), 64)), dim3(1024), 0, s, d_order_skus, n_lines, n_skus,
-                       freq, err);
-    hipLaunchKernelGGL(km_hist_kernel, dim3(std::min(grid_for(n_skus, 1024), 128)), dim3(1024), 0, s, freq, n_skus, hist);
-    hipLaunchKernelGGL(km_lloyd_kernel, dim3(1), dim3(KM_BLOCK), 0, s, hist, n_bins, k, max_iter, label, st);
-    hipLaunchKernelGGL(km_label_kernel, dim3(grid_for(n_skus, 256)), dim3(256), 0, s, freq, n_skus, label, st,
-                       d_category);
-    hipLaunchKernelGGL(km_finish_kernel, dim3(1), dim3(64), 0, s, st, err, d_k_used, d_n_iter);
+    // the previous call's contents stay in the array: what starts at zero is
+    // cleared first
+    WO_HIP(km_launch(buf, Ly, d_order_skus, n_lines, n_skus, k, max_iter, d_category, s));
+    const KmState *st = (const KmState *)(buf + Ly.o_state);
+    hipLaunchKernelGGL(km_finish_kernel, dim3(1), dim3(64), 0, s, st, d_k_used, d_n_iter);
     WO_HIP(hipGetLastError());
     return WO_OK;
 }

@@ -86,3 +86,16 @@ def test_categories_feed_the_evaluator():
     wh.free()
     d_ref, _ = oracle.eval_plans(inst2, Z, S)
     assert np.array_equal(d, d_ref)
+
+
+@pytest.mark.parametrize("n_skus,n_lines,k", [
+    (1 << 21, 2047, 64), (1 << 21, 2048, 64),      # products just under 2^53, and at it
+    (40, 40, 64), (200, 3000, 33), (9, 500, 5),    # few distinct frequencies: many lanes share one
+    (3000, 8191, 7), (3000, 8192, 7),              # histograms of one pass of bins, and of one bin more
+])
+def test_comparison_forms_and_bins(n_skus, n_lines, k):
+    rng = np.random.default_rng(n_skus + n_lines)
+    skus = np.minimum(rng.zipf(1.4, size=n_lines) - 1, n_skus - 1)
+    skus[: n_lines // 4] = np.arange(n_lines // 4) % min(n_skus, 7) // 2 * 2     # equal frequencies
+    print("forms", n_skus, n_lines, k, flush=True)
+    _compare(skus, n_skus, k)
