@@ -535,9 +535,11 @@ typedef struct {
 } wo_aisle_result;
 
 /* Evaluates the plan of instance `inst` (d_zone_of: 64 bytes, d_order_seq:
- * n_orders uint16 on the device) at every whole-decimetre width of the range
+ * n_orders uint16 on the device) for every whole-decimetre width of the range
  * in one launch of the exact evaluator, each copy of the plan with its own
- * spacing (the load's spacing_dm is not used), and returns the narrowest
+ * spacing (the load's spacing_dm is not used; a distance is affine in the
+ * spacing except under the optimal route, so that two copies give the others),
+ * and returns the narrowest
  * width meeting the constraint, deciding each width in IEEE double from the
  * integer distance.  h_dist (host int32[max - min + 1], nullable) receives
  * D at every width.  The handle's route and batching apply; the optimal

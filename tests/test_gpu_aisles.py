@@ -70,3 +70,26 @@ def test_single_width_and_odd_order_count():
     print("odd order count", flush=True)
     _compare(inst, Z[0], S[0], k=0.05, a_min=17, a_max=17)
     _compare(inst, Z[0], S[0], k=0.05, a_min=3, a_max=90)
+
+
+@pytest.mark.parametrize("route,batching", [(0, 2), (1, 2), (2, 1), (4, 2), (4, 1)])
+def test_affine_routes_under_every_batching(route, batching):
+    inst, Z, S = synth.workload("tiny", n_plans=1)
+    inst = dataclasses.replace(inst, routing=route, batching=batching)
+    print("affine", route, batching, flush=True)
+    _compare(inst, Z[0], S[0], k=0.05, a_min=8, a_max=9)
+    _compare(inst, Z[0], S[0], k=0.05, a_min=30, a_max=75)
+
+
+@pytest.mark.parametrize("below", [12, 2, 1, 0, -3])
+def test_widths_where_the_distance_saturates(below):
+    # ranges that reach the int32 limit after some widths, at the second, at
+    # the first, and that lie beyond it
+    inst, Z, S = synth.workload("tiny", n_plans=1)
+    d0, d1 = (A.distance_at(inst, Z[0], S[0], w) for w in (1000, 1001))
+    limit = 1000 + (2 ** 31 - 1 - d0) // (d1 - d0)           # the last spacing below it
+    a_min = limit - 20 - below + 1
+    print("saturating", below, flush=True)
+    _, dist = _run(inst, Z[0], S[0], 10, 20, 0.05, a_min, a_min + 15)
+    want = [min(d0 + (w - 1000) * (d1 - d0), 2 ** 31 - 1) for w in range(a_min + 20, a_min + 36)]
+    assert dist.tolist() == want
