@@ -814,11 +814,7 @@ __global__ __launch_bounds__(BLOCK, ROUTE == WO_ROUTE_SSHAPE ? 4 : 2) void eval_
                         const uint32_t *rw = (const uint32_t *)(smem + LDS_REGION + (uint32_t)t * RB);
                         const uint32_t np = rw[0];                 // >= 1: a tour has picks
                         if (np > (uint32_t)I.pick_slots) continue; // an order routed apart (below)
-                        uint32_t v[MAX_PICK_SLOTS];
-#pragma unroll
-                        for (int i = 0; i < MAX_PICK_SLOTS; i++) v[i] = (uint32_t)i < np ? rw[1 + i] : 0xFFFFFFFFu;
-                        sort32(v);
-                        acc += pick_route_cost<ROUTE>(v, np, wsp, I, magic);
+                        acc += pick_route_cost<ROUTE>(rw + 1, np, wsp, I, magic);
                     }
                     continue;
                 }

@@ -55,6 +55,21 @@ static __device__ __forceinline__ uint32_t mulhi24(uint32_t x, uint32_t m)
     return (uint32_t)(((uint64_t)(x & 0xFFFFFFu) * (uint64_t)(m & 0xFFFFFFu)) >> 32);
 }
 
+// a * b and a * b + c by the low 24 bits of a and b: full-rate instructions,
+// which the compiler does not see past a value that it cannot bound.
+static __device__ __forceinline__ uint32_t mul24(uint32_t a, uint32_t b)
+{
+    uint32_t r;
+    asm("v_mul_u32_u24 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+static __device__ __forceinline__ uint32_t mad24(uint32_t a, uint32_t b, uint32_t c)
+{
+    uint32_t r;
+    asm("v_mad_u32_u24 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+
 static __device__ __forceinline__ float window_throughput(int64_t D, const InstDev &I)
 {
     // T = D / walk + t_item * items; orders * window / T: IEEE double, one
@@ -81,21 +96,23 @@ static __device__ __forceinline__ int instance_of(const EvalArgs &A, int64_t p)
     return lo;
 }
 
-// Ascending bitonic sort of 32 words held in registers (straight-line min/max).
+// Ascending sort of 32 words held in registers: Batcher's odd-even merge
+// network, 191 exchanges of straight-line min and max (a bitonic one has 240).
 static __device__ __forceinline__ void sort32(uint32_t (&v)[MAX_PICK_SLOTS])
 {
 #pragma unroll
-    for (int k = 2; k <= MAX_PICK_SLOTS; k <<= 1)
+    for (int p = 1; p < MAX_PICK_SLOTS; p <<= 1)
 #pragma unroll
-        for (int j = k >> 1; j > 0; j >>= 1)
+        for (int k = p; k > 0; k >>= 1)
 #pragma unroll
             for (int i = 0; i < MAX_PICK_SLOTS; i++) {
-                const int l = i ^ j;
-                if (l > i) {
+                const int l = i + k;
+                // pairs k apart from k % p on, inside one block of 2 p
+                const bool pair = i >= k % p && ((i - k % p) & k) == 0 && l < MAX_PICK_SLOTS && i / (2 * p) == l / (2 * p);
+                if (pair) {
                     const uint32_t a = v[i], b = v[l];
-                    const bool up = (i & k) == 0;
-                    v[i] = up ? min(a, b) : max(a, b);
-                    v[l] = up ? max(a, b) : min(a, b);
+                    v[i] = min(a, b);
+                    v[l] = max(a, b);
                 }
             }
 }
@@ -109,52 +126,58 @@ static __device__ __forceinline__ void sort32(uint32_t (&v)[MAX_PICK_SLOTS])
 //   B : only b in the walk (even degree);
 //   E1: f and b of even degree, one component;
 //   E2: f and b of even degree, two components.
-// A tour's distances are bounded at load so that every class cost, including
-// the unreachable value OPT_INF plus any sum of additions, stays below 2^31.
-#define OPT_INF 0x40000000
-struct OptClasses { int32_t o1, f, b, e1, e2; };
+// The costs leave out 2w for every step along the cross aisles, which every
+// walk pays at least, so a step costs nothing in O1, F and B (one edge each way,
+// or both on one side) and 2w in E1 and E2 (4w in all).  They are unsigned: a
+// tour's distances are bounded at load so that every class cost stays below
+// 2^30, and the unreachable value OPT_INF plus any sum of additions below 2^32.
+// The programme is the larger part of the route's time (30 picks of a tour on
+// one lane, a chain of dependent minima), so each form below is the shortest
+// one found; the identities that shorten it are exact.
+#define OPT_INF 0x40000000u
+struct OptClasses { uint32_t o1, f, b, e1, e2; };
 
-// Carry the classes over r >= 1 steps along the cross aisles to the next
-// aisle with picks (r - 1 aisles without picks in between).  One step costs
-// 2w in O1, F and B (one edge each way, or both on one side) and 4w in E1 and
-// E2.  In the aisles passed, a class may change by a crossing (cost L) or a
-// double crossing (2 L); the cheapest such change is taken as early as it
-// lowers the step cost and as late as it raises it, which gives these forms.
-static __device__ __forceinline__ void opt_run(OptClasses &s, int32_t r, int32_t w, int32_t L)
+// The classes before the first aisle with picks, r steps from the depot at
+// the front of aisle 0; without picks that aisle may be crossed once (O1) or
+// twice (E1, and B once its front end is dropped).
+static __device__ __forceinline__ OptClasses opt_start(uint32_t r, uint32_t w2, uint32_t L)
 {
-    const int32_t a = 2 * w;
-    const int32_t ar = a * r, ar1 = ar + a, ar2 = ar1 + a;
-    const int32_t m_fbe = min(min(s.f, s.b), s.e1);
-    OptClasses n;
-    n.o1 = s.o1 + ar;
-    n.f = min(s.f, s.e1) + ar;            // E1 drops its back end
-    n.b = min(s.b, s.e1) + ar;
-    n.e1 = s.e1 + 2 * ar;
-    n.e2 = s.e2 + 2 * ar;
-    if (r >= 2) {                         // an aisle without picks lies in between
-        n.o1 = min(n.o1, min(m_fbe + ar, s.e2 + ar1) + L);
-        n.f = min(n.f, min(min(s.o1 + ar + L, s.b + ar + 2 * L), s.e2 + ar1 + 2 * L));
-        n.b = min(n.b, min(min(s.o1 + ar + L, s.f + ar + 2 * L), s.e2 + ar1 + 2 * L));
-        n.e1 = min(n.e1, min(min(s.o1 + ar1 + L, m_fbe + ar1 + 2 * L), s.e2 + ar2 + 2 * L));
-    }
-    s = n;
+    return {r ? L : OPT_INF, 0u, r ? 2u * L : OPT_INF, r ? 2u * L + w2 : OPT_INF, OPT_INF};
+}
+
+// Carry the classes over r >= 1 steps to the next aisle with picks (r - 1
+// aisles without picks in between; ar = 2w r, w2 = 2w).  E1 may drop an end.  In
+// the aisles passed, a class may change by a crossing (cost L) or a double
+// crossing (2 L); the cheapest such change is taken as early as it lowers the
+// step cost and as late as it raises it.  Every double crossing is two single
+// ones by way of O1, so that X = O1 + L, O1 being the new one, stands for all
+// that lead to F, B and E1.  Afterwards F, B < E1.
+static __device__ __forceinline__ void opt_run(OptClasses &s, uint32_t r, uint32_t ar, uint32_t w2, uint32_t L)
+{
+    const uint32_t Lr = r >= 2u ? L : OPT_INF;      // no aisle without picks: no change
+    const uint32_t m = min(min(s.f, s.b), s.e1);
+    s.o1 = min(s.o1, min(m, s.e2 + w2) + Lr);
+    const uint32_t X = s.o1 + Lr;
+    s.f = min(min(s.f, s.e1), X);
+    s.b = min(min(s.b, s.e1), X);
+    s.e1 = min(s.e1 + ar, X + w2);
+    s.e2 += ar;
 }
 
 // The aisle's own edges: a crossing (L), a double crossing (2 L), in from the
 // front to the last pick (cF), in from the back to the first pick (cB), or in
 // from both sides leaving out the largest gap between two picks (cG; 2 L when
 // the aisle has a single pick, which never beats cF or cB then).
-static __device__ __forceinline__ void opt_aisle(OptClasses &s, int32_t L, int32_t cF, int32_t cB, int32_t cG)
+static __device__ __forceinline__ void opt_aisle(OptClasses &s, uint32_t L, uint32_t cF, uint32_t cB, uint32_t cG)
 {
-    const int32_t cmin = min(min(cF, cB), cG);
-    const int32_t m_even = min(min(s.f, s.b), min(s.e1, s.e2));
-    OptClasses n;
-    n.o1 = min(s.o1 + cmin, m_even + L);
-    n.f = s.f + cF;
-    n.b = s.b + cB;
-    n.e1 = min(min(s.o1 + L, s.e1 + cmin), m_even + 2 * L);
-    n.e2 = min(min(s.f + min(cB, cG), s.b + min(cF, cG)), s.e2 + cmin);
-    s = n;
+    const uint32_t cBG = min(cB, cG), cFG = min(cF, cG), cmin = min(cF, cBG);
+    const uint32_t m = min(min(s.f, s.b), s.e2);    // E1 is above F here
+    const uint32_t o1 = s.o1;
+    s.o1 = min(o1 + cmin, m + L);
+    s.e2 = min(min(s.f + cBG, s.b + cFG), s.e2 + cmin);
+    s.e1 = min(min(o1 + L, s.e1 + cmin), m + 2u * L);
+    s.f += cF;
+    s.b += cB;
 }
 
 // Walk of one tour for the return, largest-gap, combined or optimal route,
@@ -167,38 +190,41 @@ struct PickWalk {
     uint32_t magic;
     int32_t spacing;
     uint32_t ca, a_lo;                // current aisle, first aisle
-    // optimal: the five classes, the last aisle decided, first and last
-    // depth in the current aisle and its largest gap (-1: one pick)
+    // optimal: the five classes at the current aisle, its first and last
+    // depth and its largest gap (0: one pick); all three doubled
     OptClasses s;
-    uint32_t done;
-    int32_t ylo, yhi, gap;
-    // combined: the best walks ending on the front and on the back
+    uint32_t ylo, yhi, gap;
+    // combined: the best walks ending on the front and on the back, the last
+    // aisle decided; depths as they are
     int64_t front, back;
+    uint32_t done;
     // return / largest gap: previous depth in the aisle (front: 0), largest
     // gap so far in it, and the sum over closed aisles
     int32_t py, g;
     int64_t sum;
 
-    __device__ __forceinline__ int32_t depth(uint32_t ls, uint32_t a) const
+    // the depth of a scaled location in aisle a.  Locations take 24 bits, so
+    // a * d_s does (d_s itself only takes a 25th in a single aisle, a = 0), but a
+    // pitch may not: its index times it is two 24-bit products, each at the
+    // full rate (a 32-bit one runs at a quarter of it).
+    template <int DOUBLED = 0>
+    __device__ __forceinline__ uint32_t depth(uint32_t ls, uint32_t a) const
     {
-        return (int32_t)((ls - a * I.d_s) >> (I.shift + 1)) * I.pitch + I.pitch / 2;
+        const uint32_t j = (ls - mul24(a, I.d_s)) >> (I.shift + 1), p = (uint32_t)I.pitch;
+        return mad24(j, (p & 0xFFFu) << DOUBLED, (p / 2u) << DOUBLED) + (mul24(j, p >> 12) << (12 + DOUBLED));
     }
 
     __device__ __forceinline__ PickWalk(const InstDev &inst, int32_t sp, uint32_t m, uint32_t first)
         : I(inst), magic(m), spacing(sp)
     {
-        const int32_t L = I.L;
         ca = mulhi24(first, magic);
         a_lo = ca;
-        const int32_t y = depth(first, ca);
+        const uint32_t y = depth<ROUTE == WO_ROUTE_OPTIMAL>(first, ca);
         if (ROUTE == WO_ROUTE_OPTIMAL) {
-            // start: the depot at the front of aisle 0; if aisle 0 holds no
-            // pick it may still be crossed once or twice
-            s = {a_lo ? L : OPT_INF, 0, OPT_INF, a_lo ? 2 * L : OPT_INF, OPT_INF};
-            done = 0;
+            s = opt_start(ca, 2u * (uint32_t)spacing, (uint32_t)I.L);
             ylo = y;
             yhi = y;
-            gap = -1;
+            gap = 0;
         } else if (ROUTE == WO_ROUTE_COMBINED) {
             front = 0;
             back = (int64_t)1 << 60;      // the back is not reachable yet
@@ -207,28 +233,36 @@ struct PickWalk {
             yhi = y;
         } else {
             sum = 0;
-            g = y;
-            py = y;
+            g = (int32_t)y;
+            py = (int32_t)y;
         }
     }
 
+    // Another pick; one that repeats the last (the same aisle and depth)
+    // changes nothing.
     __device__ __forceinline__ void step(uint32_t ls)
     {
         const int32_t L = I.L;
-        const uint32_t a = mulhi24(ls, magic);
-        const int32_t y = depth(ls, a);
+        uint32_t a = mulhi24(ls, magic);
+        asm("" : "+v"(a));                // 32 bits: no 64-bit compare with ca
+        const uint32_t yu = depth<ROUTE == WO_ROUTE_OPTIMAL>(ls, a);
         if (ROUTE == WO_ROUTE_OPTIMAL) {
-            if (a != ca) {                // aisle ca is complete
-                if (ca != done) opt_run(s, (int32_t)(ca - done), spacing, L);
-                opt_aisle(s, L, 2 * yhi, 2 * (L - ylo), gap >= 0 ? 2 * (L - gap) : 2 * L);
-                done = ca;
-                ca = a;
-                ylo = y;
-                gap = -1;
-            } else {
-                gap = max(gap, y - yhi);
+            // The lanes whose aisle ca is complete.  The mask is made opaque
+            // for the selects below, which the compiler would else move into
+            // the other side of the branch.
+            const uint64_t closes = __builtin_amdgcn_ballot_w64(a != ca);
+            uint64_t sel = closes;
+            asm("" : "+s"(sel));
+            if (lane_in(closes)) {
+                const uint32_t w = (uint32_t)spacing, r = a - ca;
+                opt_aisle(s, (uint32_t)L, yhi, 2u * (uint32_t)L - ylo, 2u * (uint32_t)L - gap);
+                // the spacing may pass 23 bits where the aisles are few
+                opt_run(s, r, mul24(r, (w & 0x7FFFFFu) << 1) + (mul24(r, w >> 23) << 24), 2u * w, (uint32_t)L);
             }
-            yhi = y;
+            gap = lane_in(sel) ? 0u : max(gap, yu - yhi);
+            ylo = lane_in(sel) ? yu : ylo;
+            yhi = yu;
+            ca = a;
         } else if (ROUTE == WO_ROUTE_COMBINED) {
             // each aisle with picks crossed or entered and left from the
             // cross aisle the picker is on, best choice by one length per
@@ -240,10 +274,11 @@ struct PickWalk {
                 back = b2 + st;
                 done = ca;
                 ca = a;
-                ylo = y;
+                ylo = yu;
             }
-            yhi = y;
+            yhi = yu;
         } else {
+            const int32_t y = (int32_t)yu;
             if (a != ca) {                // close aisle ca
                 if (ROUTE == WO_ROUTE_RETURN) {
                     sum += py;
@@ -264,9 +299,9 @@ struct PickWalk {
     {
         const int32_t L = I.L;
         if (ROUTE == WO_ROUTE_OPTIMAL) {
-            if (ca != done) opt_run(s, (int32_t)(ca - done), spacing, L);
-            opt_aisle(s, L, 2 * yhi, 2 * (L - ylo), gap >= 0 ? 2 * (L - gap) : 2 * L);
-            return (int64_t)min(min(s.f, s.b), s.e1);   // even ends, one component
+            opt_aisle(s, (uint32_t)L, yhi, 2u * (uint32_t)L - ylo, 2u * (uint32_t)L - gap);
+            // even ends, one component; and the way along the cross aisles
+            return (int64_t)(min(min(s.f, s.b), s.e1) + 2u * (uint32_t)spacing * ca);
         }
         if (ROUTE == WO_ROUTE_COMBINED) {
             // the walk ends on the front (crossing the last aisle from the back)
@@ -281,16 +316,21 @@ struct PickWalk {
     }
 };
 
-// Route cost of one tour from its np (1 .. MAX_PICK_SLOTS) sorted picks in
-// registers.
+// Route cost of one tour from its row of np (1 .. pick_slots) picks.  The
+// slots past np repeat the first pick, which changes no route and spares
+// each step a look at np.
 template <int ROUTE>
-static __device__ __forceinline__ int64_t pick_route_cost(const uint32_t (&v)[MAX_PICK_SLOTS], uint32_t np, int32_t spacing,
+static __device__ __forceinline__ int64_t pick_route_cost(const uint32_t *picks, uint32_t np, int32_t spacing,
                                                           const InstDev &I, uint32_t magic)
 {
+    uint32_t v[MAX_PICK_SLOTS];
+    v[0] = picks[0];
+#pragma unroll
+    for (int i = 1; i < MAX_PICK_SLOTS; i++) v[i] = (uint32_t)i < np ? picks[i] : v[0];
+    sort32(v);
     PickWalk<ROUTE> w(I, spacing, magic, v[0]);
 #pragma unroll
-    for (int i = 1; i < MAX_PICK_SLOTS; i++)
-        if ((uint32_t)i < np) w.step(v[i]);
+    for (int i = 1; i < MAX_PICK_SLOTS; i++) w.step(v[i]);
     return w.cost();
 }
 

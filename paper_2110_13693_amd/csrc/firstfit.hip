@@ -800,11 +800,7 @@ __global__ __launch_bounds__(64) void eval_ff_kernel(EvalArgs A)
                     const uint32_t np = rw[0];
                     if (np == 0) continue;                  // only a malformed row leaves a tour empty
                     if (np > (uint32_t)I.pick_slots) continue;   // an order routed apart (below)
-                    uint32_t v[MAX_PICK_SLOTS];
-#pragma unroll
-                    for (int i = 0; i < MAX_PICK_SLOTS; i++) v[i] = (uint32_t)i < np ? rw[1 + i] : 0xFFFFFFFFu;
-                    sort32(v);
-                    acc += pick_route_cost<ROUTE>(v, np, wsp, I, I.magic);
+                    acc += pick_route_cost<ROUTE>(rw + 1, np, wsp, I, I.magic);
                 }
             }
             __syncthreads();
