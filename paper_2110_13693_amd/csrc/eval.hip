@@ -14,17 +14,22 @@
 //      i-th order of the sequence starts, P being the prefix sum of the order
 //      sizes clamped to Q + 1 (an order larger than Q is a tour of its own
 //      whatever its exact size), plus a sentinel bit at the total;
-//   3. next-fit: a tour opened at unit x ends after the last order that
-//      starts within (x, x + Q]; so the next tour opens at
-//      E(x) = highest set bit of B in (x, x + Q] (a 32-bit window of B).
-//      Tours open on the orbit of 0 under E.  The orbit is found in
-//      parallel: the unit range is cut into segments, and for each segment
-//      every order start that can be the first tour opened in it (those
-//      within Q units of its start) is chased to the segment end; the true
-//      entries are then linked segment after segment and their openings
-//      marked, by sequence position, in a bitmap P (the position of the
-//      order starting at unit x is the count of set bits of B below x);
-//   4. tour ids: a thread's opening flags are P at its positions; a block
+//   3. next-fit: a tour opened at position i, unit x, ends after the last
+//      order that starts within (x, x + Q]: the next tour opens as many
+//      positions on as B has bits in that window (one, if it has none: an
+//      order larger than Q).  Every position's step is computed at once and kept
+//      as a byte.  Tours open on the orbit of position 0 under the steps, found
+//      in parallel: positions are cut into segments of 64, one wave register
+//      each (a position per lane), and pointer doubling by lane permutes
+//      carries every position to where its chain leaves the segment.  The
+//      waves compose their segments' maps and exchange them, so that every
+//      wave knows where the true chain enters each of its segments; one lane
+//      per segment then walks its 64 positions and notes the openings as a mask.
+//      (Chains of LDS reads bound this part: about 8 thousand cycles a plan
+//      of 4,000 orders, 16 with candidate chains through the bitmap and their
+//      links.  4,096 such plans 79 to 74 us, 128 uneven instances x 256 plans
+//      284 to 242 us together with the three next notes.)
+//   4. tour ids: a thread takes its positions' flags from the masks; a block
 //      scan over their counts numbers the tours, and every order's entry in
 //      the tour table receives the byte offset of its tour's LDS row;
 //   5. every order line (instance order, coalesced) sets its aisle bit in
@@ -128,60 +133,66 @@ static __device__ __forceinline__ uint32_t bits_at(const uint32_t *B, uint32_t x
     return __builtin_amdgcn_alignbit(B[w + 1], B[w], x & 31u);
 }
 
-// Leading zeros of a word by v_ffbh_u32, which gives all ones for 0.
-static __device__ __forceinline__ uint32_t ffbh_raw(uint32_t x)
-{
-    uint32_t r;
-    asm("v_ffbh_u32 %0, %1" : "=v"(r) : "v"(x));
-    return r;
-}
+// Loops over a thread's SEQ_CHUNK register positions (or a wave's segments) in
+// fours, of which only the first `ch` are in use: the workgroups of small
+// instances skip the rest.
+#define WO_FOURS(k, ch) \
+    _Pragma("unroll") for (int k##4 = 0; k##4 < SEQ_CHUNK; k##4 += 4) \
+        if (!VAR_CH || k##4 < (ch)) \
+            _Pragma("unroll") for (int k = k##4; k < k##4 + 4; k++)
 
-// One chase step in terms of y = x + 1, for a tour opened at unit x: the
-// next opening E(x) is x + 1 + the highest set bit of the window (x, x + Q]
-// of the bitmap at LDS address B, and the result is E(x) + 1.  With no order
-// larger than Q the window holds the next order start (or the sentinel); an
-// empty window would move y by 33, never back.
-static __device__ __forceinline__ uint32_t next_open1(uint32_t B, uint32_t y, uint32_t maskQ)
-{
-    const uint32_t a = word_addr(B, y);
-    const uint32_t win = __builtin_amdgcn_alignbit(*lds32(a + 4u), *lds32(a), y) & maskQ;
-    return y + 32u - ffbh_raw(win);
-}
+// Independent LDS reads before this line are all issued before the first of
+// them is used after it.  (Short of registers, the compiler would else wait for
+// each few in turn: 90 cycles a read where the phases are chains already.)
+#define WO_ALL_ISSUED() __builtin_amdgcn_sched_barrier(0)
 
-// The order ids of sequence positions [0, nv) of `s`, two per 32-bit word.
-// A full, 16-byte aligned chunk is loaded as it is and the function returns
-// true: the caller clamps it to n - 1 (with min_u16x2) when it uses it, so
-// that a prefetch does not wait for its data.  Otherwise the ids are clamped
-// here and positions nv .. CH - 1 get the sink id n + 1 (size 0).
-template <int CH>
-static __device__ __forceinline__ bool load_chunk(const uint16_t *s, int nv, uint32_t n, uint4 *out)
+// The order ids of sequence positions [0, nv) of `s`, two per 32-bit word, of
+// a chunk of ch (4, 8 or 16; at most CH).  A full chunk is loaded as it is,
+// at whatever alignment the row has (rows of an odd order count are only 2-byte
+// aligned, which global loads take; 16 loads of an id each otherwise), and the function returns true: the caller clamps it to n - 1 (with
+// min_u16x2) when it uses it, so that a prefetch does not wait for its data.
+// Otherwise the ids are clamped here and positions nv .. ch - 1 get the sink
+// id n + 1 (size 0).
+template <int CH, bool VAR_CH>
+static __device__ __forceinline__ bool load_chunk(const uint16_t *s, int nv, int ch, uint32_t n, uint4 *out)
 {
-    if (nv == CH && (((uintptr_t)s) & 15u) == 0) {
-#pragma unroll
-        for (int j = 0; j < CH / 8; j++) out[j] = ((const uint4 *)s)[j];
+    constexpr int SEQ_CHUNK = CH;
+    if (nv == ch) {
+        if (!VAR_CH || ch == CH) __builtin_memcpy(out, s, 2 * CH);
+        else if (ch == 8) __builtin_memcpy(out, s, 16);
+        else __builtin_memcpy(out, s, 8);
         return true;
     }
     const uint32_t lim = n - 1u, sink = n + 1u;
     uint32_t w[CH / 2];
-#pragma unroll
-    for (int k = 0; k < CH; k += 2) {
-        const uint32_t lo = (k < nv) ? min((uint32_t)s[k], lim) : sink;
-        const uint32_t hi = (k + 1 < nv) ? min((uint32_t)s[k + 1], lim) : sink;
-        w[k >> 1] = lo | (hi << 16);
+    WO_FOURS(k, ch)
+    {
+        const uint32_t x = k < nv ? min((uint32_t)s[k], lim) : sink;
+        if (k % 2 == 0) w[k >> 1] = x; else w[k >> 1] |= x << 16;
     }
 #pragma unroll
     for (int j = 0; j < CH / 8; j++) out[j] = make_uint4(w[4 * j], w[4 * j + 1], w[4 * j + 2], w[4 * j + 3]);
     return false;
 }
 
+// Waves per SIMD, by registers: four, as the LDS of a paper-scale plan allows;
+// the 128-thread workgroups, with chunks of a size of their own, spill 37
+// registers at four and run in 61 us at three, 69 at four (their part of 128
+// uneven instances x 256 plans).
 template <int BLOCK, int ROUTE, bool SEQ_PASS>
-__global__ __launch_bounds__(BLOCK, ROUTE == WO_ROUTE_SSHAPE ? 4 : 2) void eval_plans_kernel(EvalArgs A)
+__global__ __launch_bounds__(BLOCK, ROUTE != WO_ROUTE_SSHAPE ? 2 : BLOCK == 128 ? 3 : 4) void eval_plans_kernel(EvalArgs A)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     uint32_t &s_next = *(uint32_t *)(smem + LDS_TICKET);
     constexpr int SEQ_CHUNK = BLOCK >= 256 ? 4096 / BLOCK : 16;   // sequence positions per thread in registers
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
+    // the workgroups of small instances use 4, 8 or 16 of them, the fewest that
+    // hold the orders (with 16 always, the 200-order call took 13.1 us, not 11.7)
+    constexpr bool VAR_CH = BLOCK < 256;
+    auto chunk_of = [](int orders) -> int {
+        if (VAR_CH && orders <= 4 * BLOCK) return 4;
+        if (VAR_CH && orders <= 8 * BLOCK) return 8;
+        return (orders + BLOCK * SEQ_CHUNK - 1) / (BLOCK * SEQ_CHUNK) * SEQ_CHUNK;
+    };
     int loaded = -1;                        // instance whose tables sit in LDS
 
     // work items: a grid stride, or a queue (atomic ticket) over a work order
@@ -192,7 +203,7 @@ __global__ __launch_bounds__(BLOCK, ROUTE == WO_ROUTE_SSHAPE ? 4 : 2) void eval_
     const int64_t K = A.chunk;
     int64_t item = (int64_t)blockIdx.x * K;
     if (A.queue) {
-        if (tid == 0) s_next = atomicAdd(A.queue_ctr, 1u);
+        if (threadIdx.x == 0) s_next = atomicAdd(A.queue_ctr, 1u);
         __syncthreads();
         item = (int64_t)s_next * K;
         __syncthreads();
@@ -204,6 +215,12 @@ __global__ __launch_bounds__(BLOCK, ROUTE == WO_ROUTE_SSHAPE ? 4 : 2) void eval_
     uint4 sv_pf[SEQ_CHUNK / 8];             // two 16-bit order ids per 32-bit word
     uint32_t zc_pf = 0xFFu;
     while (item < A.n_plans) {
+        // the thread's number, opaque in each round: addresses and conditions
+        // made from it are then computed where they are used, and not kept in
+        // some 40 registers from plan to plan
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        const int lane = tid & 63;
         const bool chunk_end = (item + 1) % K == 0;    // uniform
         if (A.queue && chunk_end && tid == 0) s_next = atomicAdd(A.queue_ctr, 1u);   // ticket of the next chunk
         const int64_t p = A.work ? (int64_t)A.work[item] : item;
@@ -216,25 +233,19 @@ __global__ __launch_bounds__(BLOCK, ROUTE == WO_ROUTE_SSHAPE ? 4 : 2) void eval_
         const uint32_t n_units = (uint32_t)I.n_units;
         const int64_t row = p - (A.n_inst > 1 ? A.plan_begin[ii] : 0);
         const uint16_t *seq = A.seq + A.seq_base[ii] + row * (int64_t)n;
-        const EvalLayout Ly = eval_layout(n, I.n_units, (uint32_t)I.row_b, I.t_cap, I.chase_log2, I.chase_lanes);
+        const EvalLayout Ly = eval_layout(n, I.n_units, (uint32_t)I.row_b, I.t_cap);
         uint32_t *zs = (uint32_t *)(smem + LDS_ZS);
-        uint32_t *scan_a = (uint32_t *)(smem + Ly.red);
+        uint32_t *scan_a = (uint32_t *)(smem + LDS_RED);
         uint32_t *scan_b = scan_a + 16;
-        int64_t *sum_slot = (int64_t *)(smem + Ly.red + 128);
-        int *misc = (int *)(smem + Ly.misc);
-        uint32_t *lane_base = (uint32_t *)(smem + Ly.seg);
-        uint32_t *wbits = lane_base + (MAX_SEG + 1);
-        uint32_t *true_lane = wbits + (MAX_SEG + 1);
-        uint32_t *segs = true_lane + (MAX_SEG + 1);
+        int64_t *sum_slot = (int64_t *)(smem + LDS_RED + 128);
+        uint32_t *big_flag = (uint32_t *)(smem + LDS_FLAG);   // an order larger than Q
         uint8_t *cnt = (uint8_t *)(smem + Ly.cnt);
         uint16_t *tour = (uint16_t *)(smem + Ly.tour);
         uint32_t *B = (uint32_t *)(smem + Ly.B);
         uint32_t *P = (uint32_t *)(smem + Ly.P);
         uint32_t *pref = (uint32_t *)(smem + Ly.pref);
-        uint16_t *crec = (uint16_t *)(smem + Ly.rec);
-        uint32_t *cnrec = (uint32_t *)(smem + Ly.nrec);
-        uint32_t *cnxt = (uint32_t *)(smem + Ly.nxt);
-        uint32_t *cand = (uint32_t *)(smem + Ly.cand);
+        uint8_t *step = smem + Ly.step;
+        uint8_t *wmap = smem + Ly.wmap;
         const int T = I.t_cap;
         const uint32_t RB = (uint32_t)I.row_b;
         const uint32_t dummy = (uint32_t)T * RB;          // byte offset of the dummy row
@@ -248,14 +259,6 @@ __global__ __launch_bounds__(BLOCK, ROUTE == WO_ROUTE_SSHAPE ? 4 : 2) void eval_
             // every tour entry starts at the dummy row, so that an entry a
             // malformed sequence leaves unwritten still points inside the tile
             for (int k = tid; k < n + 2; k += BLOCK) tour[k] = (uint16_t)dummy;
-            if (tid < 64) {
-                // segment starts, fixed by the instance's unit total (a plan
-                // whose total differs is not evaluated); 32-bit products since
-                // the total is below 2^22
-                const uint32_t G0 = (uint32_t)max(I.n_seg, 1), nu = n_units;
-                segs[lane] = (uint32_t)lane < G0 ? (uint32_t)lane * nu / G0 : nu;
-                if (lane == 0) segs[MAX_SEG] = nu;
-            }
             loaded = ii;
         }
         {
@@ -263,7 +266,7 @@ __global__ __launch_bounds__(BLOCK, ROUTE == WO_ROUTE_SSHAPE ? 4 : 2) void eval_
             const int nbf = (int)((Ly.total - Ly.B) / 16);
             for (int k = tid; k < nbf; k += BLOCK) bf[k] = make_uint4(0u, 0u, 0u, 0u);
         }
-        if (tid < 16) misc[tid] = 0;
+        if (SEQ_PASS && tid == 0) *big_flag = 0u;
 
         // The phases up to the tour numbering are chains of dependent steps
         // and barriers; the aisle pass is throughput work.  Waves in the
@@ -294,7 +297,8 @@ __global__ __launch_bounds__(BLOCK, ROUTE == WO_ROUTE_SSHAPE ? 4 : 2) void eval_
         }
 
         // ---- 2. unit bitmap of order starts --------------------------------
-        const int ch = (n + BLOCK - 1) / BLOCK;
+        // whole chunks per thread, so that a wave's positions are whole segments
+        const int ch = chunk_of(n);
         const int b0 = min(n, tid * ch), b1 = min(n, b0 + ch);
         const int nv = b1 - b0;
         const bool one_piece = ch <= SEQ_CHUNK;          // uniform
@@ -308,7 +312,7 @@ __global__ __launch_bounds__(BLOCK, ROUTE == WO_ROUTE_SSHAPE ? 4 : 2) void eval_
 #pragma unroll
                 for (int j = 0; j < SEQ_CHUNK / 8; j++) ld[j] = sv_pf[j];
             } else {
-                raw = load_chunk<SEQ_CHUNK>(seq + b0, nv, (uint32_t)n, ld);
+                raw = load_chunk<SEQ_CHUNK, VAR_CH>(seq + b0, nv, ch, (uint32_t)n, ld);
             }
 #pragma unroll
             for (int j = 0; j < SEQ_CHUNK / 8; j++) {
@@ -332,18 +336,20 @@ __global__ __launch_bounds__(BLOCK, ROUTE == WO_ROUTE_SSHAPE ? 4 : 2) void eval_
                                             : item + 1 + (int64_t)(gridDim.x - 1) * K;
         uint32_t local = 0, cmax = 0;
         if (one_piece) {
-#pragma unroll
-            for (int k = 0; k < SEQ_CHUNK; k++) {
-                const uint32_t c = cnt[SV(k)];
-                if (k % 4 == 0) csp[k / 4] = c; else csp[k / 4] |= c << (8 * (k % 4));
-                local += c;
-                cmax = max(cmax, c);
+            uint32_t c16[SEQ_CHUNK];
+            WO_FOURS(k, ch) c16[k] = cnt[SV(k)];
+            WO_ALL_ISSUED();
+            WO_FOURS(k, ch)
+            {
+                if (k % 4 == 0) csp[k / 4] = c16[k]; else csp[k / 4] |= c16[k] << (8 * (k % 4));
+                local += c16[k];
+                if (SEQ_PASS) cmax = max(cmax, c16[k]);
             }
         } else {
             for (int i = b0; i < b1; i++) {
                 const uint32_t c = cnt[min((uint32_t)seq[i], (uint32_t)(n - 1))];
                 local += c;
-                cmax = max(cmax, c);
+                if (SEQ_PASS) cmax = max(cmax, c);
             }
         }
         uint32_t total_units;
@@ -370,8 +376,8 @@ __global__ __launch_bounds__(BLOCK, ROUTE == WO_ROUTE_SSHAPE ? 4 : 2) void eval_
                 // positions past the chunk have size 0 and set the next
                 // chunk's first bit (or the sentinel) again
                 uint32_t run = run0;
-#pragma unroll
-                for (int k = 0; k < SEQ_CHUNK; k++) {
+                WO_FOURS(k, ch)
+                {
                     __hip_atomic_fetch_or(lds32(word_addr(Ly.B, run)), 1u << (run & 31u), __ATOMIC_RELAXED,
                                           __HIP_MEMORY_SCOPE_WORKGROUP);
                     run += CS(k);
@@ -384,162 +390,163 @@ __global__ __launch_bounds__(BLOCK, ROUTE == WO_ROUTE_SSHAPE ? 4 : 2) void eval_
                 }
             }
             if (tid == 0) atomicOr(&B[n_units >> 5], 1u << (n_units & 31u));   // sentinel
-            if (cmax > Q) misc[0] = 1;
+            if (SEQ_PASS && cmax > Q) *big_flag = 1u;
             __syncthreads();
 
-            // order starts per unit word, for the position of an opening unit
-            const uint32_t nbw = bitmap_words((int32_t)n_units);
-            const uint32_t wpt = (nbw + BLOCK - 1) / BLOCK;
-            const uint32_t w0 = min(nbw, (uint32_t)tid * wpt), w1 = min(nbw, w0 + wpt);
-            uint32_t pc = 0;
-            for (uint32_t w = w0; w < w1; w++) pc += __popc(B[w]);
-
-            // ---- 3. segments and their candidate entries (wave 0) --------
-            const bool any_big = misc[0] != 0;         // uniform: an order larger than Q
-            int G = (any_big || I.n_seg <= 1) ? 1 : I.n_seg;   // uniform
-            if (G > 1 && tid < 64) {
-                const int g = lane;
-                const uint32_t s_g = segs[g];
-                uint32_t wb = 0;
-                if (g == 0) {
-                    wb = 1u;                          // the tour opened at unit 0
-                } else if (g < G) {
-                    const uint32_t lim = n_units - s_g;   // candidates are order starts < n_units
-                    wb = bits_at(B, s_g) & maskQ;
-                    if (lim < 32u) wb &= (1u << lim) - 1u;
-                }
-                const uint32_t c = __popc(wb);
-                const uint32_t inc = wave_incl_scan(c);
-                const uint32_t base = inc - c;
-                const uint32_t lanes = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
-                lane_base[g] = base;
-                wbits[g] = wb;
-                if (lanes <= (uint32_t)I.chase_lanes) {
-                    uint32_t m = wb, idx = base;
-                    while (m) {
-                        cand[idx++] = ((uint32_t)g << 26) | (s_g + (uint32_t)__builtin_ctz(m));
-                        m &= m - 1u;
-                    }
-                }
-                if (g == 0) misc[1] = (int)lanes;
-            }
-            {
-                // the scan's barrier also publishes the segment tables
-                uint32_t n_starts;
+            const bool any_big = SEQ_PASS && *big_flag != 0u;   // uniform
+            if (SEQ_PASS) {
+                // order starts per unit word, for the line pass
+                const uint32_t nbw = bitmap_words((int32_t)n_units);
+                const uint32_t wpt = (nbw + BLOCK - 1) / BLOCK;
+                const uint32_t w0 = min(nbw, (uint32_t)tid * wpt), w1 = min(nbw, w0 + wpt);
+                uint32_t pc = 0, n_starts;
+                for (uint32_t w = w0; w < w1; w++) pc += __popc(B[w]);
                 uint32_t base = block_excl_scan<BLOCK>(pc, scan_a, &n_starts);
                 for (uint32_t w = w0; w < w1; w++) {
                     pref[w] = base;
                     base += __popc(B[w]);
                 }
             }
-            // position in the sequence of the order that starts at unit x
-            auto pos_of = [&](uint32_t x) -> uint32_t {
-                const uint32_t w = x >> 5;
-                return pref[w] + __popc(B[w] & ~(0xFFFFFFFFu << (x & 31u)));
-            };
-            if (G > 1 && misc[1] > I.chase_lanes) G = 1;  // uniform
 
-            // ---- 4. chase ---------------------------------------------------
-            const int CR2 = I.chase_log2;
-            if (G > 1) {
-                const int L_tot = misc[1];
-                for (int l = tid; l < L_tot; l += BLOCK) {
-                    const uint32_t cv = cand[l];
-                    const int g = (int)(cv >> 26);
-                    uint32_t x = cv & 0x3FFFFFFu;
-                    const uint32_t s_g = segs[g];
-                    const uint32_t s_e = segs[g + 1];
-                    // one loop exit; records past the last slot overwrite it
-                    // and send the plan to the serial chain
-                    const uint32_t rb = Ly.rec + ((uint32_t)l << (CR2 + 1));
-                    const uint32_t rl = rb + (2u << CR2) - 2u;
-                    const uint32_t s_g1 = s_g + 1u, s_e1 = s_e + 1u;
-                    uint32_t ra = rb, y = x + 1u;
-                    do {
-                        *lds16(min(ra, rl)) = (uint16_t)(y - s_g1);
-                        ra += 2u;
-                        y = next_open1(Ly.B, y, maskQ);
-                    } while (y < s_e1);
-                    x = y - 1u;
-                    cnrec[l] = (ra - rb) >> 1;            // more than 2^CR2: records lost
-                    // the lane of the next segment whose candidate is this exit
-                    uint32_t nx = 0xFFFFFFFFu;
-                    if (g + 1 < G) {
-                        const uint32_t off = x - s_e;
-                        const uint32_t wb = wbits[g + 1];
-                        if (off < 32u && ((wb >> off) & 1u))
-                            nx = lane_base[g + 1] + __popc(wb & ((1u << off) - 1u));
-                    }
-                    cnxt[l] = nx;
-                }
-                __syncthreads();
-                // ---- link the true entries, segment after segment --------
-                // (wave 0 holds every chase lane's exit in registers and
-                // follows the links with lane reads)
-                if (tid < 64 && !misc[2]) {
-                    const int L_tot = misc[1];
-                    uint32_t c[CHASE_LANES / 64];
+            // ---- 3. steps: a position's next opening, in positions ---------
+            if (one_piece) {
+                uint32_t run1 = run0 + 1u;
+                uint32_t sp[SEQ_CHUNK / 4];
+                constexpr int HB = VAR_CH ? 4 : 8;       // windows in flight
 #pragma unroll
-                    for (int j = 0; j < CHASE_LANES / 64; j++)
-                        c[j] = (lane + 64 * j < L_tot) ? cnxt[lane + 64 * j] : 0xFFFFFFFFu;
-                    uint32_t l = 0, tl = 0;
-                    bool ok = true;
-                    for (int g = 0; g < G; g++) {
-                        if (lane == g) tl = l;
-                        if (g + 1 < G) {
-                            const uint32_t j = l >> 6;
-                            uint32_t v = c[0];
+                for (int h = 0; h < SEQ_CHUNK; h += HB)
+                    if (!VAR_CH || h < ch) {
+                        uint32_t lo[HB], hi[HB], r = run1;
 #pragma unroll
-                            for (int jj = 1; jj < CHASE_LANES / 64; jj++) v = (j == (uint32_t)jj) ? c[jj] : v;
-                            l = (uint32_t)__builtin_amdgcn_readlane((int)v, (int)(l & 63u));
-                            if (l == 0xFFFFFFFFu) { ok = false; break; }
+                        for (int k = 0; k < HB; k++) {
+                            const uint32_t a = word_addr(Ly.B, r);
+                            lo[k] = *lds32(a);
+                            hi[k] = *lds32(a + 4u);
+                            r += CS(h + k);
+                        }
+                        WO_ALL_ISSUED();
+#pragma unroll
+                        for (int k = 0; k < HB; k++) {
+                            const uint32_t win = __builtin_amdgcn_alignbit(hi[k], lo[k], run1) & maskQ;
+                            const uint32_t c = max((uint32_t)__popc(win), 1u);
+                            if (k % 4 == 0) sp[(h + k) / 4] = c; else sp[(h + k) / 4] |= c << (8 * (k % 4));
+                            run1 += CS(h + k);
                         }
                     }
-                    if (lane < G) true_lane[lane] = tl;
-                    // only a true chain's lost records matter
-                    const bool lost = lane < G && cnrec[tl] > (1u << CR2);
-                    if ((!ok || __ballot(lost) != 0) && lane == 0) misc[2] = 1;
-                }
-                __syncthreads();
-                if (!misc[2]) {
-                    for (int idx = tid; idx < (G << CR2); idx += BLOCK) {
-                        const int g = idx >> CR2, k = idx & ((1 << CR2) - 1);
-                        const uint32_t l = true_lane[g];
-                        if ((uint32_t)k < cnrec[l]) {
-                            const uint32_t r = pos_of(segs[g] + crec[(l << CR2) + k]);
-                            atomicOr(&P[r >> 5], 1u << (r & 31u));
-                        }
-                    }
-                } else {
-                    G = 1;                               // fall back to the serial chain
+                if (nv > 0)
+                    WO_FOURS(k, ch) if (k % 4 == 0) ((uint32_t *)(step + b0))[k / 4] = sp[k / 4];
+            } else {
+                uint32_t run1 = run0 + 1u;
+                for (int i = b0; i < b1; i++) {
+                    step[i] = (uint8_t)max((uint32_t)__popc(bits_at(B, run1) & maskQ), 1u);
+                    run1 += cnt[min((uint32_t)seq[i], (uint32_t)(n - 1))];
                 }
             }
-            if (G == 1) {
-                // serial chain (also handles orders larger than the capacity)
-                __syncthreads();                         // the start counts
-                if (tid == 0) {
-                    uint32_t x = 0;
-                    while (x < n_units) {
-                        const uint32_t r = pos_of(x);
-                        P[r >> 5] |= 1u << (r & 31u);
-                        const uint32_t win = bits_at(B, x + 1) & maskQ;
-                        if (win) {
-                            x = x + 32u - ffbh(win);
-                        } else {                         // an order larger than Q: its own tour
-                            uint32_t y = x + 1;
-                            while (!((B[y >> 5] >> (y & 31u)) & 1u)) y++;
-                            x = y;
+            lds_order();                                 // a wave reads its own positions' steps only
+
+            // ---- 4. segments ------------------------------------------------
+            // Lane l of seg[j] holds 4 times the position, relative to the
+            // segment, that the chain of its l-th position first reaches
+            // outside: 256 (the next segment's first) to 380, as a step is at
+            // most 32.  A chain that reaches the end goes on at each segment's
+            // first position.
+            constexpr int SPW = SEQ_CHUNK;               // segments per wave held in registers
+            constexpr int IB = VAR_CH ? 4 : SPW;         // of these, so many lane permutes in flight
+            constexpr int NWV = BLOCK / 64;
+            const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+            const int wbase = wv * 64 * ch;              // the wave's first position
+            const int last_seg = (n - 1) & ~63;
+            const bool has_pos = wbase < n;
+            uint32_t seg[SPW];
+            auto load_segments = [&](int s0) {           // s0: position of the first
+                uint32_t x[IB];
+#pragma unroll
+                for (int h = 0; h < SPW; h += IB)
+                    if (!VAR_CH || h < ch) {
+#pragma unroll
+                        for (int j = 0; j < IB; j++) x[j] = step[min(s0 + 64 * (h + j), last_seg) + lane];
+                        WO_ALL_ISSUED();
+#pragma unroll
+                        for (int j = 0; j < IB; j++)
+                            seg[h + j] = lane < n - s0 - 64 * (h + j) ? ((uint32_t)lane + x[j]) << 2 : 256u;
+                    }
+                for (int r = 0; r < 6; r++) {            // 64 positions: at most 64 steps
+                    uint32_t lo = 256u;
+#pragma unroll
+                    for (int h = 0; h < SPW; h += IB)
+                        if (!VAR_CH || h < ch) {
+#pragma unroll
+                            for (int j = 0; j < IB; j++)
+                                x[j] = (uint32_t)__builtin_amdgcn_ds_bpermute((int)seg[h + j], (int)seg[h + j]);
+                            WO_ALL_ISSUED();
+#pragma unroll
+                            for (int j = 0; j < IB; j++) {
+                                seg[h + j] = seg[h + j] < 256u ? x[j] : seg[h + j];
+                                lo = min(lo, seg[h + j]);
+                            }
                         }
+                    if (__builtin_amdgcn_ballot_w64(lo < 256u) == 0) break;
+                }
+            };
+            if (has_pos) load_segments(wbase);
+            uint32_t e = 0;                              // 4 times the entry of the wave's first segment
+            if (NWV > 1) {
+                if (wbase + 64 * ch < n) {               // a later wave needs this one's map
+                    uint32_t all = 0;
+                    for (int s0 = wbase; s0 < wbase + 64 * ch; s0 += 64 * SPW) {
+                        if (s0 > wbase) load_segments(s0);
+                        uint32_t m[SPW];
+                        WO_FOURS(j, ch) m[j] = seg[j];
+#pragma unroll
+                        for (int d = 1; d < SPW; d <<= 1)
+                            if (!VAR_CH || d < ch)
+#pragma unroll
+                            for (int j = 0; j < SPW; j += 2 * d)
+                                m[j] = (uint32_t)__builtin_amdgcn_ds_bpermute((int)m[j], (int)m[j + d]);
+                        all = s0 == wbase ? m[0] : (uint32_t)__builtin_amdgcn_ds_bpermute((int)all, (int)m[0]);
+                    }
+                    wmap[wv * 64 + lane] = (uint8_t)all;     // 4 times the entry
+                }
+                __syncthreads();
+                if (has_pos) {
+                    uint32_t m[NWV];
+#pragma unroll
+                    for (int i = 0; i < NWV - 1; i++) m[i] = wmap[i * 64 + lane];
+#pragma unroll
+                    for (int i = 0; i < NWV - 1; i++)
+                        if (i < wv) e = (uint32_t)__builtin_amdgcn_readlane((int)m[i], (int)(e >> 2));
+                }
+            }
+            uint32_t opm = 0;                            // bit k: position b0 + k opens a tour
+            if (has_pos) {
+                for (int s0 = wbase; s0 < wbase + 64 * ch; s0 += 64 * SPW) {
+                    if (!one_piece) load_segments(s0);
+                    uint32_t ent = 0;                    // lane j: entry of segment j
+                    WO_FOURS(j, ch)
+                    {
+                        ent = set_lane(ent, e, j);
+                        e = (uint32_t)__builtin_amdgcn_readlane((int)seg[j], (int)(e >> 2)) & 255u;
+                    }
+                    const int sb = s0 + 64 * lane;       // lane j walks segment j
+                    const int lim = lane < min(ch, SPW) ? min(64, n - sb) : 0;
+                    uint64_t open = 0;
+                    for (int q = (int)(ent >> 2); q < lim; q += step[sb + q]) open |= 1ull << q;
+                    if (lim > 0) *(uint2 *)&P[sb >> 5] = make_uint2((uint32_t)open, (uint32_t)(open >> 32));
+                    if (one_piece) {
+                        // the mask of the segment that the thread's positions lie in
+                        const int c0 = VAR_CH ? ch : SEQ_CHUNK;
+                        const int from = (lane * c0 >> 6) << 2, sh = lane * c0 & 63;
+                        const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)(uint32_t)open);
+                        const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)(uint32_t)(open >> 32));
+                        opm = ((sh < 32 ? lo : hi) >> (sh & 31)) & ((1u << c0) - 1u);
                     }
                 }
             }
-            __syncthreads();
+            lds_order();
 
             // ---- tour ids; tour entries for the first tile -------------------
-            uint32_t opm = 0;                            // bit k: position b0 + k opens a tour
             uint32_t n_open = 0;
             if (one_piece) {
-                opm = bits_at(P, (uint32_t)b0) & ~(0xFFFFFFFFu << nv);   // nv <= 16
                 n_open = __popc(opm);
             } else {
                 for (int i = b0; i < b1; i += 32) {
@@ -548,14 +555,18 @@ __global__ __launch_bounds__(BLOCK, ROUTE == WO_ROUTE_SSHAPE ? 4 : 2) void eval_
                     n_open += __popc(m == 32 ? bits : bits & ~(0xFFFFFFFFu << m));
                 }
             }
-            // the rows of the tile are free once the flags are set
+            uint32_t n_tours;
+            const uint32_t first_tour = block_excl_scan<BLOCK>(n_open, scan_b, &n_tours);
+            // every wave has walked its segments: the tile's rows take the steps' place
             {
                 uint4 *rows = (uint4 *)(smem + LDS_REGION);
                 const int nr4 = (int)((RB * (uint32_t)(T + 1) + 15u) / 16u);
                 for (int k = tid; k < nr4; k += BLOCK) rows[k] = make_uint4(0u, 0u, 0u, 0u);
             }
-            uint32_t n_tours;
-            const uint32_t first_tour = block_excl_scan<BLOCK>(n_open, scan_b, &n_tours);
+            if (Ly.step == Ly.tour) {                    // uniform: the steps took the tour table's place
+                for (int k = tid; k < n + 2; k += BLOCK) tour[k] = (uint16_t)dummy;
+                __syncthreads();
+            }
             // entry of the order at a position: its tour's row, or the dummy
             // row for tours outside the tile [t0, t0 + T)
             // (later tiles re-derive the tour ids from the sequence in memory)
@@ -563,8 +574,8 @@ __global__ __launch_bounds__(BLOCK, ROUTE == WO_ROUTE_SSHAPE ? 4 : 2) void eval_
                 uint32_t t = first_tour - 1u;            // wraps; a store always follows an opening
                 if (from_regs) {                         // first tile (t0 = 0): the row offset
                     uint32_t tr = t * RB;                // t * RB, below dummy = T * RB iff t < T
-#pragma unroll
-                    for (int k = 0; k < SEQ_CHUNK; k++) {
+                    WO_FOURS(k, ch)
+                    {
                         tr += ((opm >> k) & 1u) * RB;
                         tour[SV(k)] = (uint16_t)min(tr, dummy);
                     }
@@ -609,12 +620,12 @@ __global__ __launch_bounds__(BLOCK, ROUTE == WO_ROUTE_SSHAPE ? 4 : 2) void eval_
                 const InstDev &In = A.inst[iin];
                 const int nn = same ? n : In.n_orders;
                 const int cn = same ? C : In.n_cat;
-                const int chn = (nn + BLOCK - 1) / BLOCK;
-                if (chn <= SEQ_CHUNK) {                  // uniform
+                if (nn <= BLOCK * SEQ_CHUNK) {           // uniform
                     const uint16_t *seqn = same ? A.seq + seq_base0 + pn * (int64_t)nn
                                                 : A.seq + A.seq_base[iin] + (pn - A.plan_begin[iin]) * (int64_t)nn;
+                    const int chn = chunk_of(nn);
                     const int c0 = min(nn, tid * chn), c1 = min(nn, c0 + chn);
-                    pf_raw = load_chunk<SEQ_CHUNK>(seqn + c0, c1 - c0, (uint32_t)nn, sv_pf);
+                    pf_raw = load_chunk<SEQ_CHUNK, VAR_CH>(seqn + c0, c1 - c0, chn, (uint32_t)nn, sv_pf);
                     zc_pf = (tid < 64 && lane < cn) ? (uint32_t)A.zone_of[pn * 64 + lane] : 0xFFu;
                     have_pf = true;
                 }

@@ -773,8 +773,7 @@ __global__ __launch_bounds__(64) void eval_ff_kernel(EvalArgs A)
                 // records, which name their order by its entry in the
                 // next-fit kernel's tour table (the padding records name
                 // order n)
-                const uint32_t nf_tour = eval_layout(n, I.n_units, (uint32_t)I.row_b, I.t_cap, I.chase_log2,
-                                                     I.chase_lanes).tour;
+                const uint32_t nf_tour = eval_layout(n, I.n_units, (uint32_t)I.row_b, I.t_cap).tour;
                 const uint2 *lines = A.lines + I.line_off;
                 for (int r = lane; r < I.n_lines_pad; r += 64) {
                     const uint2 rec = lines[r];

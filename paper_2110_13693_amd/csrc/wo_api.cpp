@@ -430,36 +430,6 @@ extern "C" wo_status wo_load_warehouse(const wo_instance_desc *descs, int32_t n_
             gbase.push_back(off);
         }
 
-        // Parallel next-fit: about (Q / mean order size) order starts fall in
-        // a Q-unit window, each a candidate entry of a segment.  With 2^lg
-        // opening records per chain, take the fewest segments whose chains
-        // fit the estimated tours with margin, plus one; fewer if the chase
-        // lanes or a minimum length of 2Q units do not allow them.  Longer
-        // records are tried only when 32 do not fit; without any fit, plans
-        // take the serial chain.
-        const double avg_len = (double)units / d.n_orders;
-        const double cand = std::max(1.0, std::min((double)d.capacity, d.capacity / avg_len));
-        I.n_seg = 1;
-        I.chase_log2 = 5;
-        for (int lg = 5; lg <= MAX_CHASE_LOG2; lg++) {
-            const int g_recs = (int)std::ceil((double)tours_est / (0.75 * (1 << lg)));
-            const int g_lanes = 1 + (int)((0.85 * CHASE_LANES - 1.0) / cand);
-            const int g_len = (int)((double)units / (2.0 * d.capacity));
-            const int g = std::min(std::min(g_recs + 1, g_lanes), std::min(g_len, MAX_SEG));
-            const bool short_segs = (double)I.n_units / std::max(g, 1) < 65535.0;   // 16-bit records
-            if (g >= 2 && g >= g_recs && short_segs) {
-                I.n_seg = g;
-                I.chase_log2 = lg;
-                break;
-            }
-        }
-        // room for the expected chase lanes with margin, in whole waves
-        {
-            const double lanes = 1.0 + (I.n_seg - 1) * cand;
-            int cl = ((int)std::ceil(1.3 * lanes + 16.0) + 63) / 64 * 64;
-            I.chase_lanes = std::min(CHASE_LANES, std::max(64, cl));
-        }
-
         // tours per LDS tile: the expected tour count with margin (more tours
         // take another pass over the lines), never more than the orders, and
         // few enough that a row's byte offset fits the 16-bit tour entries
@@ -472,10 +442,10 @@ extern "C" wo_status wo_load_warehouse(const wo_instance_desc *descs, int32_t n_
         // the region of the rows also holds the sort of the largest listed order
         const int64_t t_big = ((int64_t)4 * I.big_np2 + I.row_b - 1) / I.row_b;
         t_cap = std::max(t_cap, t_big);
-        EvalLayout ly = eval_layout(d.n_orders, I.n_units, (uint32_t)I.row_b, (int32_t)t_cap, I.chase_log2, I.chase_lanes);
+        EvalLayout ly = eval_layout(d.n_orders, I.n_units, (uint32_t)I.row_b, (int32_t)t_cap);
         while (ly.total > wh->lds_max && t_cap > 1) {
             t_cap = t_cap / 2;
-            ly = eval_layout(d.n_orders, I.n_units, (uint32_t)I.row_b, (int32_t)t_cap, I.chase_log2, I.chase_lanes);
+            ly = eval_layout(d.n_orders, I.n_units, (uint32_t)I.row_b, (int32_t)t_cap);
         }
         I.t_cap = (int32_t)t_cap;
         if (ly.total > wh->lds_max || t_cap < t_big)

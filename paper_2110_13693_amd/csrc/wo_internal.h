@@ -27,10 +27,7 @@ struct InstDev {
     int32_t spacing;
     int32_t L;              // slots_per_side * pitch
     int32_t t_cap;          // tours per LDS tile
-    int32_t n_seg;          // item-space segments chased in parallel (1 = serial chain)
     int32_t n_lines_pad;    // line records stored: n_lines rounded up to whole groups of LINE_PAD
-    int32_t chase_log2;     // log2 of the opening records per chase lane
-    int32_t chase_lanes;    // chase lanes the LDS layout holds (a multiple of 64, <= CHASE_LANES)
     int32_t min_size;       // smallest min(size, capacity + 1) over the orders: a room below it never fills
     int32_t route;          // WO_ROUTE_*
     int32_t pick_slots;     // routes other than S-shape: pick entries per tour row (<= MAX_PICK_SLOTS)
@@ -106,35 +103,35 @@ struct EvalArgs {
     const int32_t *plan_spacing;   // device [n_plans]: aisle spacing of each plan row (null: the instance's)
 };
 
-// Parallel next-fit: lanes that chase candidate tour chains (at most
-// CHASE_LANES; an instance holds room for chase_lanes of them); each records
-// up to 2^chase_log2 openings (at most 2^MAX_CHASE_LOG2).
-constexpr int CHASE_LANES = 256;
-constexpr int MAX_CHASE_LOG2 = 6;
-constexpr int MAX_SEG = 64;
 // line records come in groups of 64 lanes x LINE_SLOTS consecutive lines,
 // padded to whole groups, so that the line pass needs no bounds checks
 constexpr int LINE_SLOTS = 8;
 constexpr int LINE_PAD = 64 * LINE_SLOTS;
-// fixed LDS offsets: the zone-start table, the work-queue ticket, then the
-// region shared by the chase records and the per-tour rows (the kernel holds
+// fixed LDS offsets: the zone-start table, the work-queue ticket, the slots of
+// block scans and sums (two of 16 words, one of 8 64-bit words) and a flag, which
+// a slow wave may still read while others lay out the next plan's instance,
+// then the
+// region shared by the next-fit steps and the per-tour rows (the kernel holds
 // no static LDS, so these are the addresses the instructions see)
 constexpr uint32_t LDS_ZS = 0;
 constexpr uint32_t LDS_TICKET = 256;
-constexpr uint32_t LDS_REGION = 272;
+constexpr uint32_t LDS_RED = 272;
+constexpr uint32_t LDS_FLAG = LDS_RED + 2 * 16 * 4 + 8 * 8;
+constexpr uint32_t LDS_REGION = LDS_FLAG + 16;
 
 // LDS layout of one evaluation block for an instance; host and device use the
 // same function so that the launch size, the line records' tour offsets and
 // the kernel agree.  The zone starts (64 words) sit at offset 0 and the shared
-// region at offset 272, so that the line pass addresses both with immediate
+// region at LDS_REGION, so that the line pass addresses both with immediate
 // offsets.  The region holds, in turn: the permutation-check bitmap
-// (validation), the chase records, and the per-tour rows of one tile.  A row
+// (validation), the next-fit step of every position with the waves' maps, and
+// the per-tour rows of one tile.  A row
 // is 1 + words 32-bit words: the tour's farthest scaled location, then its
 // aisle set (and a pad word when that count is even); a tile has t_cap rows
 // plus one dummy row.
 struct EvalLayout {
-    uint32_t rec, nrec, nxt, cand;     // chase phase (inside the region)
-    uint32_t red, misc, seg, cnt, tour, pref, B, P;
+    uint32_t step, wmap;               // next-fit (inside the region)
+    uint32_t cnt, tour, pref, B, P;
     uint32_t total;
 };
 
@@ -171,25 +168,25 @@ __host__ __device__ inline uint32_t ff_lds_bytes(int route, int32_t row_b)
     return ff_rows_off() + (uint32_t)ff_tile(route) * (uint32_t)row_b;
 }
 
-__host__ __device__ inline EvalLayout eval_layout(int32_t n_orders, int32_t n_units, uint32_t rb,
-                                                  int32_t t_cap, int32_t chase_log2, int32_t chase_lanes)
+__host__ __device__ inline EvalLayout eval_layout(int32_t n_orders, int32_t n_units, uint32_t rb, int32_t t_cap)
 {
-    const uint32_t cl = (uint32_t)chase_lanes;
     EvalLayout L;
     const uint32_t n = (uint32_t)n_orders, nb = bitmap_words(n_units);
-    uint32_t c = LDS_REGION;
-    L.rec = c;   c = align16(c + (2u * cl << chase_log2));
-    L.nrec = c;  c = align16(c + 4u * cl);
-    L.nxt = c;   c = align16(c + 4u * cl);
-    L.cand = c;  c = align16(c + 4u * cl);
+    // next-fit: a byte per lane of up to 8 waves, and a step byte per position,
+    // in whole segments of 64.  Where many orders make few rows, the steps would
+    // enlarge the region: beyond 8,192 orders they then lie in the tour table,
+    // which is filled afterwards (and laid out again before that).
+    L.wmap = LDS_REGION;
+    L.step = LDS_REGION + 8u * 64u;
+    uint32_t c = L.step + ((n + 63u) & ~63u);
     const uint32_t rows = align16(LDS_REGION + rb * (uint32_t)(t_cap + 1));
     const uint32_t seen = align16(LDS_REGION + 4u * ((n + 31) / 32));
+    const bool steps_apart = n > 8192u && c > rows;
+    if (steps_apart) c = L.step;
     uint32_t b = c > rows ? c : rows;
     if (seen > b) b = seen;
-    L.red = b;   b = align16(b + 2 * 16 * 4 + 8 * 8);   // two scan slots, one int64 reduction slot
-    L.misc = b;  b = align16(b + 16 * 4);
-    L.seg = b;   b = align16(b + 4 * 4 * (MAX_SEG + 1));   // lane_base | wbits | true_lane | seg start
     L.cnt = b;   b += cnt_bytes(n_orders);
+    if (steps_apart) L.step = b;
     L.tour = b;  b = align16(b + 2 * (n + 2));            // + dummy entry n, sink entry n + 1
     L.pref = b;  b = align16(b + 4 * nb);               // order starts below each unit word
     L.B = b;     b = align16(b + 4 * nb);

@@ -289,3 +289,25 @@ def test_layout_change_on_another_stream_while_busy_is_refused():
             ref, _ = oracle.eval_plans(inst, Zs[i], Ss[i].reshape(off[i + 1] - off[i], -1))
             assert np.array_equal(got[off[i]:off[i + 1]], ref)
     wh.free()
+
+
+@pytest.mark.parametrize("block", [64, 128, 256, 512])
+@pytest.mark.parametrize("n", [63, 64, 65, 255, 256, 257, 513, 1024, 1025, 2049, 4096, 4097, 8192, 8193, 16500])
+def test_next_fit_segments(n, block):
+    # the order counts at which a thread's positions, a wave's segments and the
+    # place of the steps change; capacities from a tour per order to the most
+    # orders a tour may hold, with and without orders larger than the capacity
+    wo = _wo()
+    rng = np.random.default_rng(n + block)
+    for capacity, lam in ((1, 0.0), (32, 0.0), (7, 1.5), (32, 3.0)):
+        inst = _random_instance(rng, 10, 30, n, capacity, 12, lam=lam)
+        Z, S = synth.make_plans(inst, 5, seed=n + capacity)
+        S[0] = np.arange(n)
+        S[1] = np.argsort(np.diff(inst.order_offsets), kind="stable")
+        print("segments", n, block, capacity, lam, flush=True)
+        wh = wo.wo_load_warehouse([inst])
+        wo.wo_set_eval_config(wh, block, small_orders=0)
+        d, _ = gpu_eval(wh, Z, S)
+        wh.free()
+        d_ref, _ = oracle.eval_plans(inst, Z, S)
+        assert np.array_equal(d, d_ref)
