@@ -27,8 +27,9 @@
 //      per segment then walks its 64 positions and notes the openings as a mask.
 //      (Chains of LDS reads bound this part: about 8 thousand cycles a plan
 //      of 4,000 orders, 16 with candidate chains through the bitmap and their
-//      links.  4,096 such plans 79 to 74 us, 128 uneven instances x 256 plans
-//      284 to 242 us together with the three next notes.)
+//      links.  4,096 such plans 79 to 72 us, 128 uneven instances x 256 plans
+//      292 to 229 us, with chunks of fewer positions for small instances,
+//      unaligned sequence loads and the instance table read as constants.)
 //   4. tour ids: a thread takes its positions' flags from the masks; a block
 //      scan over their counts numbers the tours, and every order's entry in
 //      the tour table receives the byte offset of its tour's LDS row;
@@ -199,7 +200,7 @@ __global__ __launch_bounds__(BLOCK, ROUTE != WO_ROUTE_SSHAPE ? 2 : BLOCK == 128 
     // that puts the most expensive plans first; either hands out chunks of
     // A.chunk consecutive items (a work list keeps an instance's plans
     // together, so a chunk mostly stages its instance once)
-    const int64_t seq_base0 = A.seq_base[0];
+    const int64_t seq_base0 = as_const(A.seq_base)[0];
     const int64_t K = A.chunk;
     int64_t item = (int64_t)blockIdx.x * K;
     if (A.queue) {
@@ -223,16 +224,16 @@ __global__ __launch_bounds__(BLOCK, ROUTE != WO_ROUTE_SSHAPE ? 2 : BLOCK == 128 
         const int lane = tid & 63;
         const bool chunk_end = (item + 1) % K == 0;    // uniform
         if (A.queue && chunk_end && tid == 0) s_next = atomicAdd(A.queue_ctr, 1u);   // ticket of the next chunk
-        const int64_t p = A.work ? (int64_t)A.work[item] : item;
+        const int64_t p = A.work ? (int64_t)as_const(A.work)[item] : item;
         const int ii = instance_of(A, p);
-        const InstDev &I = A.inst[ii];
+        InstConst &I = as_const(A.inst)[ii];
         const int n = I.n_orders;
         const int C = I.n_cat;
         const uint32_t Q = (uint32_t)I.capacity;
         const uint32_t maskQ = Q >= 32u ? 0xFFFFFFFFu : ((1u << Q) - 1u);
         const uint32_t n_units = (uint32_t)I.n_units;
-        const int64_t row = p - (A.n_inst > 1 ? A.plan_begin[ii] : 0);
-        const uint16_t *seq = A.seq + A.seq_base[ii] + row * (int64_t)n;
+        const int64_t row = p - (A.n_inst > 1 ? as_const(A.plan_begin)[ii] : 0);
+        const uint16_t *seq = A.seq + as_const(A.seq_base)[ii] + row * (int64_t)n;
         const EvalLayout Ly = eval_layout(n, I.n_units, (uint32_t)I.row_b, I.t_cap);
         uint32_t *zs = (uint32_t *)(smem + LDS_ZS);
         uint32_t *scan_a = (uint32_t *)(smem + LDS_RED);
@@ -612,17 +613,17 @@ __global__ __launch_bounds__(BLOCK, ROUTE != WO_ROUTE_SSHAPE ? 2 : BLOCK == 128 
 
             // ---- prefetch of the next plan's inputs -----------------------
             if (next_item < A.n_plans) {
-                const int64_t pn = A.work ? (int64_t)A.work[next_item] : next_item;
+                const int64_t pn = A.work ? (int64_t)as_const(A.work)[next_item] : next_item;
                 // one instance: the next plan's row follows from this plan's
                 // sizes with no table loads
                 const bool same = A.n_inst <= 1;
                 const int iin = same ? ii : instance_of(A, pn);
-                const InstDev &In = A.inst[iin];
+                InstConst &In = as_const(A.inst)[iin];
                 const int nn = same ? n : In.n_orders;
                 const int cn = same ? C : In.n_cat;
                 if (nn <= BLOCK * SEQ_CHUNK) {           // uniform
                     const uint16_t *seqn = same ? A.seq + seq_base0 + pn * (int64_t)nn
-                                                : A.seq + A.seq_base[iin] + (pn - A.plan_begin[iin]) * (int64_t)nn;
+                                                : A.seq + as_const(A.seq_base)[iin] + (pn - as_const(A.plan_begin)[iin]) * (int64_t)nn;
                     const int chn = chunk_of(nn);
                     const int c0 = min(nn, tid * chn), c1 = min(nn, c0 + chn);
                     pf_raw = load_chunk<SEQ_CHUNK, VAR_CH>(seqn + c0, c1 - c0, chn, (uint32_t)nn, sv_pf);
@@ -635,7 +636,7 @@ __global__ __launch_bounds__(BLOCK, ROUTE != WO_ROUTE_SSHAPE ? 2 : BLOCK == 128 
 
             // ---- 5./6. aisle sets and S-shape per tour tile ------------------
             const uint32_t magic = I.magic;
-            const int32_t wsp = A.plan_spacing ? A.plan_spacing[p] : I.spacing;   // aisle spacing of this plan
+            const int32_t wsp = A.plan_spacing ? as_const(A.plan_spacing)[p] : I.spacing;   // aisle spacing of this plan
             for (uint32_t t0 = 0; t0 < n_tours; t0 += (uint32_t)T) {
                 if (t0 > 0) {
                     __syncthreads();                     // the previous tile's rows are read

@@ -8,6 +8,17 @@
 
 namespace wo {
 
+// Tables that no kernel writes, as constant memory: at a uniform address their
+// values come by scalar loads into scalar registers.  (Through plain pointers
+// every field of a plan's instance is a vector load and a lane read, since a
+// store or a barrier might have changed it: a chain of some six trips to memory
+// before a plan of a batch could start.  128 uneven instances x 256 plans 242 to
+// 229 us, 4,096 paper-scale plans 74 to 72 us, in first fit 310 to 275 us.)
+#define WO_CONST const __attribute__((address_space(4)))
+typedef WO_CONST InstDev InstConst;
+template <class T>
+static __device__ __forceinline__ WO_CONST T *as_const(const T *p) { return (WO_CONST T *)(size_t)p; }
+
 // Inclusive prefix sum over the 64 lanes of a wave (all lanes active): shifts
 // by 1, 2, 4, 8 inside each row of 16 lanes, then the row totals carried by
 // the row broadcasts of lanes 15 and 31.
@@ -70,7 +81,7 @@ static __device__ __forceinline__ uint32_t mad24(uint32_t a, uint32_t b, uint32_
     return r;
 }
 
-static __device__ __forceinline__ float window_throughput(int64_t D, const InstDev &I)
+static __device__ __forceinline__ float window_throughput(int64_t D, InstConst &I)
 {
     // T = D / walk + t_item * items; orders * window / T: IEEE double, one
     // operation at a time (no multiply-add contraction), rounded once
@@ -87,11 +98,11 @@ static __device__ __forceinline__ float window_throughput(int64_t D, const InstD
 static __device__ __forceinline__ int instance_of(const EvalArgs &A, int64_t p)
 {
     if (A.n_inst <= 1) return 0;
-    if (A.plan_inst) return A.plan_inst[p];
+    if (A.plan_inst) return as_const(A.plan_inst)[p];
     int lo = 0, hi = A.n_inst - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
-        if (A.plan_begin[mid] <= p) lo = mid; else hi = mid - 1;
+        if (as_const(A.plan_begin)[mid] <= p) lo = mid; else hi = mid - 1;
     }
     return lo;
 }
@@ -186,9 +197,10 @@ static __device__ __forceinline__ void opt_aisle(OptClasses &s, uint32_t L, uint
 // walk, each further one is a step, and cost() closes it.
 template <int ROUTE>
 struct PickWalk {
-    const InstDev &I;
-    uint32_t magic;
-    int32_t spacing;
+    // the instance's values, held in vector registers: an instruction takes one
+    // scalar register at most, so that copies would be made at each step
+    uint32_t magic, d_s, sh, pitch_lo, pitch_hi, half;
+    int32_t L, spacing;
     uint32_t ca, a_lo;                // current aisle, first aisle
     // optimal: the five classes at the current aisle, its first and last
     // depth and its largest gap (0: one pick); all three doubled
@@ -207,21 +219,23 @@ struct PickWalk {
     // a * d_s does (d_s itself only takes a 25th in a single aisle, a = 0), but a
     // pitch may not: its index times it is two 24-bit products, each at the
     // full rate (a 32-bit one runs at a quarter of it).
-    template <int DOUBLED = 0>
+    static constexpr int DOUBLED = ROUTE == WO_ROUTE_OPTIMAL;
     __device__ __forceinline__ uint32_t depth(uint32_t ls, uint32_t a) const
     {
-        const uint32_t j = (ls - mul24(a, I.d_s)) >> (I.shift + 1), p = (uint32_t)I.pitch;
-        return mad24(j, (p & 0xFFFu) << DOUBLED, (p / 2u) << DOUBLED) + (mul24(j, p >> 12) << (12 + DOUBLED));
+        const uint32_t j = (ls - mul24(a, d_s)) >> sh;
+        return mad24(j, pitch_lo, half) + (mul24(j, pitch_hi) << (12 + DOUBLED));
     }
 
-    __device__ __forceinline__ PickWalk(const InstDev &inst, int32_t sp, uint32_t m, uint32_t first)
-        : I(inst), magic(m), spacing(sp)
+    __device__ __forceinline__ PickWalk(InstConst &inst, int32_t sp, uint32_t m, uint32_t first)
+        : magic(m), d_s(inst.d_s), sh(inst.shift + 1), pitch_lo(((uint32_t)inst.pitch & 0xFFFu) << DOUBLED),
+          pitch_hi((uint32_t)inst.pitch >> 12), half(((uint32_t)inst.pitch / 2u) << DOUBLED), L(inst.L), spacing(sp)
     {
+        asm("" : "+v"(magic), "+v"(d_s), "+v"(sh), "+v"(pitch_lo), "+v"(pitch_hi), "+v"(half), "+v"(L), "+v"(spacing));
         ca = mulhi24(first, magic);
         a_lo = ca;
-        const uint32_t y = depth<ROUTE == WO_ROUTE_OPTIMAL>(first, ca);
+        const uint32_t y = depth(first, ca);
         if (ROUTE == WO_ROUTE_OPTIMAL) {
-            s = opt_start(ca, 2u * (uint32_t)spacing, (uint32_t)I.L);
+            s = opt_start(ca, 2u * (uint32_t)spacing, (uint32_t)L);
             ylo = y;
             yhi = y;
             gap = 0;
@@ -242,10 +256,9 @@ struct PickWalk {
     // changes nothing.
     __device__ __forceinline__ void step(uint32_t ls)
     {
-        const int32_t L = I.L;
         uint32_t a = mulhi24(ls, magic);
         asm("" : "+v"(a));                // 32 bits: no 64-bit compare with ca
-        const uint32_t yu = depth<ROUTE == WO_ROUTE_OPTIMAL>(ls, a);
+        const uint32_t yu = depth(ls, a);
         if (ROUTE == WO_ROUTE_OPTIMAL) {
             // The lanes whose aisle ca is complete.  The mask is made opaque
             // for the selects below, which the compiler would else move into
@@ -297,7 +310,6 @@ struct PickWalk {
 
     __device__ __forceinline__ int64_t cost()
     {
-        const int32_t L = I.L;
         if (ROUTE == WO_ROUTE_OPTIMAL) {
             opt_aisle(s, (uint32_t)L, yhi, 2u * (uint32_t)L - ylo, 2u * (uint32_t)L - gap);
             // even ends, one component; and the way along the cross aisles
@@ -321,7 +333,7 @@ struct PickWalk {
 // each step a look at np.
 template <int ROUTE>
 static __device__ __forceinline__ int64_t pick_route_cost(const uint32_t *picks, uint32_t np, int32_t spacing,
-                                                          const InstDev &I, uint32_t magic)
+                                                          InstConst &I, uint32_t magic)
 {
     uint32_t v[MAX_PICK_SLOTS];
     v[0] = picks[0];
@@ -341,7 +353,7 @@ static __device__ __forceinline__ int64_t pick_route_cost(const uint32_t *picks,
 // starts), sort them (bitonic, padded with all ones), and thread 0 walks
 // them.  Returns the sum on thread 0 and 0 elsewhere; every thread must call.
 template <int ROUTE, int NT>
-static __device__ int64_t big_orders_cost(const EvalArgs &A, const InstDev &I, const uint32_t *zs, uint32_t *scr,
+static __device__ int64_t big_orders_cost(const EvalArgs &A, InstConst &I, const uint32_t *zs, uint32_t *scr,
                                           int32_t spacing)
 {
     const int tid = threadIdx.x;

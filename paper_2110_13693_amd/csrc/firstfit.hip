@@ -34,7 +34,7 @@ static __device__ __forceinline__ uint64_t lane64(uint32_t lo, uint32_t hi, int 
 // and fits four plans per CU.  With the counts as bytes in LDS, decremented by
 // atomics over the lists: 8.5 ms; with every list kept as a list: 6.6 ms; with
 // a store to memory per join: 5.1 ms.
-static __device__ int seed_tours_packed(const EvalArgs &A, const InstDev &I, const uint16_t *seq, const uint8_t *cnt,
+static __device__ int seed_tours_packed(const EvalArgs &A, InstConst &I, const uint16_t *seq, const uint8_t *cnt,
                                         const uint32_t *zs, uint16_t *tour_of, unsigned char *smem)
 {
     const int lane = threadIdx.x;
@@ -372,24 +372,24 @@ static __device__ int seed_tours_packed(const EvalArgs &A, const InstDev &I, con
 //      its tour's pick row, then one lane per tour sorts the picks and walks
 //      them as the next-fit kernel does;
 //   4. the wave's sum, saturated to int32, and the rate over the window.
-// Packed seed batching is a chain per plan on 16 plans per CU: four waves per
-// SIMD, for which the longer routes spill 4 registers (the optimal route 7.3 ms
-// at three waves, 4.7 at four).
+// Packed seed batching is a chain per plan on 16 plans per CU, which takes four
+// waves per SIMD (the optimal route 7.3 ms at three, 4.7 at four); the routes
+// with pick rows keep to the same.
 template <int ROUTE, int BATCH>
-__global__ __launch_bounds__(64, BATCH == FF_SEED_PACKED ? 4 : 1) void eval_ff_kernel(EvalArgs A)
+__global__ __launch_bounds__(64, ROUTE != WO_ROUTE_SSHAPE || BATCH == FF_SEED_PACKED ? 4 : 1) void eval_ff_kernel(EvalArgs A)
 {
     constexpr int TILE = ff_tile(ROUTE);
     extern __shared__ __align__(16) unsigned char smem[];
     const int lane = threadIdx.x;
     for (int64_t p = blockIdx.x; p < A.n_plans; p += gridDim.x) {
         const int ii = instance_of(A, p);
-        const InstDev &I = A.inst[ii];
+        InstConst &I = as_const(A.inst)[ii];
         const int n = I.n_orders;
         const int C = I.n_cat;
         const int32_t Q = I.capacity;
-        const int32_t wsp = A.plan_spacing ? A.plan_spacing[p] : I.spacing;   // aisle spacing of this plan
-        const int64_t row = p - (A.n_inst > 1 ? A.plan_begin[ii] : 0);
-        const uint16_t *seq = A.seq + A.seq_base[ii] + row * (int64_t)n;
+        const int32_t wsp = A.plan_spacing ? as_const(A.plan_spacing)[p] : I.spacing;   // aisle spacing of this plan
+        const int64_t row = p - (A.n_inst > 1 ? as_const(A.plan_begin)[ii] : 0);
+        const uint16_t *seq = A.seq + as_const(A.seq_base)[ii] + row * (int64_t)n;
         const uint8_t *cnt = A.cnt + I.cnt_off;
         uint32_t *zs = (uint32_t *)smem;
         uint16_t *tour_of = A.ff_tour + (int64_t)blockIdx.x * A.ff_stride;   // this workgroup's slice
@@ -780,7 +780,8 @@ __global__ __launch_bounds__(64, BATCH == FF_SEED_PACKED ? 4 : 1) void eval_ff_k
                 const uint2 *lines = A.lines + I.line_off;
                 // eight lines a lane at a time: their records, then their tours, are
                 // in flight together (4,096 paper-scale plans in first fit by
-                // the optimal route 759 to 585 us)
+                // the optimal route 759 to 585 us; 491 with scalar
+                // reads of the instance table)
                 constexpr int U = 8;
                 static_assert(LINE_PAD % (64 * U) == 0, "whole rounds");
                 for (int r0 = lane; r0 < I.n_lines_pad; r0 += 64 * U) {
