@@ -173,3 +173,20 @@ def test_batched_instances_with_long_orders(routing):
         d_ref, _ = oracle.eval_plans(inst, Zi, Si)
         assert np.array_equal(d.cpu().numpy()[12 * k:12 * (k + 1)], d_ref), k
     wh.free()
+
+
+@pytest.mark.parametrize("routing", ROUTES)
+@pytest.mark.parametrize("aisles,slots,pitch,spacing", [
+    (3, 3, 13_000_000, 20_000_000),        # spacing past 24 bits, pitch near it
+    (3, 3, 13_000_000, (1 << 23) - 1), (3, 3, 2, 1 << 23), (3, 3, 2, 1 << 24),
+    (3, 1, (1 << 26) - 2, 5),              # one slot: a pitch of 26 bits, index 0
+    (4, 60, 4094, 30), (4, 60, 4096, 30), (4, 60, 4098, 30),     # around the 12 low bits of the pitch
+])
+def test_products_past_24_bits(aisles, slots, pitch, spacing, routing):
+    for seed in range(4):
+        inst = synth.make_instance(n_aisles=aisles, slots_per_side=slots, pitch_dm=pitch, spacing_dm=spacing,
+                                   capacity=32, n_categories=2, n_skus=2 * aisles * slots, category_mode="dirichlet",
+                                   n_orders=5, lines_lambda=1.0, zipf_s=0.2, seed=seed)
+        Z, S = synth.make_plans(inst, 16, seed=seed)
+        print("products", aisles, slots, pitch, spacing, routing, flush=True)
+        _compare(_routed(inst, routing), Z, S)
