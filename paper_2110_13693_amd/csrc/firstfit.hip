@@ -338,7 +338,7 @@ static __device__ int seed_tours_packed(const EvalArgs &A, InstConst &I, const u
 // Plans under first-fit or seed order batching (the other greedy batching
 // rules of the order-picking literature beside next fit; section 5,
 // Subproblem 2 leaves the batching of orders into tours open), for each
-// route.  One wavefront evaluates one plan:
+// route.  One wavefront evaluates one plan (two under first fit by the S-shape route):
 //   1. zone starts: each category's start is the total size of the
 //      categories in lower zones (one pass over the categories per lane);
 //   2. first fit, 64 orders of the sequence at a time, one per lane, tour by
@@ -350,7 +350,7 @@ static __device__ int seed_tours_packed(const EvalArgs &A, InstConst &I, const u
 //      orders left.  A new tour takes all orders up to the first that does not
 //      fit by one running sum over the lanes; after that, as for an open tour,
 //      one ballot finds the next order that fits.  At the paper scale that is
-//      about 20 steps per 64 orders, and 4,096 plans take 0.275 ms, against
+//      about 20 steps per 64 orders, and 4,096 plans take 0.253 ms, against
 //      0.546 when each order looked for its tour in turn; over half of it is
 //      this chain of steps, 16 plans per CU in turn.  Lane j also keeps the j-th open tour in
 //      opening order and its room; full tours leave the lanes only when the
@@ -375,12 +375,24 @@ static __device__ int seed_tours_packed(const EvalArgs &A, InstConst &I, const u
 // Packed seed batching is a chain per plan on 16 plans per CU, which takes four
 // waves per SIMD (the optimal route 7.3 ms at three, 4.7 at four); the routes
 // with pick rows keep to the same.
+// First fit by the S-shape route has a second wave, which waits while the first
+// cuts the tours and then takes half of the tile passes: the chain leaves the
+// registers of eight waves per SIMD, and 16 plans per CU run as before.  4,096
+// paper-scale plans 275 to 253 us.  The other kernels have no registers for it.
+static __host__ __device__ constexpr int ff_threads(int route, int batch)
+{
+    return route == WO_ROUTE_SSHAPE && batch == FF_FIRST_FIT ? 128 : 64;
+}
+
 template <int ROUTE, int BATCH>
-__global__ __launch_bounds__(64, ROUTE != WO_ROUTE_SSHAPE || BATCH == FF_SEED_PACKED ? 4 : 1) void eval_ff_kernel(EvalArgs A)
+__global__ __launch_bounds__(ff_threads(ROUTE, BATCH), ff_threads(ROUTE, BATCH) == 128 ? 8
+                             : ROUTE != WO_ROUTE_SSHAPE || BATCH == FF_SEED_PACKED ? 4 : 1) void eval_ff_kernel(EvalArgs A)
 {
     constexpr int TILE = ff_tile(ROUTE);
     extern __shared__ __align__(16) unsigned char smem[];
-    const int lane = threadIdx.x;
+    constexpr int NT = ff_threads(ROUTE, BATCH), NW = NT / 64;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = NW > 1 ? __builtin_amdgcn_readfirstlane(tid >> 6) : 0;
     for (int64_t p = blockIdx.x; p < A.n_plans; p += gridDim.x) {
         const int ii = instance_of(A, p);
         InstConst &I = as_const(A.inst)[ii];
@@ -417,17 +429,17 @@ __global__ __launch_bounds__(64, ROUTE != WO_ROUTE_SSHAPE || BATCH == FF_SEED_PA
                 if (m != want) bad = 1;
             }
         }
-        for (int o = lane; o <= n; o += 64) tour_of[o] = 0xFFFFu;   // no tour yet; entry n: padding
+        for (int o = tid; o <= n; o += NT) tour_of[o] = 0xFFFFu;   // no tour yet; entry n: padding
         if (A.validate) {
             // every order exactly once: mark them in the tour table, which
             // is then reset
             __syncthreads();
-            for (int i = lane; i < n; i += 64) {
+            for (int i = tid; i < n; i += NT) {
                 const uint32_t o = seq[i];
                 if (o < (uint32_t)n) tour_of[o] = 0; else bad = 1;
             }
             __syncthreads();
-            for (int o = lane; o < n; o += 64) {
+            for (int o = tid; o < n; o += NT) {
                 bad |= tour_of[o] != 0;
                 tour_of[o] = 0xFFFFu;
             }
@@ -587,7 +599,7 @@ __global__ __launch_bounds__(64, ROUTE != WO_ROUTE_SSHAPE || BATCH == FF_SEED_PA
                 }
                 T++;
             }
-        } else {
+        } else if (wv == 0) {
             // ---- 2. first fit -------------------------------------------------
             const uint32_t mins = (uint32_t)__builtin_amdgcn_readfirstlane(I.min_size);   // a room below it never takes an order
             // Lanes [0, k) hold tours in opening order with their rooms, lanes
@@ -720,11 +732,17 @@ __global__ __launch_bounds__(64, ROUTE != WO_ROUTE_SSHAPE || BATCH == FF_SEED_PA
         }
 
         __builtin_amdgcn_s_setprio(0);
+        if constexpr (NW > 1) {
+            if (tid == 0) rows[0] = (uint32_t)T;
+            __syncthreads();                             // and the tour table
+            T = __builtin_amdgcn_readfirstlane((int)rows[0]);
+            __syncthreads();
+        }
 
         // ---- 3. tiles of tours -----------------------------------------------
         int64_t acc = 0;
         for (int t0 = 0; t0 < T; t0 += TILE) {
-            for (uint32_t k = lane; k < TILE * RW; k += 64) rows[k] = 0u;
+            for (uint32_t k = tid; k < TILE * RW; k += NT) rows[k] = 0u;
             __syncthreads();
             if (ROUTE == WO_ROUTE_SSHAPE) {
                 // aisle sets and farthest locations, one order per lane from
@@ -750,12 +768,12 @@ __global__ __launch_bounds__(64, ROUTE != WO_ROUTE_SSHAPE || BATCH == FF_SEED_PA
                         r.x[q] = grec[r.b0 + 64u * min((uint32_t)q, r.len - 1u) + (uint32_t)lane];
                     return r;
                 };
-                Group nx = load(0, order_of(0));
-                uint32_t o2 = order_of(1);
-                for (int g = 0; g < I.n_grp; g++) {
+                Group nx = load(wv, order_of(wv));
+                uint32_t o2 = order_of(wv + NW);
+                for (int g = wv; g < I.n_grp; g += NW) {
                     const Group c = nx;
-                    nx = load(g + 1, o2);
-                    o2 = order_of(g + 2);
+                    nx = load(g + NW, o2);
+                    o2 = order_of(g + 2 * NW);
                     const uint32_t t = (c.o < (uint32_t)n ? c.t : 0xFFFFu) - (uint32_t)t0;
                     if (t >= (uint32_t)TILE) continue;
                     uint32_t far = 0;
@@ -805,7 +823,7 @@ __global__ __launch_bounds__(64, ROUTE != WO_ROUTE_SSHAPE || BATCH == FF_SEED_PA
                 }
             }
             __syncthreads();
-            for (int tt = lane; tt < TILE && t0 + tt < T; tt += 64) {
+            for (int tt = tid; tt < TILE && t0 + tt < T; tt += NT) {
                 const uint32_t *rw = rows + (uint32_t)tt * RW;
                 if (ROUTE == WO_ROUTE_SSHAPE) {
                     const uint32_t ls = rw[0];
@@ -829,8 +847,14 @@ __global__ __launch_bounds__(64, ROUTE != WO_ROUTE_SSHAPE || BATCH == FF_SEED_PA
         // ---- 4. sum and rate -----------------------------------------------
 #pragma unroll
         for (int d = 32; d >= 1; d >>= 1) acc += __shfl_xor(acc, d, 64);
+        if constexpr (NW > 1) {
+            int64_t *part = (int64_t *)rows;             // the last tile's rows are read
+            if (tid == 64) *part = acc;
+            __syncthreads();
+            acc += *part;                                // thread 0's
+        }
         if (A.validate && bad) atomicOr(A.err, 1);
-        if (lane == 0) {
+        if (tid == 0) {
             A.dist[p] = acc > 2147483647ll ? 2147483647 : (int32_t)acc;
             if (A.thr) A.thr[p] = window_throughput(acc, I);
         }
@@ -851,7 +875,7 @@ static hipError_t launch_eval_ff_r(const EvalArgs &a, uint32_t lds_bytes, int gr
         }
         attr_bytes = lds_bytes;
     }
-    hipLaunchKernelGGL((eval_ff_kernel<ROUTE, BATCH>), dim3(grid), dim3(64), lds_bytes, s, a);
+    hipLaunchKernelGGL((eval_ff_kernel<ROUTE, BATCH>), dim3(grid), dim3(ff_threads(ROUTE, BATCH)), lds_bytes, s, a);
     return hipGetLastError();
 }
 
@@ -882,7 +906,7 @@ template <int ROUTE, int BATCH>
 static int ff_max_blocks_r(uint32_t lds_bytes)
 {
     int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, eval_ff_kernel<ROUTE, BATCH>, 64, lds_bytes) != hipSuccess) {
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, eval_ff_kernel<ROUTE, BATCH>, ff_threads(ROUTE, BATCH), lds_bytes) != hipSuccess) {
         (void)hipGetLastError();
         return 1;
     }
