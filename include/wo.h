@@ -384,7 +384,10 @@ wo_status wo_sur_set_scale(wo_sur *s, double mean, double std);
 wo_status wo_sur_get_scale(const wo_sur *s, double *mean, double *std);
 
 /* Copy the fp32 parameters to host memory (WO_SUR_PARAMS floats, layout
- * above).  Synchronises the device. */
+ * above).  Synchronises the device.  This call and wo_sur_save change nothing
+ * that other calls use: a call of another thread on the handle goes on
+ * undisturbed (read while a training runs, parameters may be of different
+ * steps). */
 wo_status wo_sur_get_params(const wo_sur *s, float *h_out);
 
 /* Forward and backward pass of one batch without an update: gradients of

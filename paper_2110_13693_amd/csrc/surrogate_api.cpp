@@ -8,6 +8,7 @@
 #include <cstdio>
 #include <cstring>
 #include <memory>
+#include <mutex>
 #include <new>
 #include <string>
 #include <vector>
@@ -55,6 +56,11 @@ struct wo_sur {
     int step = 0;                       // Adam steps taken
     int n_cat = 64;
     std::atomic<int> busy{0};
+    // Reading the parameters or saving them changes nothing that another call
+    // uses: they are laid out in a buffer of their own [P_TOTAL], by one reader
+    // at a time.
+    float *d_out = nullptr;
+    mutable std::mutex out_lock;
 };
 
 namespace {
@@ -265,7 +271,7 @@ static wo_status create(int32_t n_categories, const float *h_init, uint64_t seed
         (r = alloc(&s->d_H1T, (size_t)WORK_ROWS * N_H1)) || (r = alloc(&s->d_DU2, (size_t)WORK_ROWS * N_H2)) ||
         (r = alloc(&s->d_DU2T, (size_t)WORK_ROWS * N_H2)) || (r = alloc(&s->d_DU1T, (size_t)WORK_ROWS * N_H1)) ||
         (r = alloc(&s->d_mom, 2)) || (r = alloc(&s->d_loss, 1)) || (r = alloc(&s->d_red, W3_SLICES * N_H2 + 16)) ||
-        (r = alloc(&s->d_zt, (size_t)64 * MAX_GRAD_ROWS)))
+        (r = alloc(&s->d_zt, (size_t)64 * MAX_GRAD_ROWS)) || (r = alloc(&s->d_out, P_TOTAL)))
         return r;
     hipStream_t st = (hipStream_t)stream;
     WO_HIP(hipMemsetAsync(s->d_red, 0, sizeof(float) * (W3_SLICES * N_H2 + 16), st));
@@ -306,7 +312,7 @@ extern "C" wo_status wo_sur_free(wo_sur *s)
     void *bufs[] = {s->d_p,  s->d_g,   s->d_m,  s->d_v,   s->d_W1b, s->d_W2b,  s->d_W2kn, s->d_zb,   s->d_tb,
                     s->d_U1, s->d_U2,  s->d_H2, s->d_dy,  s->d_sq,  s->d_H1,   s->d_H1T,  s->d_DU2,  s->d_DU2T,
                     s->d_DU1T, s->d_pred, s->d_losses, s->d_mom, s->d_loss, s->d_red,
-                    s->d_zt};
+                    s->d_zt, s->d_out};
     for (void *b : bufs)
         if (b) (void)hipFree(b);
     delete s;
@@ -336,9 +342,9 @@ extern "C" wo_status wo_sur_get_params(const wo_sur *s, float *h_out)
 {
     if (!s || !h_out) return wo_fail(WO_E_INVAL, "NULL argument");
     WO_HIP(hipDeviceSynchronize());
-    // in the host layout by way of the gradient buffer, free between calls
-    WO_HIP(launch_relayout(s->d_p, s->d_g, LAYOUT_HOST, false, nullptr));
-    WO_HIP(hipMemcpy(h_out, s->d_g, sizeof(float) * P_TOTAL, hipMemcpyDeviceToHost));
+    std::lock_guard<std::mutex> reader(s->out_lock);
+    WO_HIP(launch_relayout(s->d_p, s->d_out, LAYOUT_HOST, false, nullptr));
+    WO_HIP(hipMemcpy(h_out, s->d_out, sizeof(float) * P_TOTAL, hipMemcpyDeviceToHost));
     return WO_OK;
 }
 
@@ -487,9 +493,12 @@ extern "C" wo_status wo_sur_save(const wo_sur *s, const char *path)
     WO_HIP(hipDeviceSynchronize());
     const float *from[3] = {s->d_p, s->d_m, s->d_v};
     float *to[3] = {p.data(), m.data(), v.data()};
-    for (int k = 0; k < 3; k++) {
-        WO_HIP(launch_relayout(from[k], s->d_g, LAYOUT_FILE, false, nullptr));
-        WO_HIP(hipMemcpy(to[k], s->d_g, sizeof(float) * P_TOTAL, hipMemcpyDeviceToHost));
+    {
+        std::lock_guard<std::mutex> reader(s->out_lock);
+        for (int k = 0; k < 3; k++) {
+            WO_HIP(launch_relayout(from[k], s->d_out, LAYOUT_FILE, false, nullptr));
+            WO_HIP(hipMemcpy(to[k], s->d_out, sizeof(float) * P_TOTAL, hipMemcpyDeviceToHost));
+        }
     }
     FILE *f = fopen(path, "wb");
     if (!f) return wo_fail(WO_E_INVAL, "cannot open %s for writing", path);

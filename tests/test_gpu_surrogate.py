@@ -506,3 +506,78 @@ def test_screen_with_ties(n, keep, distinct):
     assert np.array_equal(idx.cpu().numpy(), np.lexsort((np.arange(n), v))[:keep])
     s.free()
     wh.free()
+
+
+def _in_thread(fn):
+    """Run fn in a thread; join() re-raises what it raised."""
+    import threading
+
+    class T(threading.Thread):
+        error = None
+
+        def run(self):
+            try:
+                fn()
+            except BaseException as e:   # noqa: B036 (re-raised by the joining thread)
+                self.error = e
+
+        def join(self, timeout=None):
+            super().join(timeout)
+            if self.error is not None:
+                raise self.error
+    t = T()
+    t.start()
+    return t
+
+
+def test_reading_parameters_leaves_a_training_alone(tmp_path):
+    # one thread trains while another reads and saves the parameters: the
+    # training ends with the weights of an undisturbed one
+    import torch
+    wo = _wo()
+    n, batch, epochs = 32768, 4096, 12
+    z = torch.from_numpy(_zones(n, 21)).cuda()
+    d = torch.from_numpy(np.random.default_rng(22).integers(2000000, 3000000, n).astype(np.int32)).cuda()
+
+    def train(s, stream):
+        wo.wo_sur_train(s, z, d, epochs=epochs, batch=batch, seed=4, stream=stream)
+
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    alone = wo.wo_sur_create(64, flat(_params(8)))
+    train(alone, stream)
+    want = wo.wo_sur_get_params(alone)
+    alone.free()
+    s = wo.wo_sur_create(64, flat(_params(8)))
+    t = _in_thread(lambda: train(s, stream))
+    reads = 0
+    while t.is_alive() or reads == 0:
+        wo.wo_sur_get_params(s)
+        wo.wo_sur_save(s, str(tmp_path / "mid.wosur"))
+        reads += 1
+    t.join()
+    assert np.array_equal(wo.wo_sur_get_params(s), want)
+    s.free()
+
+
+def test_parameters_are_read_and_saved_at_the_same_time(tmp_path):
+    # two readers of an idle surrogate, one in the host's layout and one in the
+    # files': each gets what it gets alone
+    wo = _wo()
+    s = wo.wo_sur_create(64, flat(_params(8)))
+    want = flat(_params(8))
+    wo.wo_sur_save(s, str(tmp_path / "alone.wosur"))
+    ref = (tmp_path / "alone.wosur").read_bytes()
+
+    def save():
+        for _ in range(20):
+            wo.wo_sur_save(s, str(tmp_path / "both.wosur"))
+            assert (tmp_path / "both.wosur").read_bytes() == ref
+
+    t = _in_thread(save)
+    reads = 0
+    while t.is_alive() or reads == 0:
+        assert np.array_equal(wo.wo_sur_get_params(s), want)
+        reads += 1
+    t.join()
+    s.free()
