@@ -224,6 +224,22 @@ struct SurBusy {
     }
 };
 
+// The handle's device as the current one for the time of a call that takes no
+// stream of the caller's: its kernels go to the null stream of the current
+// device, whichever that is.
+struct OnDevice {
+    int back = -1;
+    explicit OnDevice(int device)
+    {
+        int now = device;
+        if (hipGetDevice(&now) == hipSuccess && now != device && hipSetDevice(device) == hipSuccess) back = now;
+    }
+    ~OnDevice()
+    {
+        if (back >= 0) (void)hipSetDevice(back);
+    }
+};
+
 // He-uniform initial weights from a counter generator: weight e of layer L
 // gets splitmix64(seed, L, e) mapped to U(-sqrt(6/fan_in), sqrt(6/fan_in)).
 void default_init(uint64_t seed, std::vector<float> &h)
@@ -341,6 +357,7 @@ extern "C" wo_status wo_sur_get_scale(const wo_sur *s, double *mean, double *std
 extern "C" wo_status wo_sur_get_params(const wo_sur *s, float *h_out)
 {
     if (!s || !h_out) return wo_fail(WO_E_INVAL, "NULL argument");
+    OnDevice on(s->device);
     WO_HIP(hipDeviceSynchronize());
     std::lock_guard<std::mutex> reader(s->out_lock);
     WO_HIP(launch_relayout(s->d_p, s->d_out, LAYOUT_HOST, false, nullptr));
@@ -489,6 +506,7 @@ extern "C" wo_status wo_screen_plans(wo_wh *wh, int32_t inst, wo_sur *s, int64_t
 extern "C" wo_status wo_sur_save(const wo_sur *s, const char *path)
 {
     if (!s || !path) return wo_fail(WO_E_INVAL, "NULL argument");
+    OnDevice on(s->device);
     std::vector<float> p(P_TOTAL), m(P_TOTAL), v(P_TOTAL);
     WO_HIP(hipDeviceSynchronize());
     const float *from[3] = {s->d_p, s->d_m, s->d_v};
