@@ -581,3 +581,76 @@ def test_parameters_are_read_and_saved_at_the_same_time(tmp_path):
         reads += 1
     t.join()
     s.free()
+
+
+def _screen(p, z, keep, mean=0.0, std=1.0):
+    """Predictions of plans z by parameters p, and the kept indices."""
+    import torch
+    wo = _wo()
+    inst, _, _ = synth.workload("paper", n_plans=1)
+    wh = wo.wo_load_warehouse([inst])
+    s = wo.wo_sur_create(64, flat(p))
+    wo.wo_sur_set_scale(s, mean, std)
+    zt = torch.from_numpy(z).cuda()
+    pred = torch.empty(z.shape[0], dtype=torch.float32, device="cuda")
+    idx = torch.full((keep,), -1, dtype=torch.int32, device="cuda")
+
+    def call():
+        wo.wo_screen_plans(wh, 0, s, zt, keep, idx, pred=pred)
+    call()
+    torch.cuda.synchronize()
+    return pred.cpu().numpy(), idx.cpu().numpy(), call
+
+
+def _by_first_zone(values):
+    """Parameters whose prediction falls with values[zone of category 0]."""
+    p = {k: np.zeros(sh, np.float32) for k, sh in SHAPES}
+    p["W1"][:64, 0] = values
+    p["W2"][0, 0], p["W3"][0, 0] = 1.0, -1.0
+    return p
+
+
+@pytest.mark.parametrize("equal", [159, 160, 161, 400])
+def test_selection_of_crowded_keys(equal):
+    # as many equal predictions as one bucket of the selection's sort ranks by
+    # itself, and more; the kept ones end inside a run of equal ones
+    z = _zones(4096, 31)
+    zone = z[:, 0]
+    rows = np.concatenate([np.flatnonzero(zone % 4 == v)[:equal] for v in range(3)])
+    z = np.ascontiguousarray(z[np.random.default_rng(equal).permutation(rows)])
+    print("crowded", equal, flush=True)
+    v, got, _ = _screen(_by_first_zone(np.arange(64) % 4), z, equal + 3)
+    assert np.array_equal(got, np.lexsort((np.arange(len(v)), v))[:equal + 3])
+
+
+@pytest.mark.parametrize("n", [5000, 8192, 20000])
+def test_selection_with_an_outlier(n):
+    # one value far below the others stretches the range of the buckets, so that
+    # all the others share one
+    values = np.arange(64, dtype=np.float64)
+    values[63] = 1e6
+    v, got, _ = _screen(_by_first_zone(values), _zones(n, n), 2000)
+    assert np.array_equal(got, np.lexsort((np.arange(n), v))[:2000])
+
+
+def test_selection_time_does_not_depend_on_the_keys():
+    # 8,192 equal predictions against 8,192 spread ones, the same passes before
+    # the selection: the network takes about twice the rest of the call; ranking
+    # by comparisons within one bucket took over fifty times
+    import torch
+    z = _zones(8192, 41)
+    times = []
+    for p in (_params(5), _by_first_zone(np.zeros(64))):
+        _, _, call = _screen(p, z, 4096, 2.3e7, 2.0e5)
+        best = float("inf")
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(10):
+                call()
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b))
+        times.append(best)
+    print("selection of spread and equal keys, ms:", times, flush=True)
+    assert times[1] < 6 * times[0]
