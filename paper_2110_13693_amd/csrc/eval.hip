@@ -176,22 +176,50 @@ static __device__ __forceinline__ bool load_chunk(const uint16_t *s, int nv, int
     return false;
 }
 
+// The order ids of positions [i, i + 8) of the sequence, clamped to n - 1; those
+// from b1 on get the sink id n + 1.
+static __device__ __forceinline__ uint4 load_piece(const uint16_t *seq, int i, int b1, uint32_t n)
+{
+    uint32_t w[4];
+    if (i + 8 <= b1) {
+        __builtin_memcpy(w, seq + i, 16);
+        const uint32_t lim2 = (n - 1u) * 0x10001u;
+#pragma unroll
+        for (int k = 0; k < 4; k++) w[k] = min_u16x2(w[k], lim2);
+    } else {
+#pragma unroll
+        for (int k = 0; k < 8; k++) {
+            const uint32_t x = i + k < b1 ? min((uint32_t)seq[i + k], n - 1u) : n + 1u;
+            if (k % 2 == 0) w[k >> 1] = x; else w[k >> 1] |= x << 16;
+        }
+    }
+    return make_uint4(w[0], w[1], w[2], w[3]);
+}
+
+// Sequence positions that the workgroups of a kernel keep in registers.
+static constexpr int seq_cap(int block) { return block >= 256 ? 4096 : 16 * block; }
+
 // Waves per SIMD, by registers: four, as the LDS of a paper-scale plan allows;
 // the 128-thread workgroups, with chunks of a size of their own, spill 37
 // registers at four and run in 61 us at three, 69 at four (their part of 128
 // uneven instances x 256 plans).
-template <int BLOCK, int ROUTE, bool SEQ_PASS>
-__global__ __launch_bounds__(BLOCK, ROUTE != WO_ROUTE_SSHAPE ? 2 : BLOCK == 128 ? 3 : 4) void eval_plans_kernel(EvalArgs A)
+// LONG: instances of more than seq_cap(BLOCK) orders are among the launch's, an
+// instantiation of its own, so that the other carries none of its code (4,096
+// paper-scale plans 72.5 us with it, 71.5 without).
+template <int BLOCK, int ROUTE, bool SEQ_PASS, bool LONG>
+__global__ __launch_bounds__(BLOCK, ROUTE == WO_ROUTE_RETURN && BLOCK == 512 ? 4
+                                    : ROUTE != WO_ROUTE_SSHAPE ? 2 : BLOCK == 128 ? 3 : 4) void eval_plans_kernel(EvalArgs A)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     uint32_t &s_next = *(uint32_t *)(smem + LDS_TICKET);
-    constexpr int SEQ_CHUNK = BLOCK >= 256 ? 4096 / BLOCK : 16;   // sequence positions per thread in registers
+    constexpr int SEQ_CHUNK = seq_cap(BLOCK) / BLOCK;   // sequence positions per thread in registers
     // the workgroups of small instances use 4, 8 or 16 of them, the fewest that
     // hold the orders (with 16 always, the 200-order call took 13.1 us, not 11.7)
     constexpr bool VAR_CH = BLOCK < 256;
     auto chunk_of = [](int orders) -> int {
         if (VAR_CH && orders <= 4 * BLOCK) return 4;
         if (VAR_CH && orders <= 8 * BLOCK) return 8;
+        if (!LONG) return SEQ_CHUNK;
         return (orders + BLOCK * SEQ_CHUNK - 1) / (BLOCK * SEQ_CHUNK) * SEQ_CHUNK;
     };
     int loaded = -1;                        // instance whose tables sit in LDS
@@ -302,9 +330,9 @@ __global__ __launch_bounds__(BLOCK, ROUTE != WO_ROUTE_SSHAPE ? 2 : BLOCK == 128 
         const int ch = chunk_of(n);
         const int b0 = min(n, tid * ch), b1 = min(n, b0 + ch);
         const int nv = b1 - b0;
-        const bool one_piece = ch <= SEQ_CHUNK;          // uniform
+        const bool one_piece = !LONG || ch <= SEQ_CHUNK;   // uniform
         uint32_t svp[SEQ_CHUNK / 2];                    // the chunk's order ids, two per register
-        uint32_t csp[SEQ_CHUNK / 4];                    // their clamped sizes (<= 33), four per register
+        uint32_t csp[SEQ_CHUNK / 4] = {};               // their clamped sizes (<= 33), four per register
         if (one_piece) {
             bool raw;
             uint4 ld[SEQ_CHUNK / 8];
@@ -335,6 +363,25 @@ __global__ __launch_bounds__(BLOCK, ROUTE != WO_ROUTE_SSHAPE ? 2 : BLOCK == 128 
         const int64_t next_item = !chunk_end ? item + 1
                                   : A.queue ? (int64_t)s_next * K
                                             : item + 1 + (int64_t)(gridDim.x - 1) * K;
+        if (A.validate) {
+            // permutation check: mark every order once (bitmap in the region)
+            uint32_t *seen = (uint32_t *)(smem + LDS_REGION);
+            for (int w = tid; w < (n + 31) / 32; w += BLOCK) seen[w] = 0;
+            __syncthreads();
+            for (int i = tid; i < n; i += BLOCK) {
+                const uint32_t o = seq[i];
+                if (o >= (uint32_t)n) { bad = 1; continue; }
+                const uint32_t old = atomicOr(&seen[o >> 5], 1u << (o & 31));
+                if (old & (1u << (o & 31))) bad = 1;
+            }
+            __syncthreads();                             // the sizes below may take the bitmap's place
+        }
+        // Longer sequences (a thread's positions do not fit its registers) go by
+        // pieces of 8 positions, the next piece's ids in flight: the first pass
+        // leaves the clamped sizes as bytes where the steps will lie, a thread's
+        // own positions, so that the next two passes read 8 of them at once and no
+        // order id again.  3,000 plans of 4,097 orders: 82 us, 137 by single
+        // positions, each pass reading its id and size again (8,193: 153, 329).
         uint32_t local = 0, cmax = 0;
         if (one_piece) {
             uint32_t c16[SEQ_CHUNK];
@@ -347,10 +394,21 @@ __global__ __launch_bounds__(BLOCK, ROUTE != WO_ROUTE_SSHAPE ? 2 : BLOCK == 128 
                 if (SEQ_PASS) cmax = max(cmax, c16[k]);
             }
         } else {
-            for (int i = b0; i < b1; i++) {
-                const uint32_t c = cnt[min((uint32_t)seq[i], (uint32_t)(n - 1))];
-                local += c;
-                if (SEQ_PASS) cmax = max(cmax, c);
+            uint4 nx = load_piece(seq, b0, b1, (uint32_t)n);
+            for (int i = b0; i < b1; i += 8) {
+                const uint4 o = nx;
+                if (i + 8 < b1) nx = load_piece(seq, i + 8, b1, (uint32_t)n);
+                const uint32_t w[4] = {o.x, o.y, o.z, o.w};
+                uint32_t c[8];
+#pragma unroll
+                for (int k = 0; k < 8; k++) c[k] = cnt[(w[k >> 1] >> (16 * (k & 1))) & 0xFFFFu];
+                WO_ALL_ISSUED();
+                if (SEQ_PASS)
+#pragma unroll
+                    for (int k = 0; k < 8; k++) cmax = max(cmax, c[k]);
+                const uint2 b = make_uint2(c[0] | c[1] << 8 | c[2] << 16 | c[3] << 24, c[4] | c[5] << 8 | c[6] << 16 | c[7] << 24);
+                local = __builtin_amdgcn_sad_u8(b.x, 0u, __builtin_amdgcn_sad_u8(b.y, 0u, local));
+                *(uint2 *)(step + i) = b;
             }
         }
         uint32_t total_units;
@@ -358,19 +416,7 @@ __global__ __launch_bounds__(BLOCK, ROUTE != WO_ROUTE_SSHAPE ? 2 : BLOCK == 128 
         // a malformed sequence can change the unit total; such a plan is not
         // evaluated (its result is unspecified) and no bitmap is written
         const bool units_ok = total_units == n_units;   // uniform
-        if (A.validate) {
-            // permutation check: mark every order once (bitmap in the region)
-            uint32_t *seen = (uint32_t *)(smem + LDS_REGION);
-            for (int w = tid; w < (n + 31) / 32; w += BLOCK) seen[w] = 0;
-            __syncthreads();
-            for (int i = tid; i < n; i += BLOCK) {
-                const uint32_t o = seq[i];
-                if (o >= (uint32_t)n) { bad = 1; continue; }
-                const uint32_t old = atomicOr(&seen[o >> 5], 1u << (o & 31));
-                if (old & (1u << (o & 31))) bad = 1;
-            }
-            if (!units_ok) bad = 1;
-        }
+        if (!units_ok) bad = 1;
         int64_t acc = 0;
         if (units_ok) {
             if (one_piece) {
@@ -385,9 +431,14 @@ __global__ __launch_bounds__(BLOCK, ROUTE != WO_ROUTE_SSHAPE ? 2 : BLOCK == 128 
                 }
             } else {
                 uint32_t run = run0;
-                for (int i = b0; i < b1; i++) {
-                    atomicOr(&B[run >> 5], 1u << (run & 31u));
-                    run += cnt[min((uint32_t)seq[i], (uint32_t)(n - 1))];
+                for (int i = b0; i < b1; i += 8) {
+                    const uint2 b = *(const uint2 *)(step + i);
+#pragma unroll
+                    for (int k = 0; k < 8; k++) {
+                        __hip_atomic_fetch_or(lds32(word_addr(Ly.B, run)), 1u << (run & 31u), __ATOMIC_RELAXED,
+                                              __HIP_MEMORY_SCOPE_WORKGROUP);
+                        run += (k < 4 ? b.x : b.y) >> (8 * (k & 3)) & 0xFFu;
+                    }
                 }
             }
             if (tid == 0) atomicOr(&B[n_units >> 5], 1u << (n_units & 31u));   // sentinel
@@ -438,9 +489,24 @@ __global__ __launch_bounds__(BLOCK, ROUTE != WO_ROUTE_SSHAPE ? 2 : BLOCK == 128 
                     WO_FOURS(k, ch) if (k % 4 == 0) ((uint32_t *)(step + b0))[k / 4] = sp[k / 4];
             } else {
                 uint32_t run1 = run0 + 1u;
-                for (int i = b0; i < b1; i++) {
-                    step[i] = (uint8_t)max((uint32_t)__popc(bits_at(B, run1) & maskQ), 1u);
-                    run1 += cnt[min((uint32_t)seq[i], (uint32_t)(n - 1))];
+                for (int i = b0; i < b1; i += 8) {
+                    const uint2 b = *(const uint2 *)(step + i);
+                    uint32_t lo[8], hi[8], at[8], sp[2];
+#pragma unroll
+                    for (int k = 0; k < 8; k++) {
+                        const uint32_t a = word_addr(Ly.B, run1);
+                        lo[k] = *lds32(a);
+                        hi[k] = *lds32(a + 4u);
+                        at[k] = run1;
+                        run1 += (k < 4 ? b.x : b.y) >> (8 * (k & 3)) & 0xFFu;
+                    }
+                    WO_ALL_ISSUED();
+#pragma unroll
+                    for (int k = 0; k < 8; k++) {
+                        const uint32_t c = max((uint32_t)__popc(__builtin_amdgcn_alignbit(hi[k], lo[k], at[k]) & maskQ), 1u);
+                        if (k % 4 == 0) sp[k / 4] = c; else sp[k / 4] |= c << (8 * (k % 4));
+                    }
+                    *(uint2 *)(step + i) = make_uint2(sp[0], sp[1]);
                 }
             }
             lds_order();                                 // a wave reads its own positions' steps only
@@ -495,7 +561,7 @@ __global__ __launch_bounds__(BLOCK, ROUTE != WO_ROUTE_SSHAPE ? 2 : BLOCK == 128 
                 if (wbase + 64 * ch < n) {               // a later wave needs this one's map
                     uint32_t all = 0;
                     for (int s0 = wbase; s0 < wbase + 64 * ch; s0 += 64 * SPW) {
-                        if (s0 > wbase) load_segments(s0);
+                        if (LONG && s0 > wbase) load_segments(s0);
                         uint32_t m[SPW];
                         WO_FOURS(j, ch) m[j] = seg[j];
 #pragma unroll
@@ -505,6 +571,7 @@ __global__ __launch_bounds__(BLOCK, ROUTE != WO_ROUTE_SSHAPE ? 2 : BLOCK == 128 
                             for (int j = 0; j < SPW; j += 2 * d)
                                 m[j] = (uint32_t)__builtin_amdgcn_ds_bpermute((int)m[j], (int)m[j + d]);
                         all = s0 == wbase ? m[0] : (uint32_t)__builtin_amdgcn_ds_bpermute((int)all, (int)m[0]);
+                        if (!LONG) break;
                     }
                     wmap[wv * 64 + lane] = (uint8_t)all;     // 4 times the entry
                 }
@@ -541,6 +608,7 @@ __global__ __launch_bounds__(BLOCK, ROUTE != WO_ROUTE_SSHAPE ? 2 : BLOCK == 128 
                         const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)(uint32_t)(open >> 32));
                         opm = ((sh < 32 ? lo : hi) >> (sh & 31)) & ((1u << c0) - 1u);
                     }
+                    if (!LONG) break;
                 }
             }
             lds_order();
@@ -564,7 +632,7 @@ __global__ __launch_bounds__(BLOCK, ROUTE != WO_ROUTE_SSHAPE ? 2 : BLOCK == 128 
                 const int nr4 = (int)((RB * (uint32_t)(T + 1) + 15u) / 16u);
                 for (int k = tid; k < nr4; k += BLOCK) rows[k] = make_uint4(0u, 0u, 0u, 0u);
             }
-            if (Ly.step == Ly.tour) {                    // uniform: the steps took the tour table's place
+            if (LONG && Ly.step == Ly.tour) {            // uniform: the steps took the tour table's place
                 for (int k = tid; k < n + 2; k += BLOCK) tour[k] = (uint16_t)dummy;
                 __syncthreads();
             }
@@ -580,12 +648,27 @@ __global__ __launch_bounds__(BLOCK, ROUTE != WO_ROUTE_SSHAPE ? 2 : BLOCK == 128 
                         tr += ((opm >> k) & 1u) * RB;
                         tour[SV(k)] = (uint16_t)min(tr, dummy);
                     }
-                } else {
+                } else if (!LONG) {
                     for (int i = b0; i < b1; i++) {
                         const uint32_t o = min((uint32_t)seq[i], (uint32_t)(n - 1));
                         t += (P[i >> 5] >> (i & 31)) & 1u;
                         const uint32_t rel = t - t0;
                         tour[o] = (uint16_t)(rel < (uint32_t)T ? rel * RB : dummy);
+                    }
+                } else {
+                    uint4 nx = load_piece(seq, b0, b1, (uint32_t)n);
+                    for (int i = b0; i < b1; i += 8) {
+                        const uint4 o = nx;
+                        if (i + 8 < b1) nx = load_piece(seq, i + 8, b1, (uint32_t)n);
+                        const uint32_t w[4] = {o.x, o.y, o.z, o.w};
+                        const uint32_t op = P[i >> 5] >> (i & 31);
+#pragma unroll
+                        for (int k = 0; k < 8; k++) {
+                            if (i + k < b1) t += (op >> k) & 1u;
+                            const uint32_t rel = t - t0;
+                            // past the chunk: the sink's entry
+                            tour[(w[k >> 1] >> (16 * (k & 1))) & 0xFFFFu] = (uint16_t)(rel < (uint32_t)T ? rel * RB : dummy);
+                        }
                     }
                 }
             };
@@ -621,7 +704,7 @@ __global__ __launch_bounds__(BLOCK, ROUTE != WO_ROUTE_SSHAPE ? 2 : BLOCK == 128 
                 InstConst &In = as_const(A.inst)[iin];
                 const int nn = same ? n : In.n_orders;
                 const int cn = same ? C : In.n_cat;
-                if (nn <= BLOCK * SEQ_CHUNK) {           // uniform
+                if (!LONG || nn <= BLOCK * SEQ_CHUNK) {  // uniform
                     const uint16_t *seqn = same ? A.seq + seq_base0 + pn * (int64_t)nn
                                                 : A.seq + as_const(A.seq_base)[iin] + (pn - as_const(A.plan_begin)[iin]) * (int64_t)nn;
                     const int chn = chunk_of(nn);
@@ -867,13 +950,13 @@ __global__ __launch_bounds__(BLOCK, ROUTE != WO_ROUTE_SSHAPE ? 2 : BLOCK == 128 
 // Reset of the work-queue ticket (a kernel, so that it can sit in a graph).
 __global__ void reset_ticket_kernel(uint32_t *ctr) { *ctr = 0u; }
 
-template <int BLOCK, int ROUTE, bool SEQ_PASS>
+template <int BLOCK, int ROUTE, bool SEQ_PASS, bool LONG>
 static hipError_t launch_eval_t(const EvalArgs &a, uint32_t lds_bytes, int grid, hipStream_t s)
 {
     // raise the dynamic LDS limit to what this launch needs
     static uint32_t attr_bytes = 0;
     if (lds_bytes > attr_bytes) {
-        hipError_t e = hipFuncSetAttribute((const void *)eval_plans_kernel<BLOCK, ROUTE, SEQ_PASS>,
+        hipError_t e = hipFuncSetAttribute((const void *)eval_plans_kernel<BLOCK, ROUTE, SEQ_PASS, LONG>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
         if (e != hipSuccess) {
             (void)hipGetLastError();
@@ -882,54 +965,69 @@ static hipError_t launch_eval_t(const EvalArgs &a, uint32_t lds_bytes, int grid,
         attr_bytes = lds_bytes;
     }
     if (a.queue) hipLaunchKernelGGL(reset_ticket_kernel, dim3(1), dim3(1), 0, s, a.queue_ctr);
-    hipLaunchKernelGGL((eval_plans_kernel<BLOCK, ROUTE, SEQ_PASS>), dim3(grid), dim3(BLOCK), lds_bytes, s, a);
+    hipLaunchKernelGGL((eval_plans_kernel<BLOCK, ROUTE, SEQ_PASS, LONG>), dim3(grid), dim3(BLOCK), lds_bytes, s, a);
     return hipGetLastError();
 }
 
-template <int BLOCK, int ROUTE, bool SEQ_PASS>
+template <int BLOCK, int ROUTE, bool SEQ_PASS, bool LONG>
 static int max_blocks_t(uint32_t lds_bytes)
 {
     int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, eval_plans_kernel<BLOCK, ROUTE, SEQ_PASS>, BLOCK, lds_bytes) !=
-        hipSuccess) {
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, eval_plans_kernel<BLOCK, ROUTE, SEQ_PASS, LONG>, BLOCK,
+                                                     lds_bytes) != hipSuccess) {
         (void)hipGetLastError();
         return 1;
     }
     return n > 0 ? n : 1;
 }
 
+template <int BLOCK, int ROUTE, bool SEQ_PASS>
+static int max_blocks_l(uint32_t lds_bytes, int max_orders)
+{
+    return max_orders > seq_cap(BLOCK) ? max_blocks_t<BLOCK, ROUTE, SEQ_PASS, true>(lds_bytes)
+                                       : max_blocks_t<BLOCK, ROUTE, SEQ_PASS, false>(lds_bytes);
+}
+
 template <int ROUTE, bool SEQ_PASS = false>
-static int max_blocks_r(int block, uint32_t lds_bytes)
+static int max_blocks_r(int block, uint32_t lds_bytes, int max_orders)
 {
     switch (block) {
-    case 64: return max_blocks_t<64, ROUTE, SEQ_PASS>(lds_bytes);
-    case 128: return max_blocks_t<128, ROUTE, SEQ_PASS>(lds_bytes);
-    case 256: return max_blocks_t<256, ROUTE, SEQ_PASS>(lds_bytes);
-    case 512: return max_blocks_t<512, ROUTE, SEQ_PASS>(lds_bytes);
+    case 64: return max_blocks_l<64, ROUTE, SEQ_PASS>(lds_bytes, max_orders);
+    case 128: return max_blocks_l<128, ROUTE, SEQ_PASS>(lds_bytes, max_orders);
+    case 256: return max_blocks_l<256, ROUTE, SEQ_PASS>(lds_bytes, max_orders);
+    case 512: return max_blocks_l<512, ROUTE, SEQ_PASS>(lds_bytes, max_orders);
     }
     return 1;
 }
 
-int eval_max_blocks_per_cu(int block, int route, uint32_t lds_bytes, int line_pass)
+int eval_max_blocks_per_cu(int block, int route, uint32_t lds_bytes, int max_orders, int line_pass)
 {
-    if (route == WO_ROUTE_SSHAPE && line_pass == 2) return max_blocks_r<WO_ROUTE_SSHAPE, true>(block, lds_bytes);
+    if (route == WO_ROUTE_SSHAPE && line_pass == 2)
+        return max_blocks_r<WO_ROUTE_SSHAPE, true>(block, lds_bytes, max_orders);
     switch (route) {
-    case WO_ROUTE_RETURN: return max_blocks_r<WO_ROUTE_RETURN>(block, lds_bytes);
-    case WO_ROUTE_LARGEST_GAP: return max_blocks_r<WO_ROUTE_LARGEST_GAP>(block, lds_bytes);
-    case WO_ROUTE_OPTIMAL: return max_blocks_r<WO_ROUTE_OPTIMAL>(block, lds_bytes);
-    case WO_ROUTE_COMBINED: return max_blocks_r<WO_ROUTE_COMBINED>(block, lds_bytes);
+    case WO_ROUTE_RETURN: return max_blocks_r<WO_ROUTE_RETURN>(block, lds_bytes, max_orders);
+    case WO_ROUTE_LARGEST_GAP: return max_blocks_r<WO_ROUTE_LARGEST_GAP>(block, lds_bytes, max_orders);
+    case WO_ROUTE_OPTIMAL: return max_blocks_r<WO_ROUTE_OPTIMAL>(block, lds_bytes, max_orders);
+    case WO_ROUTE_COMBINED: return max_blocks_r<WO_ROUTE_COMBINED>(block, lds_bytes, max_orders);
     }
-    return max_blocks_r<WO_ROUTE_SSHAPE>(block, lds_bytes);
+    return max_blocks_r<WO_ROUTE_SSHAPE>(block, lds_bytes, max_orders);
+}
+
+template <int BLOCK, int ROUTE, bool SEQ_PASS>
+static hipError_t launch_eval_l(const EvalArgs &a, uint32_t lds_bytes, int grid, hipStream_t s)
+{
+    return a.max_orders > seq_cap(BLOCK) ? launch_eval_t<BLOCK, ROUTE, SEQ_PASS, true>(a, lds_bytes, grid, s)
+                                         : launch_eval_t<BLOCK, ROUTE, SEQ_PASS, false>(a, lds_bytes, grid, s);
 }
 
 template <int ROUTE, bool SEQ_PASS = false>
 static hipError_t launch_eval_r(const EvalArgs &a, uint32_t lds_bytes, int grid, int block, hipStream_t s)
 {
     switch (block) {
-    case 64: return launch_eval_t<64, ROUTE, SEQ_PASS>(a, lds_bytes, grid, s);
-    case 128: return launch_eval_t<128, ROUTE, SEQ_PASS>(a, lds_bytes, grid, s);
-    case 256: return launch_eval_t<256, ROUTE, SEQ_PASS>(a, lds_bytes, grid, s);
-    case 512: return launch_eval_t<512, ROUTE, SEQ_PASS>(a, lds_bytes, grid, s);
+    case 64: return launch_eval_l<64, ROUTE, SEQ_PASS>(a, lds_bytes, grid, s);
+    case 128: return launch_eval_l<128, ROUTE, SEQ_PASS>(a, lds_bytes, grid, s);
+    case 256: return launch_eval_l<256, ROUTE, SEQ_PASS>(a, lds_bytes, grid, s);
+    case 512: return launch_eval_l<512, ROUTE, SEQ_PASS>(a, lds_bytes, grid, s);
     }
     return hipErrorInvalidValue;
 }

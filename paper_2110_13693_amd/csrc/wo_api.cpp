@@ -83,6 +83,7 @@ struct wo_wh {
     std::vector<InstDev> inst;          // host copies
     std::vector<uint32_t> lds;          // LDS bytes per instance
     uint32_t lds_max = 0;
+    int32_t max_orders = 0;             // of any instance
     int cu_count = 0;
     void *d_pool = nullptr;             // line records | order sizes
     const uint2 *d_lines = nullptr;
@@ -297,6 +298,7 @@ extern "C" wo_status wo_load_warehouse(const wo_instance_desc *descs, int32_t n_
     std::vector<uint32_t> big;              // pick rows: the orders routed apart
     for (int32_t i = 0; i < n_instances; i++) {
         const wo_instance_desc &d = descs[i];
+        wh->max_orders = std::max(wh->max_orders, d.n_orders);
         InstDev &I = wh->inst[i];
         memset(&I, 0, sizeof I);
         uint32_t per_aisle = 2u * (uint32_t)d.slots_per_side;
@@ -565,9 +567,7 @@ extern "C" wo_status wo_load_warehouse(const wo_instance_desc *descs, int32_t n_
     wh->lds_max = *std::max_element(wh->lds.begin(), wh->lds.end());
     wh->ff_lds_max = *std::max_element(wh->ff_lds.begin(), wh->ff_lds.end());
     if (wh->batching != WO_BATCH_NEXT_FIT) {
-        int32_t n_max = 0;
-        for (int32_t i = 0; i < n_instances; i++) n_max = std::max(n_max, descs[i].n_orders);
-        wh->ff_stride = ((int64_t)n_max + 1 + 63) & ~(int64_t)63;
+        wh->ff_stride = ((int64_t)wh->max_orders + 1 + 63) & ~(int64_t)63;
         wh->ff_slots = wh->cu_count *
                        eval_ff_max_blocks_per_cu(wh->route, wh->ff_batch,
                                                  *std::min_element(wh->ff_lds.begin(), wh->ff_lds.end()));
@@ -624,9 +624,9 @@ extern "C" wo_status wo_instance_info(const wo_wh *wh, int32_t i, int32_t *n_ord
 
 // Blocks to launch: `per_cu` workgroups per CU (or as many as the LDS allows,
 // at most 32 waves per CU), never more than there are plans.
-static int launch_grid(const wo_wh *wh, int block, int per_cu_cfg, uint32_t lds, int64_t n_plans)
+static int launch_grid(const wo_wh *wh, int block, int per_cu_cfg, uint32_t lds, int32_t max_orders, int64_t n_plans)
 {
-    const int fit = eval_max_blocks_per_cu(block, wh->route, lds, wh->main_mode);
+    const int fit = eval_max_blocks_per_cu(block, wh->route, lds, max_orders, wh->main_mode);
     const int per_cu = per_cu_cfg > 0 ? std::min(per_cu_cfg, fit) : fit;
     return (int)std::min<int64_t>(n_plans, (int64_t)wh->cu_count * per_cu);
 }
@@ -635,11 +635,6 @@ static int ff_grid(const wo_wh *wh, uint32_t lds, int64_t n_plans)
 {
     const int64_t fit = (int64_t)wh->cu_count * eval_ff_max_blocks_per_cu(wh->route, wh->ff_batch, lds);
     return (int)std::min<int64_t>(n_plans, std::min<int64_t>(fit, wh->ff_slots));   // one tour table slice each
-}
-
-static int launch_grid(const wo_wh *wh, uint32_t lds, int64_t n_plans)
-{
-    return launch_grid(wh, wh->block, wh->per_cu, lds, n_plans);
 }
 
 // Work lists by launch class, plans of the most expensive instances first
@@ -805,6 +800,7 @@ extern "C" wo_status wo_eval_plans(wo_wh *wh, const int64_t *plan_offsets, int64
     a.inst = wh->d_inst;
     a.n_inst = wh->n_inst;
     a.n_plans = n_plans;
+    a.max_orders = wh->max_orders;
     a.plan_begin = wh->d_map;
     a.seq_base = wh->d_map + wh->n_inst + 1;
     a.plan_inst = wh->n_inst > 1 ? wh->d_pinst : nullptr;
@@ -844,7 +840,8 @@ extern "C" wo_status wo_eval_plans(wo_wh *wh, const int64_t *plan_offsets, int64
                                wh->ff_batch, s));
     } else if (!any_small && !wh->queue) {
         // one launch, grid stride over the plan rows
-        HIP_TRY(launch_eval(a, wh->lds_max, launch_grid(wh, wh->lds_max, n_plans), wh->block, wh->route, s));
+        const int grid = launch_grid(wh, wh->block, wh->per_cu, wh->lds_max, a.max_orders, n_plans);
+        HIP_TRY(launch_eval(a, wh->lds_max, grid, wh->block, wh->route, s));
     } else {
         // one launch per class over its work list: the configured workgroups
         // for the large instances, 64- and 128-thread ones for the small ones
@@ -860,7 +857,8 @@ extern "C" wo_status wo_eval_plans(wo_wh *wh, const int64_t *plan_offsets, int64
             ac.queue_ctr = (uint32_t *)((char *)wh->d_err + 48 + 4 * c);
             const int block = c ? class_block[c] : wh->block;
             const int per_cu = c ? 0 : wh->per_cu;
-            const int grid = launch_grid(wh, block, per_cu, w.lds, w.n);
+            if (c) ac.max_orders = std::min(a.max_orders, c * wh->small_orders);   // as class_of has it
+            const int grid = launch_grid(wh, block, per_cu, w.lds, ac.max_orders, w.n);
             // the small instances' plans go out in chunks of consecutive
             // work items, so that a workgroup mostly keeps its instance's
             // tables (grid stride: 2 per step; queue: 4 per ticket), where
@@ -900,6 +898,7 @@ wo_status wo::eval_instance(wo_wh *wh, int32_t inst, int64_t n_plans, const uint
     a.inst = wh->d_inst + inst;
     a.n_inst = 1;
     a.n_plans = n_plans;
+    a.max_orders = wh->inst[inst].n_orders;
     const int64_t *zero_map = (const int64_t *)((const char *)wh->d_err + 16);   // zeroed at load
     a.plan_begin = zero_map;
     a.seq_base = zero_map;
@@ -937,7 +936,8 @@ wo_status wo::eval_instance(wo_wh *wh, int32_t inst, int64_t n_plans, const uint
         return WO_OK;
     }
     const uint32_t lds = wh->lds[inst];
-    HIP_TRY(launch_eval(a, lds, launch_grid(wh, lds, n_plans), wh->block, wh->route, s));
+    const int grid = launch_grid(wh, wh->block, wh->per_cu, lds, a.max_orders, n_plans);
+    HIP_TRY(launch_eval(a, lds, grid, wh->block, wh->route, s));
     return WO_OK;
 }
 
@@ -1269,7 +1269,8 @@ extern "C" wo_status wo_autotune_eval(wo_wh *wh, const int64_t *plan_offsets, in
             const int blk = blocks[bi], pc = per_cus[pi];
             for (int qm = 0; qm < 6 && !st; qm++) {
                 if (wh->route != WO_ROUTE_SSHAPE && (qm >> 1)) continue;   // pick rows: line per lane only
-                if (pc > eval_max_blocks_per_cu(blk, wh->route, wh->lds_max, qm >> 1)) continue;   // registers, LDS
+                if (pc > eval_max_blocks_per_cu(blk, wh->route, wh->lds_max, wh->max_orders, qm >> 1))
+                    continue;                                                // registers, LDS
                 st = time_cfg(wo_eval_config{blk, pc, qm & 1, qm >> 1, saved.small_orders, 0.f});
             }
         }

@@ -70,6 +70,7 @@ struct EvalArgs {
     const InstDev *inst;    // device table [n_inst]
     int32_t n_inst;
     int64_t n_plans;
+    int32_t max_orders;     // no instance of these plans has more orders
     const int64_t *plan_begin;  // device [n_inst + 1]: plan rows of instance i (unused if n_inst == 1)
     const int64_t *seq_base;    // device [n_inst]: element offset of instance i's first sequence row
     const int32_t *plan_inst;   // device [n_plans]: instance of each plan row (null: search plan_begin)
@@ -247,8 +248,9 @@ __host__ __device__ inline SeedPackedLayout seed_packed_layout(int32_t n_aisles)
 enum { FF_FIRST_FIT = 0, FF_SEED = 1, FF_SEED_PACKED = 2 };
 
 hipError_t launch_eval(const EvalArgs &a, uint32_t lds_bytes, int grid, int block, int route, hipStream_t s);
-// workgroups of the evaluation kernel that fit one CU (registers and LDS)
-int eval_max_blocks_per_cu(int block, int route, uint32_t lds_bytes, int line_pass = 0);
+// workgroups of the evaluation kernel that fit one CU (registers and LDS), for
+// instances of at most max_orders orders
+int eval_max_blocks_per_cu(int block, int route, uint32_t lds_bytes, int max_orders, int line_pass);
 // First-fit batching: one 64-thread workgroup per plan.
 hipError_t launch_eval_ff(const EvalArgs &a, uint32_t lds_bytes, int grid, int route, int batch, hipStream_t s);
 int eval_ff_max_blocks_per_cu(int route, int batch, uint32_t lds_bytes);

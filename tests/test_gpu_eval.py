@@ -311,3 +311,76 @@ def test_next_fit_segments(n, block):
         wh.free()
         d_ref, _ = oracle.eval_plans(inst, Z, S)
         assert np.array_equal(d, d_ref)
+
+
+@pytest.mark.parametrize("block", [64, 256])
+@pytest.mark.parametrize("n", [3, 200, 500, 1021, 4093, 4103, 8200])
+def test_tiles_of_few_tours(n, block, monkeypatch):
+    # three tours a tile: the later tiles read the sequence again by pieces of 8
+    # positions, from chunks of 4 (64 threads, 200 orders) to several pieces
+    wo = _wo()
+    monkeypatch.setenv("WO_TILE_TOURS", "3")
+    rng = np.random.default_rng(n + block)
+    inst = _random_instance(rng, 10, 30, n, 32, 12, lam=1.0)
+    Z, S = synth.make_plans(inst, 3, seed=n)
+    print("tiles", n, block, flush=True)
+    wh = wo.wo_load_warehouse([inst])
+    wo.wo_set_eval_config(wh, block, small_orders=0)
+    d, _ = gpu_eval(wh, Z, S)
+    wh.free()
+    assert np.array_equal(d, oracle.eval_plans(inst, Z, S)[0])
+
+
+@pytest.mark.parametrize("n", [4096, 4097, 8193])
+def test_validation_of_long_sequences(n, monkeypatch):
+    # the check's bitmap and the sizes of the positions share their place
+    wo = _wo()
+    rng = np.random.default_rng(n)
+    inst = _random_instance(rng, 10, 30, n, 30, 12, lam=0.5)
+    Z, S = synth.make_plans(inst, 4, seed=n)
+    wh = wo.wo_load_warehouse([inst])
+    monkeypatch.setenv("WO_VALIDATE", "1")
+    d, _ = gpu_eval(wh, Z, S)
+    assert np.array_equal(d, oracle.eval_plans(inst, Z, S)[0])
+    for i, j in ((0, n - 1), (n // 2, n // 2 + 1)):
+        bad = S.copy()
+        bad[2, i] = bad[2, j]
+        with pytest.raises(wo.WoError) as e:
+            gpu_eval(wh, Z, bad)
+        assert e.value.status == wo.WO_E_INVAL
+    wh.free()
+
+
+def _plans_ms(n, n_plans, block=256, small_orders=0):
+    """Best time of one call over random plans of an instance of n orders."""
+    import torch
+    wo = _wo()
+    rng = np.random.default_rng(n)
+    inst = _random_instance(rng, 100, 250, n, 30, 12, lam=1.5)
+    wh = wo.wo_load_warehouse([inst])
+    wo.wo_set_eval_config(wh, block, small_orders=small_orders)
+    z = torch.from_numpy(synth.generators.random_zone_perms(rng, n_plans, 12)).cuda()
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    s = torch.rand((n_plans, n), generator=gen, device="cuda").argsort(1).to(torch.int16).reshape(-1)
+    d = torch.empty(n_plans, dtype=torch.int32, device="cuda")
+    best = float("inf")
+    for _ in range(6):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(5):
+            wo.wo_eval_plans(wh, z, s, d)
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b) / 5)
+    wh.free()
+    return best
+
+
+def test_time_beyond_a_blocks_registers():
+    # plans of more orders than a workgroup keeps in registers, against one of
+    # just as many: 1.4 and 2.6 times its time by pieces of 8 positions, 2.3 and
+    # 5.4 by single positions (twice as many orders are at least twice the work)
+    t = {n: _plans_ms(n, 3000) for n in (4096, 4097, 8193)}
+    print("ms a call of 3,000 plans:", t, flush=True)
+    assert t[4097] < 1.8 * t[4096]
+    assert t[8193] < 4.0 * t[4096]
