@@ -384,3 +384,12 @@ def test_time_beyond_a_blocks_registers():
     print("ms a call of 3,000 plans:", t, flush=True)
     assert t[4097] < 1.8 * t[4096]
     assert t[8193] < 4.0 * t[4096]
+
+
+def test_time_of_small_instances_by_wide_workgroups():
+    # 256 threads for 1,000 orders, as a search on a small warehouse has them:
+    # the waves without a position do not pass over sequences (0.6 of the time of
+    # 4,000 orders; 1.15 when they did)
+    t = {n: _plans_ms(n, 16384) for n in (1000, 4000)}
+    print("ms a call of 16,384 plans:", t, flush=True)
+    assert t[1000] < 0.85 * t[4000]
