@@ -389,7 +389,14 @@ static __device__ int64_t big_orders_cost(const EvalArgs &A, InstConst &I, const
         __syncthreads();
         if (tid == 0) {
             PickWalk<ROUTE> w(I, spacing, I.magic, scr[0]);
-            for (uint32_t i = 1; i < m; i++) w.step(scr[i]);
+            // the next location in flight during a step (largest gap, orders of 500 and
+            // 900 lines: 282 to 262 us)
+            uint32_t next = scr[1];      // such an order has more than MAX_PICK_SLOTS
+            for (uint32_t i = 1; i < m; i++) {
+                const uint32_t now = next;
+                next = scr[min(i + 1u, m - 1u)];
+                w.step(now);
+            }
             acc += w.cost();
         }
     }
