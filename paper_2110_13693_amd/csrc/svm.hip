@@ -383,23 +383,27 @@ __global__ __launch_bounds__(UP_THREADS) void update_kernel(const double *X, con
 
 // Prediction: the class of the largest score (ties: the lower class), a score
 // being weights . features in feature order, then the bias, as in training.
-// 64 orders per workgroup: their rows, one contiguous block, go to LDS with
-// all loads in flight together; then each of the four waves scores its share
-// of the classes, KG at a time, with one lane per order (weights by scalar
-// loads, a row's features from LDS at an odd stride), and the first wave takes
-// the best in class order.  Four workgroups fit a CU, so that some load while
-// others multiply.  64 features, 8 classes: 8.3 us for 8,192 orders and 0.123
-// ms for 1M (4.4 TB/s of features), against 30 us and 0.194 ms when each wave
-// streamed 64 orders of its own in chunks of 8 features for all classes.
-template <int KG>
+// 64 R orders per workgroup: their rows, one contiguous block of at most 4,096
+// features, go to LDS with all loads in flight together; then 4 / R waves share
+// the classes of each 64 orders, KG at a time, with one lane per order (weights
+// by scalar loads, a row's features from LDS at an odd stride), and the first of
+// these waves takes the best of their bests.  Four workgroups fit a CU, so that
+// some load while others multiply.  64 features, 8 classes: 8.3 us for 8,192
+// orders and 0.123 ms for 1M (4.4 TB/s of features), against 30 us and 0.194 ms
+// when each wave streamed 64 orders of its own in chunks of 8 features for all
+// classes.
+template <int R, int KG>
 __global__ __launch_bounds__(256) void predict_kernel(const double *X, int64_t n, int32_t F, int32_t f_inv, int32_t K,
                                                      const double *Wt, int32_t *cls)
 {
-    extern __shared__ double lds[];                  // the rows, then the scores [K][64]
+    extern __shared__ double lds[];                  // the rows, then the waves' best scores [256] and classes [256]
+    constexpr int WPR = 4 / R;                       // waves that share a row's classes
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int sub = w % WPR;
+    const int32_t row = w / WPR * 64 + lane;         // this lane's order
     const int32_t ld = F | 1;
-    for (int64_t i0 = (int64_t)blockIdx.x * 64; i0 < n; i0 += (int64_t)gridDim.x * 64) {
-        const int32_t rows = (int32_t)std::min<int64_t>(64, n - i0), total = rows * F;
+    for (int64_t i0 = (int64_t)blockIdx.x * (64 * R); i0 < n; i0 += (int64_t)gridDim.x * (64 * R)) {
+        const int32_t rows = (int32_t)std::min<int64_t>(64 * R, n - i0), total = rows * F;
         const double *src = X + i0 * F;
         {
             double v[16];
@@ -414,12 +418,13 @@ __global__ __launch_bounds__(256) void predict_kernel(const double *X, int64_t n
             }
         }
         __syncthreads();
-        const double *mine = lds + std::min(lane, rows - 1) * ld;
-        double sc[16];                               // this wave's classes: w * KG + j, then 4 KG further
-#pragma unroll
-        for (int c = 0; c < 16 / KG; c++) {
-            const int32_t k0 = (c * 4 + w) * KG;
-            if (k0 >= K) break;
+        const double *mine = lds + std::min(row, rows - 1) * ld;
+        // the best of this wave's classes (sub * KG + j, then 4 / R KG further).
+        // The sequence that starts from class 0 and takes every larger score keeps
+        // class 0 where its score is NaN and never takes a NaN or -inf.
+        int32_t best = sub == 0 ? 0 : WO_SVM_MAX_CLASSES;
+        double bs = -INFINITY;
+        for (int32_t k0 = sub * KG; k0 < K; k0 += WPR * KG) {
             double s[KG];
             const double *wt[KG];
 #pragma unroll
@@ -443,30 +448,33 @@ __global__ __launch_bounds__(256) void predict_kernel(const double *X, int64_t n
                 for (int j = 0; j < KG; j++) s[j] = s[j] + wt[j][f] * v;
             }
 #pragma unroll
-            for (int j = 0; j < KG; j++) sc[c * KG + j] = s[j] + wt[j][F];
-        }
-        __syncthreads();                             // the rows are read
-#pragma unroll
-        for (int c = 0; c < 16 / KG; c++)
-#pragma unroll
             for (int j = 0; j < KG; j++) {
-                const int32_t k = (c * 4 + w) * KG + j;
-                if (k < K) lds[k * 64 + lane] = sc[c * KG + j];
-            }
-        __syncthreads();
-        if (w == 0 && lane < rows) {
-            int32_t best = 0;
-            double bs = lds[lane];
-            for (int32_t k = 1; k < K; k++) {
-                const double v = lds[k * 64 + lane];
-                if (v > bs) {
+                const double v = s[j] + wt[j][F];
+                if (k0 + j < K && (k0 + j == 0 || v > bs)) {
                     bs = v;
-                    best = k;
+                    best = k0 + j;
                 }
             }
-            cls[i0 + lane] = best;
         }
-        __syncthreads();                             // the scores are read
+        if (WPR > 1) {
+            int32_t *bk = (int32_t *)(lds + 256);
+            __syncthreads();                         // the rows are read
+            lds[sub * (64 * R) + row] = bs;
+            bk[sub * (64 * R) + row] = best;
+            __syncthreads();
+            if (sub == 0)
+#pragma unroll
+                for (int u = 1; u < WPR; u++) {
+                    const double v = lds[u * (64 * R) + row];
+                    const int32_t k = bk[u * (64 * R) + row];
+                    if (v > bs || (v == bs && k < best)) {
+                        bs = v;
+                        best = k;
+                    }
+                }
+        }
+        if (sub == 0 && row < rows) cls[i0 + row] = best;
+        __syncthreads();                             // the rows, or the bests, are read
     }
 }
 
@@ -590,10 +598,19 @@ extern "C" wo_status wo_svm_predict(wo_svm *m, int64_t n, const double *d_featur
     if (n < 0) return wo_fail(WO_E_INVAL, "n < 0");
     if (n == 0) return WO_OK;
     hipStream_t s = (hipStream_t)stream;
-    const size_t lds = sizeof(double) * 64 * (size_t)std::max(m->F | 1, m->K);
-    // two classes at a time up to 8 of them (a wave then has two), else four
-    auto kernel = m->K <= 8 ? predict_kernel<2> : predict_kernel<4>;
-    hipLaunchKernelGGL(kernel, dim3(grid_for(n, 64)), dim3(256), lds, s, d_features, n, m->F, (1 << 20) / m->F + 1,
+    // Rows of few features make a workgroup of 64 orders too small for its own
+    // start (1M orders of 8 features, 2 classes: 60 us, 24 with 256 orders): the
+    // 64, 128 or 256 orders whose features a workgroup's loads take at once,
+    // where the GPU still gets several workgroups per CU.
+    const int R = n < 32768 || m->F > 32 ? 1 : m->F > 16 ? 2 : 4;
+    // two classes at a time where each wave has no more than two, else four
+    const bool two = m->K * R <= 8;
+    auto kernel = R == 1   ? (two ? predict_kernel<1, 2> : predict_kernel<1, 4>)
+                  : R == 2 ? (two ? predict_kernel<2, 2> : predict_kernel<2, 4>)
+                           : (two ? predict_kernel<4, 2> : predict_kernel<4, 4>);
+    // the rows; the waves' bests of 256 orders and classes take their place
+    const size_t lds = sizeof(double) * std::max<size_t>(64 * (size_t)R * (m->F | 1), 256 + 128);
+    hipLaunchKernelGGL(kernel, dim3(grid_for(n, 64 * R)), dim3(256), lds, s, d_features, n, m->F, (1 << 20) / m->F + 1,
                        m->K, m->Wt, d_class);
     WO_HIP(hipGetLastError());
     return WO_OK;

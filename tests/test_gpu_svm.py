@@ -153,3 +153,58 @@ def test_training_rounds_and_zeros(F, K, n, density):
     w_gpu, _, _ = wo.wo_svm_get_weights(s)
     assert np.array_equal(w_gpu, O.train(x, y, K, 0.05, 2), equal_nan=True)
     s.free()
+
+
+@pytest.mark.parametrize("F,K", [(1, 2), (1, 64), (8, 3), (16, 2), (16, 33), (17, 2), (17, 4), (32, 5), (33, 8), (64, 9)])
+@pytest.mark.parametrize("n", [32767, 32768 + 255])
+def test_prediction_of_many_orders(F, K, n):
+    # 64, 128 or 256 orders per workgroup, by the features, from 32,768 orders
+    # on; scores that tie, are infinite or NaN in the first class, in a later one
+    # or in all
+    import torch
+    wo = _wo()
+    rng = np.random.default_rng(F * 1000 + K + n)
+    x = rng.normal(size=(n, F))
+    x[1::97] = 0.0
+    x[5::89, 0], x[7::83, F - 1] = np.inf, np.nan
+    x[11::79, 0], x[13::73] = -np.inf, -np.inf
+    m = 200
+    y = rng.integers(0, K, m).astype(np.int32)
+    s = wo.wo_svm_create(F, K, m, 0.05)
+    train = np.nan_to_num(x[:m], posinf=1.0, neginf=-1.0)
+    print("many orders", F, K, n, flush=True)
+    for steps in (0, 2):
+        if steps:
+            wo.wo_svm_push(s, _t(train, np.float64), _t(y, np.int32))
+            wo.wo_svm_train(s, steps)
+        w_gpu, _, _ = wo.wo_svm_get_weights(s)
+        cls = torch.full((n,), -7, dtype=torch.int32, device="cuda")
+        wo.wo_svm_predict(s, _t(x, np.float64), cls)
+        torch.cuda.synchronize()
+        assert np.array_equal(cls.cpu().numpy(), O.predict(x, w_gpu))
+    s.free()
+
+
+def test_prediction_time_follows_the_features():
+    # a million orders of 8 features against 64: an eighth of the bytes takes
+    # 0.15 of the time with 256 orders per workgroup, a half with 64
+    import torch
+    wo = _wo()
+    n, t = 1000000, {}
+    for F in (8, 64):
+        s = wo.wo_svm_create(F, 2, 64, 0.05)
+        x = torch.rand((n, F), dtype=torch.float64, device="cuda")
+        cls = torch.empty(n, dtype=torch.int32, device="cuda")
+        wo.wo_svm_predict(s, x, cls)
+        t[F] = float("inf")
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(5):
+                wo.wo_svm_predict(s, x, cls)
+            b.record()
+            torch.cuda.synchronize()
+            t[F] = min(t[F], a.elapsed_time(b) / 5)
+        s.free()
+    print("ms a call of 1,000,000 orders:", t, flush=True)
+    assert t[8] < 0.3 * t[64]
