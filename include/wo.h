@@ -164,7 +164,11 @@ enum { WO_ROUTE_SSHAPE = 0, WO_ROUTE_RETURN = 1, WO_ROUTE_LARGEST_GAP = 2, WO_RO
  * batching keeps per-plan tables in LDS -- about 4 bytes per order, 2 per
  * line and 4 per aisle -- and takes orders that visit at most 1,023 aisles;
  * an instance beyond either limit fails at load with WO_E_UNSUPPORTED (the
- * paper-scale instance needs 38 KB). */
+ * paper-scale instance needs 38 KB).  Loads of up to 4,096 orders per instance
+ * and 15 lines per order are batched from lists in device memory that the
+ * handle holds, at most 1.5 GB (536 MB at the paper scale, whatever the number
+ * of plans; the environment variable WO_SEED_SCRATCH_MB lowers the limit, and
+ * where the device has less left the handle takes less, down to none). */
 enum { WO_BATCH_NEXT_FIT = 0, WO_BATCH_FIRST_FIT = 1, WO_BATCH_SEED = 2 };
 #define WO_MAX_PICK_SLOTS 32
 #define WO_MAX_ROUTED_ORDER_LINES 8192

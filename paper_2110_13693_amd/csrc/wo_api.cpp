@@ -246,6 +246,61 @@ static wo_status check_desc(const wo_instance_desc &d, int idx)
     return WO_OK;
 }
 
+// First fit and seed batching: the most workgroups a launch may have, and the
+// tables of which each has a slice.
+static int ff_most_slots(const wo_wh *wh)
+{
+    return wh->cu_count * eval_ff_max_blocks_per_cu(wh->route, wh->ff_batch,
+                                                    *std::min_element(wh->ff_lds.begin(), wh->ff_lds.end()));
+}
+
+static wo_status ff_tables(wo_wh *wh)
+{
+    wo_status st = dev_alloc((void **)&wh->d_ff_tour, sizeof(uint16_t) * (size_t)wh->ff_stride * wh->ff_slots);
+    return st ? st : dev_alloc((void **)&wh->d_ff_queue, sizeof(uint32_t) * (size_t)wh->ff_stride * wh->ff_slots);
+}
+
+// Packed seed batching: a slice of lists and masks for each workgroup of a
+// launch, laid out once with the handle (a call may be captured, and a captured
+// launch keeps its pointers).  16 workgroups per CU at most, as the registers
+// allow, and SEED_SCRATCH bytes in all: the paper scale takes 536 MB for its 16
+// per CU, 4,096 orders of 15 lines over 400 aisles 1.48 GB (with 7 per CU 4,096
+// of their plans take 59 ms, 33 with 16).  Where the device has not that much
+// left, half as many workgroups are tried, down to one per CU, then the general
+// form, which keeps its tables in LDS: no load fails for these lists.
+// (WO_SEED_SCRATCH_MB lowers the limit.)
+static wo_status seed_scratch(wo_wh *wh)
+{
+    int64_t cap = SEED_SCRATCH;
+    if (const char *mb = getenv("WO_SEED_SCRATCH_MB")) cap = std::min<int64_t>(cap, atoll(mb) << 20);
+    int64_t lines_max = 0, hot_max = 0;
+    for (const InstDev &I : wh->inst) {
+        lines_max = std::max<int64_t>(lines_max, I.n_lines);
+        // a line is in one list at most and a list is an aisle's, which bounds
+        // the long ones
+        hot_max = std::max<int64_t>(hot_max, std::min(I.n_lines / (SEED_COLD + 1), I.n_aisles));
+    }
+    wh->seed_apos = 2u * SEED_FWD * (uint32_t)wh->ff_stride;
+    wh->seed_hot = (uint32_t)(((int64_t)wh->seed_apos + 2 * lines_max + 255) & ~(int64_t)255);
+    wh->seed_stride = (int64_t)wh->seed_hot + 512 * hot_max;
+    const int64_t fit = cap / wh->seed_stride;
+    int64_t slots = std::min<int64_t>(ff_most_slots(wh), 16 * wh->cu_count);
+    if (slots > fit) slots = fit / wh->cu_count * wh->cu_count;       // as many for every CU
+    for (; slots >= wh->cu_count; slots /= 2) {
+        wh->ff_slots = (int)slots;
+        wo_status st = dev_alloc((void **)&wh->d_seed_scr, (size_t)wh->seed_stride * slots);
+        if (!st) st = ff_tables(wh);
+        if (!st) return WO_OK;
+        (void)hipGetLastError();
+        for (void **p : {(void **)&wh->d_seed_scr, (void **)&wh->d_ff_tour, (void **)&wh->d_ff_queue}) {
+            if (*p) (void)hipFree(*p);
+            *p = nullptr;
+        }
+    }
+    wh->ff_batch = FF_SEED;
+    return WO_OK;
+}
+
 extern "C" wo_status wo_load_warehouse(const wo_instance_desc *descs, int32_t n_instances, void *stream,
                                        wo_wh **out)
 {
@@ -568,23 +623,16 @@ extern "C" wo_status wo_load_warehouse(const wo_instance_desc *descs, int32_t n_
     wh->ff_lds_max = *std::max_element(wh->ff_lds.begin(), wh->ff_lds.end());
     if (wh->batching != WO_BATCH_NEXT_FIT) {
         wh->ff_stride = ((int64_t)wh->max_orders + 1 + 63) & ~(int64_t)63;
-        wh->ff_slots = wh->cu_count *
-                       eval_ff_max_blocks_per_cu(wh->route, wh->ff_batch,
-                                                 *std::min_element(wh->ff_lds.begin(), wh->ff_lds.end()));
         if (wh->ff_batch == FF_SEED_PACKED) {
-            int32_t lines_max = 0;
-            for (int32_t i = 0; i < n_instances; i++) lines_max = std::max(lines_max, wh->inst[i].n_lines);
-            wh->ff_slots = std::min(wh->ff_slots, 16 * wh->cu_count);
-            wh->seed_apos = 2u * SEED_FWD * (uint32_t)wh->ff_stride;
-            wh->seed_hot = (uint32_t)(((int64_t)wh->seed_apos + 2 * (int64_t)lines_max + 255) & ~(int64_t)255);
-            // a line is in one list at most, so this bounds the long ones
-            wh->seed_stride = (int64_t)wh->seed_hot + 512 * (int64_t)(lines_max / (SEED_COLD + 1) + 1);
-            if ((st = dev_alloc((void **)&wh->d_seed_scr, (size_t)wh->seed_stride * wh->ff_slots))) return st;
+            if ((st = seed_scratch(wh))) return st;
+            if (wh->ff_batch == FF_SEED)                 // no room for the lists: the general form
+                for (int32_t i = 0; i < n_instances; i++) wh->ff_lds[i] = std::max(wh->ff_lds[i], seed_need[i]);
+            wh->ff_lds_max = *std::max_element(wh->ff_lds.begin(), wh->ff_lds.end());
         }
-        if ((st = dev_alloc((void **)&wh->d_ff_tour, sizeof(uint16_t) * (size_t)wh->ff_stride * wh->ff_slots)))
-            return st;
-        if ((st = dev_alloc((void **)&wh->d_ff_queue, sizeof(uint32_t) * (size_t)wh->ff_stride * wh->ff_slots)))
-            return st;
+        if (wh->ff_batch != FF_SEED_PACKED) {
+            wh->ff_slots = ff_most_slots(wh);
+            if ((st = ff_tables(wh))) return st;
+        }
     }
     guard.release();
     *out = wh;

@@ -230,6 +230,7 @@ constexpr int SEED_PACKED_ORDERS = 4096;
 constexpr int SEED_PACKED_LINES = 15;
 constexpr int SEED_FWD = 4;
 constexpr int SEED_COLD = 64;           // longest list kept as one: an entry per lane
+constexpr int64_t SEED_SCRATCH = 1536ll << 20;  // most scratch of a handle
 struct SeedPackedLayout {
     uint32_t mask, aend, tbits, total;
 };

@@ -177,3 +177,53 @@ def test_packed_form_edges(case):
     Z[0, :12] = np.arange(12)                                    # the identity: aisle 0 holds SKUs 0 .. 59
     print("case", case, flush=True)
     _compare(inst, Z, S)
+
+
+def _device_mb():
+    import torch
+    torch.cuda.synchronize()
+    return torch.cuda.mem_get_info()[0] / 2**20
+
+
+def test_memory_of_the_largest_packed_load():
+    # 4,096 orders of 15 lines over 400 aisles: the lists' masks number no more
+    # than the aisles, 1.48 GB in all for 16 workgroups per CU (2.7 GB when their
+    # number was bounded by the lines alone)
+    from tests.whelpers import tiny_geometry
+    wo = _wo()
+    rng = np.random.default_rng(73)
+    inst = _sd(tiny_geometry([[int(x) for x in rng.integers(0, 12000, 15)] for _ in range(4096)], capacity=30, n_aisles=400,
+                             slots=30, n_cat=12, cat_size=1000))
+    Z, S = synth.make_plans(inst, 2, seed=5)
+    before = _device_mb()
+    wh = wo.wo_load_warehouse([inst])
+    used = before - _device_mb()
+    d, _ = gpu_eval(wh, Z, S)
+    wh.free()
+    print("MB of the load:", used, flush=True)
+    assert used < 1700
+    assert np.array_equal(d, oracle.eval_plans(inst, Z, S)[0])
+
+
+@pytest.mark.parametrize("mb,most", [("0", 40), ("1", 40), ("60", 100), ("200", 260)])
+def test_less_scratch_than_the_lists_want(mb, most, monkeypatch):
+    # a limit below one workgroup's slice per CU gives the general form, a
+    # higher one fewer workgroups than the registers allow, with several plans
+    # each; the distances are the same
+    wo = _wo()
+    inst, Z, S = synth.workload("paper", n_plans=600)
+    inst = _sd(inst)
+    monkeypatch.setenv("WO_SEED_SCRATCH_MB", mb)
+    before = _device_mb()
+    wh = wo.wo_load_warehouse([inst])
+    used = before - _device_mb()
+    print("limit", mb, "MB of the load:", used, flush=True)
+    d, _ = gpu_eval(wh, Z, S)
+    wh.free()
+    assert used < most
+    monkeypatch.delenv("WO_SEED_SCRATCH_MB")
+    wh = wo.wo_load_warehouse([inst])
+    d_all, _ = gpu_eval(wh, Z, S)
+    wh.free()
+    assert np.array_equal(d, d_all)
+    assert np.array_equal(d[:8], oracle.eval_plans(inst, Z[:8], S[:8])[0])
