@@ -985,9 +985,10 @@ static __device__ __forceinline__ uint32_t order_key(float f)
 
 constexpr int TOPK_THREADS = 1024;
 constexpr int TK_U = 16, TK_BINS = 2048, TK_CAP = 8192, TK_SORT_BINS = 4096;
-// Entries of a bin from which the network is faster.  8,192 keys in bins of 137
-// equal ones: the call 104 us by ranks, 116 by the network; of 273: 156 to 261
-// and 115; all equal: 3,200 and 116.
+// Comparisons of the ranks (the sum of the bins' squares) per entry of the
+// network from which the network is faster.  8,192 keys in bins of 137 equal
+// ones: the call 104 us by ranks, 116 by the network; of 273: 156 to 261 and 115;
+// all equal: 3,200 and 116.
 constexpr uint32_t TK_CROWD = 160;
 static_assert(TK_CAP >= TOPK_MAX, "the winners fit");
 
@@ -1128,7 +1129,7 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_kernel(const uint32_t *src,
     const uint32_t width = hi - least;
     const int shift = width < (uint32_t)TK_SORT_BINS ? 0 : 20 - __builtin_clz(width);   // width >> shift < TK_SORT_BINS
     for (int i = tid; i < TK_SORT_BINS; i += TOPK_THREADS) bins[i] = 0u;
-    if (tid == 0) sel[0] = 0u;                           // 1: a crowded bin
+    if (tid == 0) sel[0] = 0u;                           // comparisons
     __syncthreads();
     constexpr int PER = TK_CAP / TOPK_THREADS;
     unsigned long long e[PER];
@@ -1138,12 +1139,29 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_kernel(const uint32_t *src,
         const uint32_t i = (uint32_t)(j * TOPK_THREADS + tid);
         e[j] = i < total ? ent[i] : 0ull;
         at[j] = i < total ? atomicAdd(&bins[((uint32_t)(e[j] >> 32) - least) >> shift], 1u) : 0u;
-        if (at[j] >= TK_CROWD) sel[0] = 1u;              // (every writer stores 1)
     }
     __syncthreads();
-    if (sel[0]) {                                        // uniform
-        int P2 = 2;
-        while (P2 < (int)total) P2 <<= 1;                // at most TK_CAP
+    {
+        uint32_t c[TK_SORT_BINS / TOPK_THREADS], sum = 0, sq = 0;
+#pragma unroll
+        for (int j = 0; j < TK_SORT_BINS / TOPK_THREADS; j++) {
+            c[j] = bins[tid * (TK_SORT_BINS / TOPK_THREADS) + j];
+            sum += c[j];
+            sq += c[j] * c[j];
+        }
+        sq = wave_incl_scan(sq);
+        if (lane == 63) atomicAdd(&sel[0], sq);          // at most TK_CAP^2
+        uint32_t run = block_excl_scan(sum, part);
+#pragma unroll
+        for (int j = 0; j < TK_SORT_BINS / TOPK_THREADS; j++) {
+            bins[tid * (TK_SORT_BINS / TOPK_THREADS) + j] = run;
+            run += c[j];
+        }
+    }
+    __syncthreads();
+    int P2 = 2;
+    while (P2 < (int)total) P2 <<= 1;                    // at most TK_CAP
+    if (sel[0] > TK_CROWD * (uint32_t)P2) {              // uniform
         for (int i = (int)total + tid; i < P2; i += TOPK_THREADS) ent[i] = ~0ull;
         for (int size = 2; size <= P2; size <<= 1)
             for (int stride = size >> 1; stride > 0; stride >>= 1) {
@@ -1162,21 +1180,6 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_kernel(const uint32_t *src,
         for (int i = tid; i < k; i += TOPK_THREADS) out[i] = (int32_t)(ent[i] & 0xFFFFFFFFull);
         return;
     }
-    {
-        uint32_t c[TK_SORT_BINS / TOPK_THREADS], sum = 0;
-#pragma unroll
-        for (int j = 0; j < TK_SORT_BINS / TOPK_THREADS; j++) {
-            c[j] = bins[tid * (TK_SORT_BINS / TOPK_THREADS) + j];
-            sum += c[j];
-        }
-        uint32_t run = block_excl_scan(sum, part);
-#pragma unroll
-        for (int j = 0; j < TK_SORT_BINS / TOPK_THREADS; j++) {
-            bins[tid * (TK_SORT_BINS / TOPK_THREADS) + j] = run;
-            run += c[j];
-        }
-    }
-    __syncthreads();
 #pragma unroll
     for (int j = 0; j < PER; j++)
         if ((uint32_t)(j * TOPK_THREADS + tid) < total) srt[bins[((uint32_t)(e[j] >> 32) - least) >> shift] + at[j]] = e[j];
