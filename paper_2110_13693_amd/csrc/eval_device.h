@@ -330,19 +330,42 @@ struct PickWalk {
 
 // Route cost of one tour from its row of np (1 .. pick_slots) picks.  The
 // slots past np repeat the first pick, which changes no route and spares
-// each step a look at np.
+// each step a look at np.  The combined route's steps, the dearest, come in eights
+// of which rows of few slots leave out the last: their entries sort to the end
+// (3,732 plans of 4,000 orders at capacity 13: 261 to 204 us; at 30 185 both ways).
 template <int ROUTE>
 static __device__ __forceinline__ int64_t pick_route_cost(const uint32_t *picks, uint32_t np, int32_t spacing,
                                                           InstConst &I, uint32_t magic)
 {
     uint32_t v[MAX_PICK_SLOTS];
     v[0] = picks[0];
+    if constexpr (ROUTE != WO_ROUTE_COMBINED) {
 #pragma unroll
-    for (int i = 1; i < MAX_PICK_SLOTS; i++) v[i] = (uint32_t)i < np ? picks[i] : v[0];
+        for (int i = 1; i < MAX_PICK_SLOTS; i++) v[i] = (uint32_t)i < np ? picks[i] : v[0];
+        sort32(v);
+        PickWalk<ROUTE> w(I, spacing, magic, v[0]);
+#pragma unroll
+        for (int i = 1; i < MAX_PICK_SLOTS; i++) w.step(v[i]);
+        return w.cost();
+    }
+    const int slots = I.pick_slots;                      // uniform
+#pragma unroll
+    for (int e = 0; e < MAX_PICK_SLOTS; e += 8) {
+        if (e < slots) {
+#pragma unroll
+            for (int i = e ? e : 1; i < e + 8; i++) v[i] = (uint32_t)i < np ? picks[i] : v[0];
+        } else {
+#pragma unroll
+            for (int i = e; i < e + 8; i++) v[i] = 0xFFFFFFFFu;
+        }
+    }
     sort32(v);
     PickWalk<ROUTE> w(I, spacing, magic, v[0]);
 #pragma unroll
-    for (int i = 1; i < MAX_PICK_SLOTS; i++) w.step(v[i]);
+    for (int e = 0; e < MAX_PICK_SLOTS; e += 8)
+        if (e < slots)
+#pragma unroll
+            for (int i = e ? e : 1; i < e + 8; i++) w.step(v[i]);
     return w.cost();
 }
 

@@ -351,12 +351,13 @@ def test_validation_of_long_sequences(n, monkeypatch):
     wh.free()
 
 
-def _plans_ms(n, n_plans, block=256, small_orders=0):
+def _plans_ms(n, n_plans, block=256, small_orders=0, routing=0, capacity=30):
     """Best time of one call over random plans of an instance of n orders."""
+    import dataclasses
     import torch
     wo = _wo()
     rng = np.random.default_rng(n)
-    inst = _random_instance(rng, 100, 250, n, 30, 12, lam=1.5)
+    inst = dataclasses.replace(_random_instance(rng, 100, 250, n, capacity, 12, lam=1.5), routing=routing)
     wh = wo.wo_load_warehouse([inst])
     wo.wo_set_eval_config(wh, block, small_orders=small_orders)
     z = torch.from_numpy(synth.generators.random_zone_perms(rng, n_plans, 12)).cuda()

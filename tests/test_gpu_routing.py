@@ -8,6 +8,7 @@ import pytest
 
 import oracle
 import synth
+from tests.gpu_util import gpu_eval
 from tests.test_gpu_eval import _compare, _random_instance, _structured_sequences, _wo
 
 pytestmark = pytest.mark.gpu
@@ -190,3 +191,27 @@ def test_products_past_24_bits(aisles, slots, pitch, spacing, routing):
         Z, S = synth.make_plans(inst, 16, seed=seed)
         print("products", aisles, slots, pitch, spacing, routing, flush=True)
         _compare(_routed(inst, routing), Z, S)
+
+
+@pytest.mark.parametrize("capacity", [1, 7, 8, 9, 16, 24, 25, 32])
+def test_combined_route_of_short_rows(capacity):
+    # the steps of a row come in eights: capacities at and around whole ones,
+    # orders up to the row's length and beyond the capacity
+    rng = np.random.default_rng(capacity)
+    inst = dataclasses.replace(_random_instance(rng, 20, 15, 300, capacity, 12, lam=2.5), routing=4)
+    Z, S = synth.make_plans(inst, 9, seed=capacity)
+    print("combined", capacity, flush=True)
+    wo = _wo()
+    wh = wo.wo_load_warehouse([inst])
+    d, _ = gpu_eval(wh, Z, S)
+    wh.free()
+    assert np.array_equal(d, oracle.eval_plans(inst, Z, S)[0])
+
+
+def test_combined_route_time_at_a_small_capacity():
+    # tours of 13 items against tours of 30 of the same orders: 1.1 times the time
+    # where the steps past a row's slots are left out, 1.4 where they are taken
+    from tests.test_gpu_eval import _plans_ms
+    t = {Q: _plans_ms(4000, 3732, small_orders=1024, routing=4, capacity=Q) for Q in (13, 30)}
+    print("ms a call of 3,732 plans:", t, flush=True)
+    assert t[13] < 1.25 * t[30]
