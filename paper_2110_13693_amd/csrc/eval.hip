@@ -984,7 +984,7 @@ static int max_blocks_t(uint32_t lds_bytes)
         (void)hipGetLastError();
         return 1;
     }
-    return n > 0 ? n : 1;
+    return std::max(1, std::min(n, lds_fit(lds_bytes)));
 }
 
 template <int BLOCK, int ROUTE, bool SEQ_PASS>

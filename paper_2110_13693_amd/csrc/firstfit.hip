@@ -911,7 +911,7 @@ static int ff_max_blocks_r(uint32_t lds_bytes)
         (void)hipGetLastError();
         return 1;
     }
-    return n > 0 ? n : 1;
+    return std::max(1, std::min(n, lds_fit(lds_bytes)));
 }
 
 template <int BATCH>

@@ -2,6 +2,8 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
 #include <stdint.h>
 
 #include "../../include/wo.h"
@@ -247,6 +249,13 @@ __host__ __device__ inline SeedPackedLayout seed_packed_layout(int32_t n_aisles)
 
 // order batching kernels of firstfit.hip
 enum { FF_FIRST_FIT = 0, FF_SEED = 1, FF_SEED_PACKED = 2 };
+
+// Workgroups whose LDS a CU holds: it is allocated in pieces of 1,280 bytes, 128
+// of them, which the runtime's occupancy does not count.  A grid of one workgroup
+// too many per CU takes its plans in a wave of its own behind the others (3,732
+// plans of 2,000 orders, return route: five per CU launched of which four run,
+// 105 us; four 65 us).
+inline int lds_fit(uint32_t lds_bytes) { return 128 / (int)std::max(1u, (lds_bytes + 1279u) / 1280u); }
 
 hipError_t launch_eval(const EvalArgs &a, uint32_t lds_bytes, int grid, int block, int route, hipStream_t s);
 // workgroups of the evaluation kernel that fit one CU (registers and LDS), for

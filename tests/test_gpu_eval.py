@@ -394,3 +394,33 @@ def test_time_of_small_instances_by_wide_workgroups():
     t = {n: _plans_ms(n, 16384) for n in (1000, 4000)}
     print("ms a call of 16,384 plans:", t, flush=True)
     assert t[1000] < 0.85 * t[4000]
+
+
+def _return_route_lds(n, capacity=30):
+    """LDS of a plan of _plans_ms's instance of n orders under the return route,
+    as the library lays it out (4,096 orders at most)."""
+    rng = np.random.default_rng(n)
+    lens = np.minimum(np.diff(_random_instance(rng, 100, 250, n, capacity, 12, lam=1.5).order_offsets), capacity + 1)
+    tours, load = 1, 0
+    for k in lens:
+        if load + k > capacity:
+            tours, load = tours + 1, 0
+        load += int(k)
+    up = lambda x, a: (x + a - 1) // a * a   # noqa: E731
+    row = 4 * ((max(capacity, int(lens.max())) + 1) | 1)
+    rows = min(int(np.ceil(1.04 * tours)) + 8, n, 65535 // row - 1) + 1
+    words = int(lens.sum()) // 32 + 3
+    at = max(up(480 + row * rows, 16), 480 + 512 + up(n, 64)) + up(n + 2, 16)
+    at = up(at + 2 * (n + 2), 16)
+    return up(up(up(at + 4 * words, 16) + 4 * words, 16) + 4 * (n // 32 + 3), 16)
+
+
+def test_grid_by_the_lds_that_a_cu_allocates():
+    # plans whose LDS fits a CU five times in bytes but four times in the pieces
+    # that it is allocated in: 3,732 plans are four rounds of 1,024 (2.9 times the
+    # time of one); a grid of 1,280 takes a fifth of them in rounds of their own
+    # (4 times)
+    n = next(k for k in range(1900, 2049) if 32000 < _return_route_lds(k) <= 32768)
+    t = {P: _plans_ms(n, P, small_orders=1024, routing=1) for P in (1024, 3732)}
+    print("orders", n, "LDS", _return_route_lds(n), "ms a call:", t, flush=True)
+    assert t[3732] < 3.5 * t[1024]
