@@ -202,13 +202,15 @@ static constexpr int seq_cap(int block) { return block >= 256 ? 4096 : 16 * bloc
 // Waves per SIMD, by registers: four, as the LDS of a paper-scale plan allows;
 // the 128-thread workgroups, with chunks of a size of their own, spill 37
 // registers at four and run in 61 us at three, 69 at four (their part of 128
-// uneven instances x 256 plans).
+// uneven instances x 256 plans); with pick rows too, 2 to 10 registers spilt (3,732
+// plans of 1,366 orders by the optimal route 95 us, 116 at two).
 // LONG: instances of more than seq_cap(BLOCK) orders are among the launch's, an
 // instantiation of its own, so that the other carries none of its code (4,096
 // paper-scale plans 72.5 us with it, 71.5 without).
 template <int BLOCK, int ROUTE, bool SEQ_PASS, bool LONG>
 __global__ __launch_bounds__(BLOCK, ROUTE == WO_ROUTE_RETURN && BLOCK == 512 ? 4
-                                    : ROUTE != WO_ROUTE_SSHAPE ? 2 : BLOCK == 128 ? 3 : 4) void eval_plans_kernel(EvalArgs A)
+                                    : BLOCK == 128 && (ROUTE == WO_ROUTE_SSHAPE || !LONG) ? 3
+                                    : ROUTE != WO_ROUTE_SSHAPE ? 2 : 4) void eval_plans_kernel(EvalArgs A)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     uint32_t &s_next = *(uint32_t *)(smem + LDS_TICKET);

@@ -215,3 +215,13 @@ def test_combined_route_time_at_a_small_capacity():
     t = {Q: _plans_ms(4000, 3732, small_orders=1024, routing=4, capacity=Q) for Q in (13, 30)}
     print("ms a call of 3,732 plans:", t, flush=True)
     assert t[13] < 1.25 * t[30]
+
+
+@pytest.mark.parametrize("routing", [2, 3, 4])
+def test_plans_per_cu_of_the_128_thread_kernels(routing):
+    # five plans of 1,366 orders per CU go through at once as four do (1.1 times
+    # the time); where the registers leave room for four, in two rounds (1.35)
+    from tests.test_gpu_eval import _plans_ms
+    t = {P: _plans_ms(1366, P, small_orders=1024, routing=routing) for P in (1024, 1280)}
+    print("route", routing, "ms a call:", t, flush=True)
+    assert t[1280] < 1.25 * t[1024]
