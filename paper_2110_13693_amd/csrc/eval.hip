@@ -148,7 +148,7 @@ static __device__ __forceinline__ uint32_t bits_at(const uint32_t *B, uint32_t x
 #define WO_ALL_ISSUED() __builtin_amdgcn_sched_barrier(0)
 
 // The order ids of sequence positions [0, nv) of `s`, two per 32-bit word, of
-// a chunk of ch (4, 8 or 16; at most CH).  A full chunk is loaded as it is,
+// a chunk of ch (4, 8, 12 or 16; at most CH).  A full chunk is loaded as it is,
 // at whatever alignment the row has (rows of an odd order count are only 2-byte
 // aligned, which global loads take; 16 loads of an id each otherwise), and the function returns true: the caller clamps it to n - 1 (with
 // min_u16x2) when it uses it, so that a prefetch does not wait for its data.
@@ -160,6 +160,7 @@ static __device__ __forceinline__ bool load_chunk(const uint16_t *s, int nv, int
     constexpr int SEQ_CHUNK = CH;
     if (nv == ch) {
         if (!VAR_CH || ch == CH) __builtin_memcpy(out, s, 2 * CH);
+        else if (ch == 12) __builtin_memcpy(out, s, 24);
         else if (ch == 8) __builtin_memcpy(out, s, 16);
         else __builtin_memcpy(out, s, 8);
         return true;
@@ -215,12 +216,14 @@ __global__ __launch_bounds__(BLOCK, ROUTE == WO_ROUTE_RETURN && BLOCK == 512 ? 4
     extern __shared__ __align__(16) unsigned char smem[];
     uint32_t &s_next = *(uint32_t *)(smem + LDS_TICKET);
     constexpr int SEQ_CHUNK = seq_cap(BLOCK) / BLOCK;   // sequence positions per thread in registers
-    // the workgroups of small instances use 4, 8 or 16 of them, the fewest that
-    // hold the orders (with 16 always, the 200-order call took 13.1 us, not 11.7)
+    // the workgroups of small instances use 4, 8, 12 or 16 of them, the fewest that
+    // hold the orders (with 16 always, the 200-order call took 13.1 us, not 11.7;
+    // without 12, 3,732 plans of 700 orders 26.5 us, not 22.5; of 1,366 41.3, not 36.6)
     constexpr bool VAR_CH = BLOCK < 256;
     auto chunk_of = [](int orders) -> int {
         if (VAR_CH && orders <= 4 * BLOCK) return 4;
         if (VAR_CH && orders <= 8 * BLOCK) return 8;
+        if (VAR_CH && orders <= 12 * BLOCK) return 12;
         if (!LONG) return SEQ_CHUNK;
         return (orders + BLOCK * SEQ_CHUNK - 1) / (BLOCK * SEQ_CHUNK) * SEQ_CHUNK;
     };
@@ -496,8 +499,7 @@ __global__ __launch_bounds__(BLOCK, ROUTE == WO_ROUTE_RETURN && BLOCK == 512 ? 4
                             run1 += CS(h + k);
                         }
                     }
-                if (nv > 0)
-                    WO_FOURS(k, ch) if (k % 4 == 0) ((uint32_t *)(step + b0))[k / 4] = sp[k / 4];
+                WO_FOURS(k, ch) if (k % 4 == 0 && k < nv) ((uint32_t *)(step + b0))[k / 4] = sp[k / 4];
             } else {
                 uint32_t run1 = run0 + 1u;
                 for (int i = b0; i < b1; i += 8) {
@@ -572,6 +574,9 @@ __global__ __launch_bounds__(BLOCK, ROUTE == WO_ROUTE_RETURN && BLOCK == 512 ? 4
                         if (LONG && s0 > wbase) load_segments(s0);
                         uint32_t m[SPW];
                         WO_FOURS(j, ch) m[j] = seg[j];
+                        if (VAR_CH && ch == 12)          // no such segments: the map that changes nothing
+#pragma unroll
+                            for (int j = 12; j < SPW; j++) m[j] = 256u + 4u * (uint32_t)lane;
 #pragma unroll
                         for (int d = 1; d < SPW; d <<= 1)
                             if (!VAR_CH || d < ch)
@@ -610,11 +615,17 @@ __global__ __launch_bounds__(BLOCK, ROUTE == WO_ROUTE_RETURN && BLOCK == 512 ? 4
                     if (lim > 0) *(uint2 *)&P[sb >> 5] = make_uint2((uint32_t)open, (uint32_t)(open >> 32));
                     if (one_piece) {
                         // the mask of the segment that the thread's positions lie in
+                        // (12 of them may reach into the next one)
                         const int c0 = VAR_CH ? ch : SEQ_CHUNK;
                         const int from = (lane * c0 >> 6) << 2, sh = lane * c0 & 63;
                         const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)(uint32_t)open);
                         const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)(uint32_t)(open >> 32));
-                        opm = ((sh < 32 ? lo : hi) >> (sh & 31)) & ((1u << c0) - 1u);
+                        uint32_t above = 0;
+                        if (VAR_CH && ch == 12) {
+                            const uint32_t next = (uint32_t)__builtin_amdgcn_ds_bpermute(from + 4, (int)(uint32_t)open);
+                            above = sh < 32 ? hi : next;
+                        }
+                        opm = __builtin_amdgcn_alignbit(above, sh < 32 ? lo : hi, sh & 31) & ((1u << c0) - 1u);
                     }
                     if (!LONG) break;
                 }
@@ -669,7 +680,7 @@ __global__ __launch_bounds__(BLOCK, ROUTE == WO_ROUTE_RETURN && BLOCK == 512 ? 4
                         const uint4 o = nx;
                         if (i + 8 < b1) nx = load_piece(seq, i + 8, b1, (uint32_t)n);
                         const uint32_t w[4] = {o.x, o.y, o.z, o.w};
-                        const uint32_t op = P[i >> 5] >> (i & 31);
+                        const uint32_t op = bits_at(P, (uint32_t)i);
 #pragma unroll
                         for (int k = 0; k < 8; k++) {
                             if (i + k < b1) t += (op >> k) & 1u;

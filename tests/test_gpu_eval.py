@@ -424,3 +424,34 @@ def test_grid_by_the_lds_that_a_cu_allocates():
     t = {P: _plans_ms(n, P, small_orders=1024, routing=1) for P in (1024, 3732)}
     print("orders", n, "LDS", _return_route_lds(n), "ms a call:", t, flush=True)
     assert t[3732] < 3.5 * t[1024]
+
+
+@pytest.mark.parametrize("n,block", [(513, 64), (575, 64), (576, 64), (577, 64), (700, 64), (767, 64), (768, 64), (769, 64),
+                                     (1025, 128), (1087, 128), (1088, 128), (1471, 128), (1472, 128), (1473, 128),
+                                     (1535, 128), (1536, 128), (1537, 128)])
+def test_chunks_of_12_positions(n, block):
+    # chunks of 12 positions reach over the ends of segments of 64; the last
+    # thread's chunk may end past the last segment; the second wave starts at
+    # position 768, where a tour goes on
+    wo = _wo()
+    rng = np.random.default_rng(n)
+    for capacity, lam in ((1, 0.0), (32, 0.0), (7, 1.5), (32, 3.0)):
+        inst = _random_instance(rng, 10, 30, n, capacity, 12, lam=lam)
+        Z, S = synth.make_plans(inst, 5, seed=n + capacity)
+        S[0] = np.arange(n)
+        S[1] = np.argsort(np.diff(inst.order_offsets), kind="stable")
+        print("chunks", n, block, capacity, lam, flush=True)
+        wh = wo.wo_load_warehouse([inst])
+        wo.wo_set_eval_config(wh, block, small_orders=0)
+        for _ in range(2):               # the second call's plans find the first's tables
+            d, _ = gpu_eval(wh, Z, S)
+            assert np.array_equal(d, oracle.eval_plans(inst, Z, S)[0])
+        wh.free()
+
+
+def test_time_of_chunks_of_12_positions():
+    # 700 orders by 64 threads against 900: 0.83 of the time with 12 positions
+    # per thread, 0.98 with 16 (the last 20 threads then had none)
+    t = {n: _plans_ms(n, 3732, block=64) for n in (700, 900)}
+    print("ms a call of 3,732 plans:", t, flush=True)
+    assert t[700] < 0.91 * t[900]
