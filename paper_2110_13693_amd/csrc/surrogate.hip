@@ -1129,7 +1129,7 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_kernel(const uint32_t *src,
     const uint32_t width = hi - least;
     const int shift = width < (uint32_t)TK_SORT_BINS ? 0 : 20 - __builtin_clz(width);   // width >> shift < TK_SORT_BINS
     for (int i = tid; i < TK_SORT_BINS; i += TOPK_THREADS) bins[i] = 0u;
-    if (tid == 0) sel[0] = 0u;                           // comparisons
+    if (tid < 2) sel[tid] = 0u;                          // 1: a bin that may be crowded; comparisons
     __syncthreads();
     constexpr int PER = TK_CAP / TOPK_THREADS;
     unsigned long long e[PER];
@@ -1139,6 +1139,7 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_kernel(const uint32_t *src,
         const uint32_t i = (uint32_t)(j * TOPK_THREADS + tid);
         e[j] = i < total ? ent[i] : 0ull;
         at[j] = i < total ? atomicAdd(&bins[((uint32_t)(e[j] >> 32) - least) >> shift], 1u) : 0u;
+        if (at[j] >= TK_CROWD) sel[0] = 1u;              // (else the comparisons stay below the limit)
     }
     __syncthreads();
     {
@@ -1149,8 +1150,10 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_kernel(const uint32_t *src,
             sum += c[j];
             sq += c[j] * c[j];
         }
-        sq = wave_incl_scan(sq);
-        if (lane == 63) atomicAdd(&sel[0], sq);          // at most TK_CAP^2
+        if (sel[0]) {                                    // uniform
+            sq = wave_incl_scan(sq);
+            if (lane == 63) atomicAdd(&sel[1], sq);      // at most TK_CAP^2
+        }
         uint32_t run = block_excl_scan(sum, part);
 #pragma unroll
         for (int j = 0; j < TK_SORT_BINS / TOPK_THREADS; j++) {
@@ -1159,9 +1162,8 @@ __global__ __launch_bounds__(TOPK_THREADS) void topk_kernel(const uint32_t *src,
         }
     }
     __syncthreads();
-    int P2 = 2;
-    while (P2 < (int)total) P2 <<= 1;                    // at most TK_CAP
-    if (sel[0] > TK_CROWD * (uint32_t)P2) {              // uniform
+    const int P2 = total > 1u ? 1 << (32 - __builtin_clz(total - 1u)) : 1;   // at most TK_CAP
+    if (sel[1] > TK_CROWD * (uint32_t)P2) {              // uniform
         for (int i = (int)total + tid; i < P2; i += TOPK_THREADS) ent[i] = ~0ull;
         for (int size = 2; size <= P2; size <<= 1)
             for (int stride = size >> 1; stride > 0; stride >>= 1) {
