@@ -535,7 +535,7 @@ typedef struct {
     int32_t width_dm;          /* the optimum a (max_width_dm when no width is feasible) */
     int32_t spacing_dm;        /* a + 2 r: the aisles' centre-to-centre distance */
     int32_t feasible;          /* 1 when k * delta <= a holds at width_dm */
-    int32_t widths_evaluated;
+    int32_t widths_evaluated;  /* widths decided: those of the range */
     int32_t distance;          /* D of the plan at width_dm (int32, saturating) */
     double orders_per_window;  /* delta at width_dm, in IEEE double */
     double utilization;        /* A_ind / A_max at width_dm */

@@ -27,8 +27,8 @@
 //      per segment then walks its 64 positions and notes the openings as a mask.
 //      (Chains of LDS reads bound this part: about 8 thousand cycles a plan
 //      of 4,000 orders, 16 with candidate chains through the bitmap and their
-//      links.  4,096 such plans 79 to 72 us, 128 uneven instances x 256 plans
-//      292 to 229 us, with chunks of fewer positions for small instances,
+//      links.  4,096 such plans 79 to 70 us, 128 uneven instances x 256 plans
+//      277 to 212 us, with chunks of fewer positions for small instances,
 //      unaligned sequence loads and the instance table read as constants.)
 //   4. tour ids: a thread takes its positions' flags from the masks; a block
 //      scan over their counts numbers the tours, and every order's entry in

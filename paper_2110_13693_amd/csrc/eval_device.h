@@ -8,7 +8,8 @@
 
 namespace wo {
 
-// Tables that no kernel writes, as constant memory: at a uniform address their
+// Tables that are not written while the kernel runs (copies and earlier kernels of
+// the stream fill them), as constant memory: at a uniform address their
 // values come by scalar loads into scalar registers.  (Through plain pointers
 // every field of a plan's instance is a vector load and a lane read, since a
 // store or a barrier might have changed it: a chain of some six trips to memory

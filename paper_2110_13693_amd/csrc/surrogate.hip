@@ -774,7 +774,7 @@ __global__ __launch_bounds__(64 * W1_WAVES) void w1_grad_kernel(const uint16_t *
     }
     __syncthreads();
     for (int k = tid; k < W1_SLICE * 64; k += 64 * W1_WAVES) {
-        // slice k / 4096 of W1's layout, row (zone) j, unit r of the slice
+        // slice k / 8,192 of W1's layout, row (zone) j, unit r of the slice
         const int q = k / (64 * W1_UNITS), j = (k / W1_UNITS) & 63, r = k % W1_UNITS;
         gW1[((int64_t)(h0 / W1_UNITS + q) * N_IN + c * 64 + j) * W1_UNITS + r] = out[q * W1_UNITS + r][j];
     }

@@ -882,8 +882,8 @@ extern "C" wo_status wo_eval_plans(wo_wh *wh, const int64_t *plan_offsets, int64
     bool any_small = false;
     for (int32_t i = 0; i < wh->n_inst; i++) any_small |= class_of(wh, i) != 0 && map[i + 1] > map[i];
     if (wh->batching != WO_BATCH_NEXT_FIT) {
-        // first fit has a kernel of its own, one wavefront per plan; the
-        // launch configuration above applies to next fit only
+        // first fit and seed batching have a kernel of their own; the launch
+        // configuration above applies to next fit only
         HIP_TRY(launch_eval_ff(a, wh->ff_lds_max, ff_grid(wh, wh->ff_lds_max, n_plans), wh->route,
                                wh->ff_batch, s));
     } else if (!any_small && !wh->queue) {

@@ -155,7 +155,8 @@ constexpr int MAX_BIG_ORDER_LINES = WO_MAX_ROUTED_ORDER_LINES;
 __host__ __device__ inline uint32_t row_bytes(int32_t words) { return 4u * ((uint32_t)(words + 1) | 1u); }
 __host__ __device__ inline uint32_t pick_row_bytes(int32_t slots) { return 4u * ((uint32_t)(slots + 1) | 1u); }
 
-// First-fit batching runs in a kernel of its own, one wavefront per plan.
+// First fit and seed batching run in a kernel of their own, one wavefront per plan
+// (two under first fit by the S-shape route).
 // LDS: the zone starts (64 words), then one tile of tour rows (192 S-shape
 // rows, or 64 pick rows for the other routes); the tour of every order goes
 // to a global table with one slice per workgroup of the launch, and open
@@ -261,7 +262,8 @@ hipError_t launch_eval(const EvalArgs &a, uint32_t lds_bytes, int grid, int bloc
 // workgroups of the evaluation kernel that fit one CU (registers and LDS), for
 // instances of at most max_orders orders
 int eval_max_blocks_per_cu(int block, int route, uint32_t lds_bytes, int max_orders, int line_pass);
-// First-fit batching: one 64-thread workgroup per plan.
+// First fit and seed batching: one workgroup per plan, of 128 threads under first fit
+// by the S-shape route, else of 64.
 hipError_t launch_eval_ff(const EvalArgs &a, uint32_t lds_bytes, int grid, int route, int batch, hipStream_t s);
 int eval_ff_max_blocks_per_cu(int route, int batch, uint32_t lds_bytes);
 
