@@ -204,7 +204,7 @@ static constexpr int seq_cap(int block) { return block >= 256 ? 4096 : 16 * bloc
 // the 128-thread workgroups, with chunks of a size of their own, spill 37
 // registers at four and run in 61 us at three, 69 at four (their part of 128
 // uneven instances x 256 plans); with pick rows too, 2 to 10 registers spilt (3,732
-// plans of 1,366 orders by the optimal route 95 us, 116 at two).
+// plans of 1,366 orders by the optimal route 87 us, 107 at two).
 // LONG: instances of more than seq_cap(BLOCK) orders are among the launch's, an
 // instantiation of its own, so that the other carries none of its code (4,096
 // paper-scale plans 72.5 us with it, 71.5 without).

@@ -388,8 +388,8 @@ __global__ __launch_bounds__(UP_THREADS) void update_kernel(const double *X, con
 // the classes of each 64 orders, KG at a time, with one lane per order (weights
 // by scalar loads, a row's features from LDS at an odd stride), and the first of
 // these waves takes the best of their bests.  Four workgroups fit a CU, so that
-// some load while others multiply.  64 features, 8 classes: 8.3 us for 8,192
-// orders and 0.123 ms for 1M (4.4 TB/s of features), against 30 us and 0.194 ms
+// some load while others multiply.  64 features, 8 classes: 9 us for 8,192
+// orders and 0.104 ms for 1M (5.2 TB/s of features), against 30 us and 0.194 ms
 // when each wave streamed 64 orders of its own in chunks of 8 features for all
 // classes.
 template <int R, int KG>
